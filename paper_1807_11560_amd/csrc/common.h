@@ -41,6 +41,33 @@ struct Dims {
 int prod_rows_max(const Dims& d);
 
 // ---------------------------------------------------------------- tables
+// One table of k_tables (see there for the kinds): `total` elements at dst.
+enum TableKind {
+  TAB_INV = 0, TAB_INV_HALF = 1, TAB_FWD = 2, TAB_FWD_HALF = 3,  // plain
+  TAB_ROW_INV = 4, TAB_ROW_INV_HALF = 5,                         // fragment order, see mfma.h
+  TAB_PAIR_INV = 6, TAB_PAIR_INV_HALF = 7, TAB_PAIR_FWD = 8,
+  TAB_SYNTH1 = 9, TAB_SYNTH2 = 10, TAB_COL1 = 11, TAB_COL0 = 12, TAB_COL0_INV = 13,  // instantiated shapes
+  TAB_SYMBOLS = 14,                                              // L~ to dst, K~ to dst2 (K = K0, G = K1)
+  TAB_ZERO = 15                                                  // unsigned zeros
+};
+struct TableJob {
+  void* dst;
+  void* dst2;
+  int kind, K, G, total, s;
+  double alpha;
+};
+constexpr int kMaxTables = 32;
+struct TableJobs { TableJob j[kMaxTables]; };
+
+// Tables of one grid in fragment order (see mfma.h); null where a grid has no use for one.
+struct Frags {
+  const float4* row1;   // inverse axis 1 and axis 2
+  const float4* row2;
+  const float4* inv0;   // pairs: inverse axis 0, forward axes 0 and 1
+  const float4* fwd0;
+  const float4* fwd1;
+};
+
 // Twiddle tables for one transform direction set (grid G = M or N).
 struct Twiddles {
   const float2* inv0;  // [2][G0][K0]  exp(+2 pi i k x/G), variant 1 times 2 pi i k
@@ -96,12 +123,22 @@ struct ProdArgs {
   int nout, prog;
 };
 
-// Band-side step of one output component (k_colstep): forward stages 1 and
-// 0 of one or two product fields s1 ([Kh][M0][M1] each), the update
+// Synthesis of one or two groups (k_synth)
+struct SynthArgs {
+  const float2* t1[2];  // stage-0 output of group g: [3][2][M0][K1*Kh]
+  float* dst[2];        // fields of group g: [3][nM][4] (value, d0, d1, d2)
+  const float* w1a;     // [2][M1p][2K1]    real block form of the stage-1 twiddles
+  const float* w2b;     // [2][2Khp][M2p]   real block form of the stage-2 twiddles
+};
+
+// Band-side step of one output component (the column kernels): forward stages
+// 1 and 0 of one or two product fields s1 ([Kh][M0][M1] each), the update
 // out = base + ca*(K~ if syma)*F(a) + cb*(K~ if symb)*F(b) + ce*extra, the
 // inverse stage 0 of out (of L~ out where t1l) into up to two padded-grid
 // stage-0 buffers [2 vars][M0][Kh][K1] for the next step, and, if t1n is
-// set, the image-grid inverse stage 0 of out into t1n [N0][Kh][K1].
+// set, the image-grid inverse stage 0 of out into t1n [N0][Kh][K1].  Without
+// products (a null; k_column_chain only) the band values are the base, and out
+// may be null (nothing is stored).
 struct ColJob {
   const float2* a;
   const float2* b;
@@ -150,8 +187,7 @@ struct GridStepArgs {
 
 // ------------------------------------------------------- launch wrappers
 // Each returns hipSuccess or the launch error.
-hipError_t launch_twiddles(float2* dst, int K, int G, int mode, hipStream_t st);
-hipError_t launch_symbols(float* Lsym, float* Ksym, const Dims& d, hipStream_t st);
+hipError_t launch_tables(const TableJobs& jobs, int njobs, hipStream_t st);
 hipError_t launch_full_to_half(const float2* full, float2* half, const Dims& d, hipStream_t st);
 // full = expand(a + cb b), times the band symbol sym when given
 hipError_t launch_half_to_full(const float2* a, const float2* b, float cb, float2* full,
@@ -161,20 +197,26 @@ hipError_t launch_half_to_full(const float2* a, const float2* b, float cb, float
 // Output [nvar][G0][Kh][K1]; image_grid selects the timer family of the launch.
 hipError_t launch_inv0(const Inv0Jobs& jobs, int njobs, int nvar, const float2* tw, const float* Lsym,
                        int K0, int C, int G0, int Kh, bool image_grid, hipStream_t st);
-hipError_t launch_synth_tables(const Twiddles& tw, float* tables, const Dims& d, hipStream_t st);
+// Table jobs of the instantiated shapes' synthesis and column step; return their number.
+int synth_table_jobs(TableJob* j, float* tables, const Dims& d);
+int col_table_jobs(TableJob* j, float2* tab, const Dims& d);
 size_t synth_table_floats(const Dims& d);
 size_t synth_shared_bytes(const Dims& d);
 // Synthesis of group 0 and, when t1g1 is set, group 1.
 hipError_t launch_synth(const float2* t1g0, const float2* t1g1, float* dst0, float* dst1,
-                        const float* tables, const Dims& d, hipStream_t st);
+                        const float* tables, const Frags& fr, const Dims& d, hipStream_t st);
+// The shapes without instantiated kernels (chain.hip): nf new fields.
+hipError_t launch_synth_chain(const SynthArgs& a, int nf, const Frags& fr, const Dims& d, hipStream_t st);
+hipError_t launch_column_chain(const ColJobs& jobs, int njobs, const Dims& d, const Frags& frM, const Frags& frN,
+                               const float* Lsym, const float* Ksym, float invG, hipStream_t st);
 size_t prods_shared_bytes(const Dims& d, int nout);
 hipError_t launch_prods(const ProdArgs& a, const Dims& d, const Twiddles& tw, hipStream_t st);
 hipError_t launch_colstep(const ColJobs& jobs, int njobs, const Dims& d, const Twiddles& tw,
-                          const float2* coltab, const float* Lsym, const float* Ksym, hipStream_t st);
+                          const float2* coltab, const Frags& frM, const Frags& frN, const float* Lsym,
+                          const float* Ksym, hipStream_t st);
 size_t col_table_count(const Dims& d);
 // Whether the column kernel can form the image-grid stage 0 (t1n) for this shape.
 bool colstep_fuses_grid0(const Dims& d);
-hipError_t launch_col_tables(const Twiddles& tw, float2* tab, const Dims& d, hipStream_t st);
 size_t colstep_shared_bytes(const Dims& d);
 hipError_t launch_fwd1(const Fwd1Jobs& jobs, int njobs, const float2* tw, int G0, int G1, int K1,
                        int Kh, hipStream_t st);
@@ -283,6 +325,9 @@ enum KernelFamily {
 // launch, hands the kernel node of a sampled launch in a capture to the
 // timer.  Each timed launch calls the three in this order.
 void timer_work(int family, double flops, double bytes);
+inline int column_family(const ColJobs& jobs) {
+  return jobs.j[0].a ? KF_COLUMN : jobs.j[0].t1n ? KF_INV0_GRID : KF_INV0;
+}
 bool timer_events(int family, hipEvent_t* start, hipEvent_t* stop);
 void timer_captured(int family, hipStream_t st);
 

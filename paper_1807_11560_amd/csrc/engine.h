@@ -134,6 +134,7 @@ class Engine {
   hipError_t tail_def(const float* I1);
   hipError_t hessvec_def(const float2* dvh, float2* out);
   hipError_t hessvec_sweep(float2* out);
+  hipError_t inv0_pair(const float2* in0, int l0, const float2* in1, int l1, hipStream_t s);
   hipError_t inv0_group(const float2* in, int g, int lflag, hipStream_t s);
   hipError_t colstep_on(const ColJob* jobs, int n, hipStream_t s);
   hipError_t prods_on(int prog, const float* const* g, int ng, float2* out, hipStream_t s);
@@ -166,6 +167,8 @@ class Engine {
   float* dvg_ = nullptr;  // grid velocity increment of one step [3][nN] (exact product)
   float* synth_tab_ = nullptr;  // MFMA-form stage-1/2 twiddles of the padded grid
   float2* col_tab_ = nullptr;   // MFMA-form twiddles of the column step
+  float4* frag_ = nullptr;      // fragment tables of both grids
+  Frags frM_{}, frN_{};
 };
 
 }  // namespace lddmm

@@ -8,6 +8,7 @@
 // Fields of the trajectory that later sweeps reuse are cached on the padded
 // grid when they are first synthesised.
 #include "engine.h"
+#include "shapes.h"
 
 #include <algorithm>
 #include <map>
@@ -25,6 +26,16 @@ namespace {
 size_t twiddle_count(const int* G, const Dims& d) {
   return 2 * (size_t)G[0] * d.K[0] + 2 * (size_t)G[1] * d.K[1] + 2 * (size_t)G[2] * d.Kh +
          (size_t)d.K[0] * G[0] + (size_t)d.K[1] * G[1] + (size_t)d.Kh * G[2];
+}
+
+// float4 counts of the fragment tables (see mfma.h)
+int t16(int n) { return (n + 15) / 16; }
+size_t row_inv(int K, int G) { return (size_t)2 * t16(G) * t16(K) * 128; }
+size_t pair_inv(int K, int G) { return (size_t)2 * t16(G) * ((K + 7) / 8) * 64; }
+size_t pair_fwd(int K, int G) { return (size_t)t16(K) * ((G + 7) / 8) * 64; }
+size_t frag_count(const Dims& d) {
+  return row_inv(d.K[1], d.M[1]) + row_inv(d.Kh, d.M[2]) + pair_inv(d.K[0], d.M[0]) + pair_fwd(d.K[0], d.M[0]) +
+         pair_fwd(d.K[1], d.M[1]) + pair_inv(d.K[0], d.N[0]) / 2;
 }
 }  // namespace
 
@@ -130,12 +141,26 @@ void Engine::layout(Carver& c) {
   pcg = c.take<double>(SC_COUNT);
   Lsym = c.take<float>((size_t)d.nb);
   Ksym = c.take<float>((size_t)d.nb);
-  twbuf_ = c.take<float2>(twiddle_count(d.M, d) + twiddle_count(d.N, d));
+  {
+    // One region for the tables: those of the instantiated shapes, or the
+    // fragment tables in their place.  Never smaller than the former, so that
+    // the workspace of a problem (and with it what lddmm_shoot_static takes)
+    // does not depend on which kernels serve it.
+    auto tables = [&](Carver& r, bool inst) {
+      twbuf_ = r.take<float2>((inst ? twiddle_count(d.M, d) : (size_t)d.Kh * d.M[2]) + twiddle_count(d.N, d));
+      synth_tab_ = inst ? r.take<float>(synth_table_floats(d)) : nullptr;
+      col_tab_ = inst ? r.take<float2>(col_table_count(d)) : nullptr;
+      frag_ = inst ? nullptr : r.take<float4>(frag_count(d));
+    };
+    Carver a{nullptr}, b{nullptr};
+    tables(a, true);
+    tables(b, band_instantiated(d));
+    Carver r{c.take<char>(std::max(a.off, b.off))};
+    tables(r, band_instantiated(d));
+  }
   const size_t C = (size_t)d.K[1] * d.Kh;
   T1_ = c.take<float2>((def ? 4 : 2) * 3 * 2 * (size_t)d.M[0] * C);
   NG_ = c.take<float>(24 * (size_t)d.nM);
-  synth_tab_ = c.take<float>(synth_table_floats(d));
-  col_tab_ = c.take<float2>(col_table_count(d));
   S1_ = c.take<float2>(9 * (size_t)d.M[0] * d.M[1] * d.Kh);
   T1N.assign(def ? 0 : (ck ? 1 : nt), nullptr);
   for (auto& p : T1N) p = c.take<float2>(3 * (size_t)d.N[0] * C);
@@ -172,19 +197,31 @@ Engine::Engine(const Dims& d, void* ws, hipStream_t st)
     : d_(d), st_(st), fuse_grid0_(colstep_fuses_grid0(d) && d.ckpt == 0) {
   Carver c{static_cast<char*>(ws)};
   layout(c);
-  // twiddle table views
+  // table views (of the padded grid's plain tables only the last where its
+  // kernels read fragment tables)
+  const bool inst = band_instantiated(d);
   float2* t = twbuf_;
   for (int pass = 0; pass < 2; ++pass) {
     Twiddles& tw = pass == 0 ? twM_ : twN_;
     const int* G = pass == 0 ? d.M : d.N;
     for (int j = 0; j < 3; ++j) tw.G[j] = G[j];
-    tw.inv0 = t; t += 2 * (size_t)G[0] * d.K[0];
-    tw.inv1 = t; t += 2 * (size_t)G[1] * d.K[1];
-    tw.inv2 = t; t += 2 * (size_t)G[2] * d.Kh;
-    tw.fwd0 = t; t += (size_t)d.K[0] * G[0];
-    tw.fwd1 = t; t += (size_t)d.K[1] * G[1];
+    if (pass == 1 || inst) {
+      tw.inv0 = t; t += 2 * (size_t)G[0] * d.K[0];
+      tw.inv1 = t; t += 2 * (size_t)G[1] * d.K[1];
+      tw.inv2 = t; t += 2 * (size_t)G[2] * d.Kh;
+      tw.fwd0 = t; t += (size_t)d.K[0] * G[0];
+      tw.fwd1 = t; t += (size_t)d.K[1] * G[1];
+    }
     tw.fwd2 = t; t += (size_t)d.Kh * G[2];
   }
+  if (inst) return;
+  const float4* f = frag_;
+  frM_.row1 = f; f += row_inv(d.K[1], d.M[1]);
+  frM_.row2 = f; f += row_inv(d.Kh, d.M[2]);
+  frM_.inv0 = f; f += pair_inv(d.K[0], d.M[0]);
+  frM_.fwd0 = f; f += pair_fwd(d.K[0], d.M[0]);
+  frM_.fwd1 = f; f += pair_fwd(d.K[1], d.M[1]);
+  frN_.inv0 = f;
 }
 
 size_t Engine::workspace_bytes(const Dims& d) {
@@ -195,20 +232,41 @@ size_t Engine::workspace_bytes(const Dims& d) {
 }
 
 hipError_t Engine::init_tables() {
+  TableJobs jobs{};
+  int n = 0;
+  auto add = [&](const void* dst, int kind, int K, int G, size_t total) {
+    jobs.j[n] = TableJob{const_cast<void*>(dst), nullptr, kind, K, G, (int)total, d_.s, d_.alpha};
+    ++n;
+  };
+  const int* K = d_.K;
+  const bool inst = band_instantiated(d_);
   for (int pass = 0; pass < 2; ++pass) {
     const Twiddles& tw = pass == 0 ? twM_ : twN_;
     const int* G = tw.G;
-    TRY(launch_twiddles(const_cast<float2*>(tw.inv0), d_.K[0], G[0], 0, st_));
-    TRY(launch_twiddles(const_cast<float2*>(tw.inv1), d_.K[1], G[1], 0, st_));
-    TRY(launch_twiddles(const_cast<float2*>(tw.inv2), d_.K[2], G[2], 1, st_));
-    TRY(launch_twiddles(const_cast<float2*>(tw.fwd0), d_.K[0], G[0], 2, st_));
-    TRY(launch_twiddles(const_cast<float2*>(tw.fwd1), d_.K[1], G[1], 2, st_));
-    TRY(launch_twiddles(const_cast<float2*>(tw.fwd2), d_.K[2], G[2], 3, st_));
+    if (pass == 1 || inst) add(tw.inv0, TAB_INV, K[0], G[0], 2 * (size_t)G[0] * K[0]);
+    if (pass == 1) {
+      add(tw.inv1, TAB_INV, K[1], G[1], 2 * (size_t)G[1] * K[1]);
+      add(tw.inv2, TAB_INV_HALF, K[2], G[2], 2 * (size_t)G[2] * d_.Kh);
+      add(tw.fwd0, TAB_FWD, K[0], G[0], (size_t)K[0] * G[0]);
+      add(tw.fwd1, TAB_FWD, K[1], G[1], (size_t)K[1] * G[1]);
+    }
+    add(tw.fwd2, TAB_FWD_HALF, K[2], G[2], (size_t)d_.Kh * G[2]);
   }
-  TRY(launch_fill(reinterpret_cast<float*>(count), 64, 0.f, st_));
-  TRY(launch_synth_tables(twM_, synth_tab_, d_, st_));
-  TRY(launch_col_tables(twM_, col_tab_, d_, st_));
-  return launch_symbols(Lsym, Ksym, d_, st_);
+  if (inst) {
+    n += synth_table_jobs(jobs.j + n, synth_tab_, d_);
+    n += col_table_jobs(jobs.j + n, col_tab_, d_);
+  } else {
+    add(frM_.row1, TAB_ROW_INV, K[1], d_.M[1], 4 * row_inv(K[1], d_.M[1]));
+    add(frM_.row2, TAB_ROW_INV_HALF, d_.Kh, d_.M[2], 4 * row_inv(d_.Kh, d_.M[2]));
+    add(frM_.inv0, TAB_PAIR_INV, K[0], d_.M[0], 4 * pair_inv(K[0], d_.M[0]));
+    add(frM_.fwd0, TAB_PAIR_FWD, K[0], d_.M[0], 4 * pair_fwd(K[0], d_.M[0]));
+    add(frM_.fwd1, TAB_PAIR_FWD, K[1], d_.M[1], 4 * pair_fwd(K[1], d_.M[1]));
+    add(frN_.inv0, TAB_PAIR_INV, K[0], d_.N[0], 2 * pair_inv(K[0], d_.N[0]));
+  }
+  add(count, TAB_ZERO, 0, 0, 64);
+  add(Lsym, TAB_SYMBOLS, K[0], K[1], d_.nb);
+  jobs.j[n - 1].dst2 = Ksym;
+  return launch_tables(jobs, n, st_);
 }
 
 hipError_t Engine::load_band(const void* full, float2* half) {
@@ -228,19 +286,35 @@ const float2* Engine::s1(int o) const { return S1_ + (size_t)o * d_.Kh * d_.M[0]
 // Inverse stage 0 of the new groups of a step (at the start of a sweep;
 // later steps get it from the column kernel of the previous step).
 hipError_t Engine::inv0_groups(const float2* in0, int l0, const float2* in1, int l1) {
-  const int C = d_.K[1] * d_.Kh;
-  Inv0Jobs jobs{};
-  int nj = 0;
+  return inv0_pair(in0, l0, in1, l1, st_);
+}
+
+// Padded-grid stage 0 of in0 into group 0 and of in1 (when given) into group 1.
+hipError_t Engine::inv0_pair(const float2* in0, int l0, const float2* in1, int l1, hipStream_t s) {
   const float2* ins[2] = {in0, in1};
   const int lf[2] = {l0, l1};
-  for (int g = 0; g < 2; ++g)
+  if (!band_instantiated(d_)) {
+    ColJob jobs[6];
+    int nj = 0;
+    for (int g = 0; g < (in1 ? 2 : 1); ++g)
+      for (int c = 0; c < 3; ++c) {
+        ColJob& j = (g == 1 && in1 == in0) ? jobs[c] : (jobs[nj++] = ColJob{});
+        j.base = ins[g] + (size_t)c * d_.nb;
+        j.t1[j.nt1] = t1(g, c);
+        j.t1l[j.nt1++] = lf[g];
+      }
+    return colstep_on(jobs, nj, s);
+  }
+  Inv0Jobs jobs{};
+  int nj = 0;
+  for (int g = 0; g < (in1 ? 2 : 1); ++g)
     for (int c = 0; c < 3; ++c) {
       jobs.j[nj].in = ins[g] + (size_t)c * d_.nb;
       jobs.j[nj].out = t1(g, c);
       jobs.j[nj].lflag = lf[g];
       ++nj;
     }
-  return launch_inv0(jobs, nj, 2, twM_.inv0, Lsym, d_.K[0], C, d_.M[0], d_.Kh, false, st_);
+  return launch_inv0(jobs, nj, 2, twM_.inv0, Lsym, d_.K[0], d_.K[1] * d_.Kh, d_.M[0], d_.Kh, false, s);
 }
 
 // Synthesis of the two new groups (into the cache when given, else into
@@ -249,7 +323,7 @@ hipError_t Engine::mstep(int prog, int nout, float* store0, float* store1, const
   const size_t nM = (size_t)d_.nM;
   float* g0 = store0 ? store0 : NG_;
   float* g1 = store1 ? store1 : NG_ + 12 * nM;
-  TRY(launch_synth(t1(0, 0), t1(1, 0), g0, g1, synth_tab_, d_, st_));
+  TRY(launch_synth(t1(0, 0), t1(1, 0), g0, g1, synth_tab_, frM_, d_, st_));
   if (nout == 0) return hipSuccess;
   ProdArgs a{};
   a.g[0] = g0;
@@ -294,7 +368,7 @@ hipError_t Engine::colstep_on(const ColJob* jobs, int n, hipStream_t s) {
   for (int i = 0; i < n; ++i) js.j[i] = jobs[i];
   js.w0n = twN_.inv0;  // value variant [N0][K0]
   js.N0 = d_.N[0];
-  return launch_colstep(js, n, d_, twM_, col_tab_, Lsym, Ksym, s);
+  return launch_colstep(js, n, d_, twM_, col_tab_, frM_, frN_, Lsym, Ksym, s);
 }
 
 // Forward stages 1 and 0 of the three grid fields in S1N with the given
@@ -318,14 +392,22 @@ const float2* Engine::s2n(int o) const { return S2N_ + (size_t)o * d_.N[0] * d_.
 
 // Image-grid inverse stage 0 of one band field into t1n [3][N0][Kh][K1].
 hipError_t Engine::grid_stage0(const float2* band, float2* t1n, hipStream_t s) {
-  const int C = d_.K[1] * d_.Kh;
+  const size_t n = (size_t)d_.N[0] * d_.K[1] * d_.Kh;
+  if (!band_instantiated(d_)) {
+    ColJob jobs[3] = {};
+    for (int c = 0; c < 3; ++c) {
+      jobs[c].base = band + (size_t)c * d_.nb;
+      jobs[c].t1n = t1n + c * n;
+    }
+    return colstep_on(jobs, 3, s);
+  }
   Inv0Jobs jobs{};
   for (int c = 0; c < 3; ++c) {
     jobs.j[c].in = band + (size_t)c * d_.nb;
-    jobs.j[c].out = t1n + (size_t)c * d_.N[0] * C;
+    jobs.j[c].out = t1n + c * n;
     jobs.j[c].lflag = 0;
   }
-  return launch_inv0(jobs, 3, 1, twN_.inv0, Lsym, d_.K[0], C, d_.N[0], d_.Kh, true, s);
+  return launch_inv0(jobs, 3, 1, twN_.inv0, Lsym, d_.K[0], d_.K[1] * d_.Kh, d_.N[0], d_.Kh, true, s);
 }
 
 // Stage-0 buffer of the grid step of time step n: formed by the column
@@ -384,18 +466,7 @@ hipError_t Engine::tail(const float* a, const float* b, const float* r, float co
     fj[c].out = out + (size_t)c * d_.nb;
   }
   TRY(fwd_grid(fj, 3, s));
-  const int C = d_.K[1] * d_.Kh;
-  Inv0Jobs jobs{};
-  int nj = 0;
-  const float2* ins[2] = {out, zero_band};
-  for (int g = 0; g < 2; ++g)
-    for (int c = 0; c < 3; ++c) {
-      jobs.j[nj].in = ins[g] + (size_t)c * d_.nb;
-      jobs.j[nj].out = t1(g, c);
-      jobs.j[nj].lflag = g == 0;
-      ++nj;
-    }
-  return launch_inv0(jobs, nj, 2, twM_.inv0, Lsym, d_.K[0], C, d_.M[0], d_.Kh, false, s);
+  return inv0_pair(out, 1, zero_band, 0, s);
 }
 
 hipError_t Engine::shoot_band(bool cache, const StepHook& hook) {
@@ -791,7 +862,7 @@ hipError_t Engine::adjoint_exact(int cur) {
   TRY(launch_fill(reinterpret_cast<float*>(W[nt]), 6LL * d_.nb, 0.f, st_));
   TRY(inv0_group(W[nt], 0, 0, st_));
   for (int n = nt - 1; n >= 0; --n) {
-    TRY(launch_synth(t1(0, 0), nullptr, NG_, nullptr, synth_tab_, d_, st_));
+    TRY(launch_synth(t1(0, 0), nullptr, NG_, nullptr, synth_tab_, frM_, d_, st_));
     ProdArgs a{};
     a.g[0] = NG_;
     a.g[1] = VG[n];
@@ -814,14 +885,23 @@ hipError_t Engine::adjoint_exact(int cur) {
 // to rho~ / drho~ at t = 1; groups 0 and 1 stay with the main chain.
 
 hipError_t Engine::inv0_group(const float2* in, int g, int lflag, hipStream_t s) {
-  const int C = d_.K[1] * d_.Kh;
+  if (!band_instantiated(d_)) {
+    ColJob jobs[3] = {};
+    for (int c = 0; c < 3; ++c) {
+      jobs[c].base = in + (size_t)c * d_.nb;
+      jobs[c].t1[0] = t1(g, c);
+      jobs[c].t1l[0] = lflag;
+      jobs[c].nt1 = 1;
+    }
+    return colstep_on(jobs, 3, s);
+  }
   Inv0Jobs jobs{};
   for (int c = 0; c < 3; ++c) {
     jobs.j[c].in = in + (size_t)c * d_.nb;
     jobs.j[c].out = t1(g, c);
     jobs.j[c].lflag = lflag;
   }
-  return launch_inv0(jobs, 3, 2, twM_.inv0, Lsym, d_.K[0], C, d_.M[0], d_.Kh, false, s);
+  return launch_inv0(jobs, 3, 2, twM_.inv0, Lsym, d_.K[0], d_.K[1] * d_.Kh, d_.M[0], d_.Kh, false, s);
 }
 
 hipError_t Engine::prods_on(int prog, const float* const* g, int ng, float2* out, hipStream_t s) {
@@ -893,7 +973,7 @@ hipError_t Engine::forward_def(const float* I0) {
       TRY(launch_axpy_band(Phi[0], V[0], -dt, Phi[1], 3 * d_.nb, aux_));
       return inv0_group(Phi[1], 2, 0, aux_);
     }
-    TRY(launch_synth(t1(2, 0), nullptr, PG[k], nullptr, synth_tab_, d_, aux_));
+    TRY(launch_synth(t1(2, 0), nullptr, PG[k], nullptr, synth_tab_, frM_, d_, aux_));
     const float* g[2] = {PG[k], VG[k]};
     TRY(prods_on(PROG_DEF_FWD, g, 2, S1A_, aux_));
     const bool last = k + 1 == nt;
@@ -926,7 +1006,7 @@ hipError_t Engine::tail_def(const float* I1) {
   TRY(launch_rho_fwd2(ra, S1N_, d_, twN_, st_));
   TRY(band_pair(R, KR, st_));
   TRY(inv0_group(R, 3, 0, st_));
-  TRY(launch_synth(t1(2, 0), t1(3, 0), PG[nt], RG, synth_tab_, d_, st_));
+  TRY(launch_synth(t1(2, 0), t1(3, 0), PG[nt], RG, synth_tab_, frM_, d_, st_));
   const float* g[2] = {PG[nt], RG};
   return def_head(PROG_DEF_TAIL, g, 2, KR, U[nt]);
 }
@@ -951,7 +1031,7 @@ hipError_t Engine::hessvec_def(const float2* dvh, float2* out) {
       TRY(launch_axpy_band(Phi[0], dV[0], -dt, dPhi[0], 3 * d_.nb, aux_));
       return inv0_group(dPhi[0], 2, 0, aux_);
     }
-    TRY(launch_synth(t1(2, 0), nullptr, NGA_, nullptr, synth_tab_, d_, aux_));
+    TRY(launch_synth(t1(2, 0), nullptr, NGA_, nullptr, synth_tab_, frM_, d_, aux_));
     const float* g[4] = {NGA_, VG[k], PG[k], dVG[k]};
     TRY(prods_on(PROG_DEF_H, g, 4, S1A_, aux_));
     const bool last = k + 1 == nt;
@@ -999,11 +1079,11 @@ hipError_t Engine::hessvec_def(const float2* dvh, float2* out) {
   // dU_nt = K~ drho~ + K~ ((D~u_nt)^T * drho~ [+ (D~du_nt)^T * rho~, full Newton])
   TRY(launch_fill(reinterpret_cast<float*>(dW[0]), 6LL * d_.nb, 0.f, st_));
   if (d_.hessian != 2) {
-    TRY(launch_synth(t1(3, 0), nullptr, NGA_, nullptr, synth_tab_, d_, st_));
+    TRY(launch_synth(t1(3, 0), nullptr, NGA_, nullptr, synth_tab_, frM_, d_, st_));
     const float* g[2] = {PG[nt], NGA_};
     TRY(def_head(PROG_DEF_TAIL, g, 2, KdR, dU[0]));
   } else {
-    TRY(launch_synth(t1(2, 0), t1(3, 0), NGA_, NGA_ + 12 * nM, synth_tab_, d_, st_));
+    TRY(launch_synth(t1(2, 0), t1(3, 0), NGA_, NGA_ + 12 * nM, synth_tab_, frM_, d_, st_));
     const float* g[4] = {NGA_, NGA_ + 12 * nM, PG[nt], RG};
     TRY(def_head(PROG_DEF_HTAIL, g, 4, KdR, dU[0]));
   }

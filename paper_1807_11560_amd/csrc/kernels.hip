@@ -7,14 +7,15 @@
 // (paper §3.1) is evaluated on the padded grid M >= 3K/2 - 2 where it is
 // alias-free on the band.  Partial derivatives are folded into the twiddle
 // tables of the axis they act on.
-#include "common.h"
-
-#include <hip/hip_ext.h>
+#include "mfma.h"
 
 #include <math.h>
 
 #include <algorithm>
 #include <type_traits>
+
+#include "launch.h"
+#include "shapes.h"
 
 namespace lddmm {
 
@@ -84,110 +85,6 @@ __device__ __forceinline__ void st4(float2* p, float4 v) { *reinterpret_cast<flo
 __device__ __forceinline__ void st22(float2* p, float4 v) {
   p[0] = make_float2(v.x, v.y);
   p[1] = make_float2(v.z, v.w);
-}
-
-// ---------------------------------------------------------------- shapes
-// Sizes seen by a kernel: compile-time for the shapes this library is tuned
-// for (index arithmetic then folds into constants), runtime otherwise.
-struct BandDyn {
-  static constexpr bool kStatic = false;
-  int k0, k1, kh, m0, m1, m2;
-  __device__ __forceinline__ int K0() const { return k0; }
-  __device__ __forceinline__ int K1() const { return k1; }
-  __device__ __forceinline__ int Kh() const { return kh; }
-  __device__ __forceinline__ int M0() const { return m0; }
-  __device__ __forceinline__ int M1() const { return m1; }
-  __device__ __forceinline__ int M2() const { return m2; }
-};
-template <int K, int M>
-struct BandIso {
-  static constexpr bool kStatic = true;
-  __device__ static constexpr int K0() { return K; }
-  __device__ static constexpr int K1() { return K; }
-  __device__ static constexpr int Kh() { return K / 2; }
-  __device__ static constexpr int M0() { return M; }
-  __device__ static constexpr int M1() { return M; }
-  __device__ static constexpr int M2() { return M; }
-};
-struct GridDyn {
-  static constexpr bool kStatic = false;
-  int n0, n1, n2, k1, kh;
-  __device__ __forceinline__ int N0() const { return n0; }
-  __device__ __forceinline__ int N1() const { return n1; }
-  __device__ __forceinline__ int N2() const { return n2; }
-  __device__ __forceinline__ int K1() const { return k1; }
-  __device__ __forceinline__ int Kh() const { return kh; }
-};
-template <int A, int B, int C, int K>
-struct GridShape {
-  static constexpr bool kStatic = true;
-  __device__ static constexpr int N0() { return A; }
-  __device__ static constexpr int N1() { return B; }
-  __device__ static constexpr int N2() { return C; }
-  __device__ static constexpr int K1() { return K; }
-  __device__ static constexpr int Kh() { return K / 2; }
-};
-template <int N, int K>
-using GridIso = GridShape<N, N, N, K>;
-
-// ------------------------------------------------------------- tables
-// mode 0: inverse, full axis  [2][G][K]
-// mode 1: inverse, half axis  [2][G][K/2], weight 1 at k = 0 else 2
-// mode 2: forward, full axis  [K][G]
-// mode 3: forward, half axis  [K/2][G]
-__global__ void k_twiddles(float2* dst, int K, int G, int mode) {
-  const int Kq = (mode == 1 || mode == 3) ? K / 2 : K;
-  const int total = (mode <= 1) ? 2 * G * Kq : Kq * G;
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  int v = 0, x, q;
-  if (mode <= 1) {
-    v = i / (G * Kq);
-    x = (i / Kq) % G;
-    q = i % Kq;
-  } else {
-    q = i / G;
-    x = i % G;
-  }
-  const bool half = (mode == 1 || mode == 3);
-  const int k = half ? q : (q < K / 2 ? q : q - K);
-  if (!half && q == K / 2) { dst[i] = make_float2(0.f, 0.f); return; }
-  long long r = ((long long)k * x) % G;
-  if (r < 0) r += G;
-  double s, c;
-  sincospi(2.0 * (double)r / (double)G, &s, &c);
-  double re = c, im = (mode >= 2) ? -s : s;
-  if (mode <= 1 && v == 1) {  // times 2 pi i k
-    const double w = 2.0 * M_PI * (double)k;
-    const double nre = -w * im, nim = w * re;
-    re = nre;
-    im = nim;
-  }
-  if (mode == 1 && q > 0) { re *= 2.0; im *= 2.0; }
-  dst[i] = make_float2((float)re, (float)im);
-}
-
-// L~ and K~ = 1 / L~ at the band slot (q0, q1, k2) (FP64, rounded once);
-// kernels that need a few symbols per thread form them here instead of
-// loading them from the tables.
-__device__ __forceinline__ float2 band_symbols(int q0, int q1, int k2, int K0, int K1, int s, double alpha) {
-  const int k0 = q0 < K0 / 2 ? q0 : q0 - K0;
-  const int k1 = q1 < K1 / 2 ? q1 : q1 - K1;
-  const double tp = 2.0 * M_PI;
-  const double lap = tp * tp * ((double)k0 * k0 + (double)k1 * k1 + (double)k2 * k2);
-  const double base = 1.0 + alpha * lap;
-  double L = 1.0;
-  for (int e = 0; e < s; ++e) L *= base;
-  return make_float2((float)L, (float)(1.0 / L));
-}
-
-__global__ void k_symbols(float* Lsym, float* Ksym, int K0, int K1, int Kh, int s, double alpha) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= K0 * K1 * Kh) return;
-  // band layout [Kh][K0][K1]
-  const float2 lk = band_symbols((i / K1) % K0, i % K1, i / (K0 * K1), K0, K1, s, alpha);
-  Lsym[i] = lk.x;
-  Ksym[i] = lk.y;
 }
 
 // ------------------------------------------------------- layout changes
@@ -361,50 +258,6 @@ __device__ __forceinline__ void jact_acc(float* o, const float* ja, const float*
 // (stage-1 derivative table) and d/dx0 (stage-0 derivative input).  The
 // four results go to the group's field array [3][nM][4]: per component and
 // padded-grid point (value, d/dx0, d/dx1, d/dx2).
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef short shortx4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-
-// Compensated BF16 products on the matrix cores (precision LDDMM_FP32_BF16X3):
-// each FP32 operand x is split as hi = bf16(x), lo = bf16(x - hi) (round to
-// nearest even both times), and a b is formed as ah bh + ah bl + al bh with
-// FP32 accumulation; the dropped al bl is about 2^-16 of a b.  One FP32
-// k-step of v_mfma_f32_16x16x4f32 becomes one v_mfma_f32_16x16x16_bf16 whose
-// four k slots per lane hold the three terms and a zero: the A operand
-// (ah, ah, al, 0), the B operand (bh, bl, bh, 0).  Both operands index k
-// by (lane / 16, slot) alike, so the slot order only has to pair the terms.
-__device__ __forceinline__ shortx4 bf3_a(float x) {
-  const __bf16 h = (__bf16)x;
-  const __bf16 l = (__bf16)(x - (float)h);
-  const bf16x4 v = {h, h, l, (__bf16)0.f};
-  return __builtin_bit_cast(shortx4, v);
-}
-__device__ __forceinline__ shortx4 bf3_b(float x) {
-  const __bf16 h = (__bf16)x;
-  const __bf16 l = (__bf16)(x - (float)h);
-  const bf16x4 v = {h, l, h, (__bf16)0.f};
-  return __builtin_bit_cast(shortx4, v);
-}
-__device__ __forceinline__ floatx4 mma_bf3(shortx4 a, shortx4 b, floatx4 acc) {
-  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
-}
-// acc += a b over one k-step of a 16x16 tile (lane layout of
-// v_mfma_f32_16x16x4f32: A[row = lane % 16][k = lane / 16], B[k][col = lane % 16]).
-template <bool BF3>
-__device__ __forceinline__ floatx4 mma(float a, float b, floatx4 acc) {
-  if constexpr (BF3)
-    return mma_bf3(bf3_a(a), bf3_b(b), acc);
-  else
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
-}
-
-struct SynthArgs {
-  const float2* t1[2];  // stage-0 output of group g: [3][2][M0][K1*Kh]
-  float* dst[2];        // fields of group g: [3][nM][4] (value, d0, d1, d2)
-  const float* w1a;     // [2][M1p][2K1]    real block form of the stage-1 twiddles
-  const float* w2b;     // [2][2Khp][M2p]   real block form of the stage-2 twiddles
-};
-
 constexpr int kSynthW2Pre = 16;
 constexpr int kSynthT = 3;  // tiles a wave computes together
 template <class S, bool BF3>
@@ -447,8 +300,7 @@ __global__ void __launch_bounds__(256) k_synth(SynthArgs a, S sh) {
   };
   // stage-1 table rows of this tile: w1a [2][M1p][K2r]
   const float* w1rows = a.w1a + (size_t)rt * 16 * K2r;
-  const size_t w1var = (size_t)M1p * K2r;
-  if constexpr (S::kStatic) {
+  {
     // the loads of GEMM1's operands in flight at once, four floats per load
     constexpr int sM1p = (S::M1() + 15) & ~15, sK1 = S::K1(), sKh = S::Kh(), sKhp = (sKh + 7) & ~7;
     constexpr int sK2r = 2 * sK1, KP = sK1 / 2, R4 = sK2r / 4;
@@ -479,21 +331,6 @@ __global__ void __launch_bounds__(256) k_synth(SynthArgs a, S sh) {
       if (kh >= sKh) v = make_float4(0.f, 0.f, 0.f, 0.f);
       put_t1(vs, k1, kh, make_float2(v.x, v.y));
       put_t1(vs, k1 + 1, kh, make_float2(v.z, v.w));
-    });
-  } else {
-    batched_fill<float>(2 * 16 * K2r, [&](int i) {
-      const int vv = i / (16 * K2r), row = (i / K2r) % 16, k = i % K2r;
-      return w1rows[vv * w1var + (size_t)row * K2r + k];
-    }, [&](int i, float v) {
-      const int vv = i / (16 * K2r), row = (i / K2r) % 16, k = i % K2r;
-      w1s[((size_t)vv * 16 + row) * lda1 + k] = v;
-    });
-    batched_fill<float2>(2 * K1 * Khp, [&](int i) {
-      int vs = i / (K1 * Khp), k1 = (i / Khp) % K1, kh = i % Khp;
-      return (kh < Kh) ? src[((size_t)vs * M0 + x0) * C + (size_t)kh * K1 + k1] : make_float2(0.f, 0.f);
-    }, [&](int i, float2 t) {
-      int vs = i / (K1 * Khp), k1 = (i / Khp) % K1, kh = i % Khp;
-      put_t1(vs, k1, kh, t);
     });
   }
   __syncthreads();
@@ -605,33 +442,6 @@ __global__ void __launch_bounds__(256) k_synth(SynthArgs a, S sh) {
         *reinterpret_cast<float4*>(out + 4 * (((long long)x0 * M1 + x1) * M2 + x2)) =
             make_float4(acc[0][r], acc[3][r], acc[2][r], acc[1][r]);
     }
-  }
-}
-
-// MFMA-friendly real forms of the stage-1 and stage-2 inverse twiddles.
-__global__ void k_synth_tables(const float2* inv1, const float2* inv2, float* w1a, float* w2b, int M1,
-                               int M2, int K1, int Kh, int M1p, int M2p, int Khp) {
-  const int n1 = 2 * M1p * 2 * K1;
-  const int n2 = 2 * 2 * Khp * M2p;
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n1) {
-    int v = i / (M1p * 2 * K1), row = (i / (2 * K1)) % M1p, k = i % (2 * K1);
-    float val = 0.f;
-    if (row < M1) {
-      float2 w = inv1[((size_t)v * M1 + row) * K1 + (k < K1 ? k : k - K1)];
-      val = (k < K1) ? w.x : -w.y;
-    }
-    w1a[i] = val;
-  } else if (i < n1 + n2) {
-    int e = i - n1;
-    int v = e / (2 * Khp * M2p), j = (e / M2p) % (2 * Khp), x2 = e % M2p;
-    int kh = (j < Khp) ? j : j - Khp;
-    float val = 0.f;
-    if (x2 < M2 && kh < Kh) {
-      float2 w = inv2[((size_t)v * M2 + x2) * Kh + kh];
-      val = (j < Khp) ? w.x : -w.y;
-    }
-    w2b[e] = val;
   }
 }
 
@@ -838,126 +648,6 @@ __global__ void __launch_bounds__(256) k_prods(ProdArgs a, Twiddles tw, S sh, in
   }
 }
 
-// --------------------------------------- column step on the band side
-// One block per (job, kh, group of KG k1 values): forward stage 1 (x1 -> k1)
-// and stage 0 (x0 -> k0) of the job's one or two product fields at this kh,
-// the band update out = base + ca S_a F(a) + cb S_b F(b) + ce extra (S = K~
-// or 1), and the next step's inverse stage 0 (k0 -> x0, value and d0
-// variants, optionally of L~ out) for the same columns.
-template <int KG, class S>
-__global__ void __launch_bounds__(256) k_colstep(ColJobs jobs, Twiddles tw, const float* __restrict__ Lsym,
-                                                 const float* __restrict__ Ksym, S sh, float invG, int xsz,
-                                                 int stage_w0) {
-  extern __shared__ float2 shc[];
-  const int M0 = sh.M0(), M1 = sh.M1(), K0 = sh.K0(), K1 = sh.K1(), Kh = sh.Kh();
-  const ColJob job = jobs.j[blockIdx.z];
-  const int kh = blockIdx.y;
-  const int kb = blockIdx.x * KG;
-  const int C = K1 * Kh;
-  const int nterm = job.b ? 2 : 1;
-  // region X: one S1 slice at a time (and later the inverse twiddles, when
-  // they fit; else phase 3 reads them from global memory); region Y: the rest
-  float2* sx = shc;                       // [M0][M1]
-  float2* w0s = shc;                      // [2][M0][K0] (phase 3, when staged)
-  float2* wf1 = shc + xsz;                // [KG][M1]
-  float2* s2 = wf1 + KG * M1;             // [2][M0][KG]
-  float2* wf0 = s2 + 2 * M0 * KG;         // [K0][M0]
-  float2* bnd = wf0 + K0 * M0;            // [2][K0][KG]  (out, L~ out)
-
-  batched_fill<float2>(KG * M1, [&](int i) {
-    int kk = i / M1, x = i % M1;
-    int k1 = kb + kk;
-    return (k1 < K1) ? tw.fwd1[(size_t)k1 * M1 + x] : make_float2(0.f, 0.f);
-  }, [&](int i, float2 v) { wf1[i] = v; });
-  batched_fill<float2>(K0 * M0, [&](int i) { return tw.fwd0[i]; }, [&](int i, float2 v) { wf0[i] = v; });
-  // stage 1', one term at a time: s2[t][x0][kk] = sum_x1 wf1[kk][x1] S[t][x0][x1]
-  for (int t = 0; t < nterm; ++t) {
-    const float2* src = (t ? job.b : job.a) + (size_t)kh * M0 * M1;
-    if (t) __syncthreads();  // the previous slice has been consumed
-    batched_fill<float2>(M0 * M1, [&](int i) { return src[i]; }, [&](int i, float2 v) { sx[i] = v; });
-    __syncthreads();
-    for (int i = threadIdx.x; i < M0 * KG; i += blockDim.x) {
-      int x0 = i / KG, kk = i % KG;
-      const float2* row = sx + (size_t)x0 * M1;
-      const float2* w = wf1 + (size_t)kk * M1;
-      float2 acc = make_float2(0.f, 0.f);
-      for (int x = 0; x < M1; ++x) cmac(acc, w[x], row[x]);
-      s2[(size_t)t * M0 * KG + i] = acc;
-    }
-  }
-  __syncthreads();
-  // stage 0' + band update
-  for (int i = threadIdx.x; i < K0 * KG; i += blockDim.x) {
-    int k0 = i / KG, kk = i % KG;
-    int k1 = kb + kk;
-    float2 res = make_float2(0.f, 0.f);
-    if (k1 < K1 && k0 != K0 / 2 && k1 != K1 / 2) {
-      const size_t idx = ((size_t)kh * K0 + k0) * K1 + k1;
-      float2 fa = make_float2(0.f, 0.f), fb = make_float2(0.f, 0.f);
-      const float2* w = wf0 + (size_t)k0 * M0;
-      for (int x0 = 0; x0 < M0; ++x0) cmac(fa, w[x0], s2[(size_t)x0 * KG + kk]);
-      if (nterm == 2)
-        for (int x0 = 0; x0 < M0; ++x0) cmac(fb, w[x0], s2[((size_t)M0 + x0) * KG + kk]);
-      if (job.base) res = job.base[idx];
-      const float ks = Ksym[idx];
-      const float sa = job.ca * invG * (job.syma ? ks : 1.f);
-      res.x = fmaf(sa, fa.x, res.x);
-      res.y = fmaf(sa, fa.y, res.y);
-      if (nterm == 2) {
-        const float sb = job.cb * invG * (job.symb ? ks : 1.f);
-        res.x = fmaf(sb, fb.x, res.x);
-        res.y = fmaf(sb, fb.y, res.y);
-      }
-      if (job.extra) {
-        const float2 e = job.extra[idx];
-        res.x = fmaf(job.ce, e.x, res.x);
-        res.y = fmaf(job.ce, e.y, res.y);
-      }
-    }
-    if (k1 < K1) job.out[((size_t)kh * K0 + k0) * K1 + k1] = res;
-    bnd[i] = res;
-    float l = (k1 < K1) ? Lsym[((size_t)kh * K0 + k0) * K1 + k1] : 0.f;
-    bnd[K0 * KG + i] = make_float2(l * res.x, l * res.y);
-  }
-  if (job.nt1 == 0 && !job.t1n) return;
-  __syncthreads();
-  if (job.t1n) {
-    // image-grid stage 0 of out: t1n[x0][kh][k1] = sum_k0 w0n[x0][k0] out[k0][k1]
-    const int N0 = jobs.N0;
-    for (int i = threadIdx.x; i < N0 * KG; i += blockDim.x) {
-      const int x0 = i / KG, kk = i % KG, k1 = kb + kk;
-      if (k1 >= K1) continue;
-      const float2* w = jobs.w0n + (size_t)x0 * K0;
-      float2 acc = make_float2(0.f, 0.f);
-      for (int k0 = 0; k0 < K0; ++k0) cmac(acc, w[k0], bnd[(size_t)k0 * KG + kk]);
-      job.t1n[((size_t)x0 * Kh + kh) * K1 + k1] = acc;
-    }
-  }
-  if (job.nt1 == 0) return;
-  const float2* w0t = tw.inv0;
-  if (stage_w0) {
-    batched_fill<float2>(2 * M0 * K0, [&](int i) { return tw.inv0[i]; }, [&](int i, float2 v) { w0s[i] = v; });
-    w0t = w0s;
-  }
-  __syncthreads();
-  // next inverse stage 0: t1[v][x0][k1][kh] = sum_k0 w0[v][x0][k0] b[k0]
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    if (u >= job.nt1) break;
-    const float2* bsrc = bnd + ((u == 0 ? job.t1l[0] : job.t1l[1]) ? K0 * KG : 0);
-    float2* dst = (u == 0) ? job.t1[0] : job.t1[1];
-    for (int i = threadIdx.x; i < 2 * M0 * KG; i += blockDim.x) {
-      int v = i / (M0 * KG), x0 = (i / KG) % M0, kk = i % KG;
-      int k1 = kb + kk;
-      if (k1 >= K1) continue;
-      const float2* w = w0t + ((size_t)v * M0 + x0) * K0;
-      float2 acc = make_float2(0.f, 0.f);
-      for (int k0 = 0; k0 < K0; ++k0) cmac(acc, w[k0], bsrc[(size_t)k0 * KG + kk]);
-      dst[((size_t)v * M0 + x0) * C + (size_t)kh * K1 + k1] = acc;
-    }
-  }
-}
-
 // ------------------------------------------ MFMA column step (tuned shapes)
 // Complex 16x16 output tile by four real MFMAs per k-step of four:
 // acc0 += Ar Br, acc1 += Ai Bi, acc2 += Ar Bi, acc3 += Ai Br, so the tile is
@@ -999,44 +689,6 @@ __device__ __forceinline__ void ctile(const float2* __restrict__ A, int lda, con
 
 __device__ __forceinline__ void zero_acc(floatx4* acc, int n) {
   for (int i = 0; i < n; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-}
-
-// Logical block index (x, y, z) of a launch whose workgroups the command
-// processor hands round-robin to the eight XCDs (workgroup p to XCD p % 8):
-// with the block count a multiple of 8, XCD x takes the contiguous logical
-// range [x T/8, (x + 1) T/8), so blocks that are neighbours in the logical
-// order run on one XCD and meet in its L2.  The logical order runs x fastest,
-// or with ZFirst z fastest, then x, then y (for launches whose z blocks of
-// one (x, y) read the same input: the column steps' k1 tiles and parts of one
-// kh read the same stage-1 input, and neighbouring kh share 32-byte granules
-// of the band).
-template <bool ZFirst>
-__device__ __forceinline__ uint3 xcd_block3() {
-  const unsigned gx = gridDim.x, gy = gridDim.y, gz = gridDim.z, total = gx * gy * gz;
-  unsigned p = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-  if (total % 8u == 0) p = (p % 8u) * (total / 8u) + p / 8u;
-  if constexpr (ZFirst) return make_uint3((p / gz) % gx, p / (gz * gx), p % gz);
-  return make_uint3(p % gx, (p / gx) % gy, p / (gx * gy));
-}
-
-// Tables for the MFMA column step: w1t[x1][k1] = fwd1[k1][x1] (columns padded
-// to Kp), w0f[k0][x0] = fwd0 (rows padded to Kp), w0i[v][x0][k0] = inv0 (rows
-// padded to Mp); padding is zero.
-__global__ void k_col_tables(const float2* fwd1, const float2* fwd0, const float2* inv0, float2* w1t,
-                             float2* w0f, float2* w0i, int M, int K, int Mp, int Kp) {
-  const int n1 = M * Kp, n2 = Kp * M, n3 = 2 * Mp * K;
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const float2 z = make_float2(0.f, 0.f);
-  if (i < n1) {
-    int x1 = i / Kp, k1 = i % Kp;
-    w1t[i] = (k1 < K) ? fwd1[(size_t)k1 * M + x1] : z;
-  } else if (i < n1 + n2) {
-    int e = i - n1, k0 = e / M, x0 = e % M;
-    w0f[e] = (k0 < K) ? fwd0[(size_t)k0 * M + x0] : z;
-  } else if (i < n1 + n2 + n3) {
-    int e = i - n1 - n2, v = e / (Mp * K), x0 = (e / K) % Mp, k0 = e % K;
-    w0i[e] = (x0 < M) ? inv0[((size_t)v * M + x0) * K + k0] : z;
-  }
 }
 
 // One block per (kh, job, 16-wide tile of k1, part), four waves; same contract
@@ -2741,39 +2393,11 @@ __global__ void k_pcg_update_d(const double* sc, const float2* r, float2* dv, in
 }
 
 // ================================================= launch wrappers
-// Launch of a kernel the timer may sample: a sampled launch carries the
-// timer's start and stop events in its dispatch (they then hold the times the
-// dispatch began and completed, which include the command processor's
-// per-dispatch work around the kernel); while a graph is being captured, the
-// kernel node is handed to the timer instead.
-#define LAUNCH_TIMED(fam, kernel, grid, block, shm, st, ...)                              \
-  do {                                                                                     \
-    hipEvent_t ev0_ = nullptr, ev1_ = nullptr;                                             \
-    if (timer_events((fam), &ev0_, &ev1_))                                                 \
-      hipExtLaunchKernelGGL(kernel, grid, block, shm, st, ev0_, ev1_, 0, __VA_ARGS__);    \
-    else                                                                                   \
-      hipLaunchKernelGGL(kernel, grid, block, shm, st, __VA_ARGS__);                       \
-    timer_captured((fam), st);                                                             \
-  } while (0)
-
-static inline unsigned nblk(long long n, int t) { return (unsigned)((n + t - 1) / t); }
-
-static bool band_iso(const Dims& d, int K, int M) {
-  return d.K[0] == K && d.K[1] == K && d.K[2] == K && d.M[0] == M && d.M[1] == M && d.M[2] == M;
-}
 static bool grid_iso(const Dims& d, int N, int K) {
   return d.N[0] == N && d.N[1] == N && d.N[2] == N && d.K[1] == K && d.K[2] == K;
 }
 static bool grid_is(const Dims& d, int A, int B, int C, int K) {
   return d.N[0] == A && d.N[1] == B && d.N[2] == C && d.K[1] == K && d.K[2] == K;
-}
-// Calls f with the band shape type for these sizes.
-template <class F>
-static hipError_t with_band(const Dims& d, F&& f) {
-  if (band_iso(d, 32, 48)) return f(BandIso<32, 48>{});
-  if (band_iso(d, 16, 24)) return f(BandIso<16, 24>{});
-  if (band_iso(d, 24, 36)) return f(BandIso<24, 36>{});
-  return f(BandDyn{d.K[0], d.K[1], d.Kh, d.M[0], d.M[1], d.M[2]});
 }
 template <class F>
 static hipError_t with_grid(const Dims& d, F&& f) {
@@ -2789,19 +2413,6 @@ static hipError_t with_grid(const Dims& d, F&& f) {
   if (grid_is(d, 160, 192, 160, 24)) return f(GridShape<160, 192, 160, 24>{});
   if (grid_is(d, 160, 192, 160, 32)) return f(GridShape<160, 192, 160, 32>{});
   return f(GridDyn{d.N[0], d.N[1], d.N[2], d.K[1], d.Kh});
-}
-
-hipError_t launch_twiddles(float2* dst, int K, int G, int mode, hipStream_t st) {
-  int Kq = (mode == 1 || mode == 3) ? K / 2 : K;
-  int total = (mode <= 1) ? 2 * G * Kq : Kq * G;
-  hipLaunchKernelGGL(k_twiddles, dim3(nblk(total, 256)), dim3(256), 0, st, dst, K, G, mode);
-  return hipGetLastError();
-}
-
-hipError_t launch_symbols(float* Lsym, float* Ksym, const Dims& d, hipStream_t st) {
-  hipLaunchKernelGGL(k_symbols, dim3(nblk(d.nb, 256)), dim3(256), 0, st, Lsym, Ksym, d.K[0], d.K[1],
-                     d.Kh, d.s, d.alpha);
-  return hipGetLastError();
 }
 
 hipError_t launch_full_to_half(const float2* full, float2* half, const Dims& d, hipStream_t st) {
@@ -2875,19 +2486,19 @@ size_t synth_shared_bytes(const Dims& d) {
          sizeof(float);
 }
 
-hipError_t launch_synth_tables(const Twiddles& tw, float* tables, const Dims& d, hipStream_t st) {
+// MFMA-friendly real forms of the stage-1 and stage-2 inverse twiddles:
+// w1a [2][M1p][2 K1] = (re | -im), w2b [2][2 Khp][M2p] = (re ; -im), padding zero.
+int synth_table_jobs(TableJob* j, float* tables, const Dims& d) {
   int M1p, M2p, Khp;
   synth_padding(d, &M1p, &M2p, &Khp);
-  const size_t n = synth_table_floats(d);
-  float* w1a = tables;
   float* w2b = tables + 2 * (size_t)M1p * 2 * d.K[1];
-  hipLaunchKernelGGL(k_synth_tables, dim3(nblk((long long)n, 256)), dim3(256), 0, st, tw.inv1, tw.inv2, w1a,
-                     w2b, d.M[1], d.M[2], d.K[1], d.Kh, M1p, M2p, Khp);
-  return hipGetLastError();
+  j[0] = TableJob{tables, nullptr, TAB_SYNTH1, d.K[1], d.M[1], 2 * M1p * 2 * d.K[1], 0, 0.0};
+  j[1] = TableJob{w2b, nullptr, TAB_SYNTH2, d.K[2], d.M[2], 2 * 2 * Khp * M2p, 0, 0.0};
+  return 2;
 }
 
 hipError_t launch_synth(const float2* t1g0, const float2* t1g1, float* dst0, float* dst1,
-                        const float* tables, const Dims& d, hipStream_t st) {
+                        const float* tables, const Frags& fr, const Dims& d, hipStream_t st) {
   int M1p, M2p, Khp;
   synth_padding(d, &M1p, &M2p, &Khp);
   SynthArgs a{};
@@ -2903,18 +2514,18 @@ hipError_t launch_synth(const float2* t1g0, const float2* t1g1, float* dst0, flo
              nf * (2.0 * d.M[0] * d.K[1] * d.Kh * 8.0 + 4.0 * nM * 4.0));
   (void)Khp;
   (void)M2p;
-  hipError_t e = with_band(d, [&](auto sh) {
-    do {
+  return with_band(d, [&](auto sh) {
+    if constexpr (decltype(sh)::kStatic) {
+      const dim3 grid(d.M[0], nf, M1p / 16);
       if (d.prec)
-        LAUNCH_TIMED(KF_SYNTH, (k_synth<decltype(sh), true>), dim3(d.M[0], nf, M1p / 16), dim3(256), synth_shared_bytes(d), st,
-                   a, sh);
+        LAUNCH_TIMED(KF_SYNTH, (k_synth<decltype(sh), true>), grid, dim3(256), synth_shared_bytes(d), st, a, sh);
       else
-        LAUNCH_TIMED(KF_SYNTH, (k_synth<decltype(sh), false>), dim3(d.M[0], nf, M1p / 16), dim3(256), synth_shared_bytes(d), st,
-                   a, sh);
-    } while (0);
-    return hipGetLastError();
+        LAUNCH_TIMED(KF_SYNTH, (k_synth<decltype(sh), false>), grid, dim3(256), synth_shared_bytes(d), st, a, sh);
+      return hipGetLastError();
+    } else {
+      return launch_synth_chain(a, nf, fr, d, st);
+    }
   });
-  return e;
 }
 
 int prod_rows_max(const Dims& d) {
@@ -2959,27 +2570,14 @@ hipError_t launch_prods(const ProdArgs& a, const Dims& d, const Twiddles& tw, hi
   return e;
 }
 
-constexpr int kColGroup = 8;
-
-// LDS plan of the generic column kernel: region X holds one S1 slice and,
-// when the total stays within the LDS of a workgroup, the inverse twiddles
-// of phase 3.
-static void colstep_lds_plan(const Dims& d, int* xsz, int* stage_w0, size_t* bytes) {
-  const int M0 = d.M[0], M1 = d.M[1], K0 = d.K[0];
-  const size_t rest = (size_t)kColGroup * M1 + 2 * (size_t)M0 * kColGroup + (size_t)K0 * M0 +
-                      2 * (size_t)K0 * kColGroup;
-  const size_t staged = (size_t)std::max(M0 * M1, 2 * M0 * K0);
-  const bool st = (staged + rest) * sizeof(float2) <= kMaxLds;
-  *xsz = st ? (int)staged : M0 * M1;
-  *stage_w0 = st ? 1 : 0;
-  *bytes = ((size_t)*xsz + rest) * sizeof(float2);
-}
-
+// Limit on the problem sizes (validated at the boundary): the LDS tile of a
+// column step with one product slice and, where they fit too, its tables.
 size_t colstep_shared_bytes(const Dims& d) {
-  int xsz, sw;
-  size_t b;
-  colstep_lds_plan(d, &xsz, &sw, &b);
-  return b;
+  const int M0 = d.M[0], M1 = d.M[1], K0 = d.K[0], G = 8;
+  const size_t rest = (size_t)G * M1 + 2 * (size_t)M0 * G + (size_t)K0 * M0 + 2 * (size_t)K0 * G;
+  const size_t staged = (size_t)std::max(M0 * M1, 2 * M0 * K0);
+  const size_t with_table = (staged + rest) * sizeof(float2);
+  return with_table <= kMaxLds ? with_table : ((size_t)M0 * M1 + rest) * sizeof(float2);
 }
 
 size_t col_table_count(const Dims& d) {
@@ -2988,35 +2586,34 @@ size_t col_table_count(const Dims& d) {
   return (size_t)M * Kp + (size_t)Kp * M + 2 * (size_t)Mp * K;
 }
 
-hipError_t launch_col_tables(const Twiddles& tw, float2* tab, const Dims& d, hipStream_t st) {
+// Tables of the MFMA column step: w1t[x1][k1] = fwd1[k1][x1] (columns padded
+// to Kp), w0f[k0][x0] = fwd0 (rows padded to Kp), w0i[v][x0][k0] = inv0 (rows
+// padded to Mp); padding is zero.
+int col_table_jobs(TableJob* j, float2* tab, const Dims& d) {
   const int M = d.M[0], K = d.K[0];
   const int Mp = round_up(M, 16), Kp = round_up(K, 16);
-  // the MFMA column kernel runs for shapes with K0 = K1 and M0 = M1 only
-  if (d.M[1] != M || d.K[1] != K) return hipSuccess;
-  float2* w1t = tab;
-  float2* w0f = w1t + (size_t)M * Kp;
-  float2* w0i = w0f + (size_t)Kp * M;
-  hipLaunchKernelGGL(k_col_tables, dim3(nblk((long long)col_table_count(d), 256)), dim3(256), 0, st, tw.fwd1,
-                     tw.fwd0, tw.inv0, w1t, w0f, w0i, M, K, Mp, Kp);
-  return hipGetLastError();
+  float2* w0f = tab + (size_t)M * Kp;
+  j[0] = TableJob{tab, nullptr, TAB_COL1, K, M, M * Kp, 0, 0.0};
+  j[1] = TableJob{w0f, nullptr, TAB_COL0, K, M, Kp * M, 0, 0.0};
+  j[2] = TableJob{w0f + (size_t)Kp * M, nullptr, TAB_COL0_INV, K, M, 2 * Mp * K, 0, 0.0};
+  return 3;
 }
 
-static bool colstep_mfma_shape(const Dims& d) {
-  return band_iso(d, 32, 48) || band_iso(d, 16, 24) || band_iso(d, 24, 36);
-}
 
 bool colstep_fuses_grid0(const Dims& d) {
-  if (!colstep_mfma_shape(d)) return true;  // the generic kernel reads the table from global memory
+  if (!band_instantiated(d)) return true;
   const int K = d.K[0], M = d.M[0], Mp = round_up(M, 16);
   return d.N[0] % 16 == 0 && d.N[0] * K <= 256 * kGrid0Pre && d.N[0] * (K + 2) <= 2 * Mp * (M + 2);
 }
 
 hipError_t launch_colstep(const ColJobs& jobs, int njobs, const Dims& d, const Twiddles& tw,
-                          const float2* coltab, const float* Lsym, const float* Ksym, hipStream_t st) {
+                          const float2* coltab, const Frags& frM, const Frags& frN, const float* Lsym,
+                          const float* Ksym, hipStream_t st) {
   for (int i = 0; i < njobs; ++i) {
     if (jobs.j[i].t1n && (!colstep_fuses_grid0(d) || jobs.N0 != d.N[0] || !jobs.w0n)) return hipErrorInvalidValue;
-    // the tuned kernel loads pairs of complex values
-    if (colstep_mfma_shape(d) && (((uintptr_t)jobs.j[i].a | (uintptr_t)jobs.j[i].b | (uintptr_t)coltab |
+    // the tuned kernel takes products only, and loads pairs of complex values
+    if (band_instantiated(d) && !jobs.j[i].a) return hipErrorInvalidValue;
+    if (band_instantiated(d) && (((uintptr_t)jobs.j[i].a | (uintptr_t)jobs.j[i].b | (uintptr_t)coltab |
                                    (uintptr_t)jobs.w0n) & 15))
       return hipErrorInvalidValue;
   }
@@ -3025,14 +2622,14 @@ hipError_t launch_colstep(const ColJobs& jobs, int njobs, const Dims& d, const T
     double fl = 0, by = 0;
     for (int i = 0; i < njobs; ++i) {
       const ColJob& j = jobs.j[i];
-      int terms = 1 + (j.b != nullptr);
+      const int terms = (j.a != nullptr) + (j.b != nullptr);
       const double N0 = j.t1n ? d.N[0] : 0.0;
       fl += terms * (M0 * M1 * K1 + K0 * K1 * M0) * Kh * 8.0 + j.nt1 * 2.0 * M0 * K0 * K1 * Kh * 8.0 +
             N0 * K0 * K1 * Kh * 8.0;
-      by += terms * M0 * M1 * Kh * 8.0 + K0 * K1 * Kh * 8.0 * (1 + (j.base != nullptr) + (j.extra != nullptr)) +
+      by += terms * M0 * M1 * Kh * 8.0 + K0 * K1 * Kh * 8.0 * ((j.out != nullptr) + (j.base != nullptr) + (j.extra != nullptr)) +
             j.nt1 * 2.0 * M0 * K1 * Kh * 8.0 + N0 * K1 * Kh * 8.0;
     }
-    timer_work(KF_COLUMN, fl, by);
+    timer_work(column_family(jobs), fl, by);
   }
   const float invG = (float)(1.0 / ((double)d.M[0] * d.M[1] * d.M[2]));
   const int M = d.M[0], K = d.K[0];
@@ -3112,14 +2709,7 @@ hipError_t launch_colstep(const ColJobs& jobs, int njobs, const Dims& d, const T
     } while (0);
     e = hipGetLastError();
   } else {
-    dim3 grid(nblk(d.K[1], kColGroup), d.Kh, njobs);
-    int xsz, stage_w0;
-    size_t shm;
-    colstep_lds_plan(d, &xsz, &stage_w0, &shm);
-    BandDyn sh{d.K[0], d.K[1], d.Kh, d.M[0], d.M[1], d.M[2]};
-    LAUNCH_TIMED(KF_COLUMN, (k_colstep<kColGroup, BandDyn>), grid, dim3(256), shm, st, jobs, tw, Lsym, Ksym, sh, invG,
-                 xsz, stage_w0);
-    e = hipGetLastError();
+    e = launch_column_chain(jobs, njobs, d, frM, frN, Lsym, Ksym, invG, st);
   }
   return e;
 }
