@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "launch.h"
+#include "sample.h"
 #include "shapes.h"
 
 namespace lddmm {
@@ -279,6 +280,7 @@ static hipError_t with_int(int n, F&& f) {
 }
 
 hipError_t launch_synth_chain(const SynthArgs& a, int nf, const Frags& fr, const Dims& d, hipStream_t st) {
+  if (!fr.row1 || !fr.row2) return hipErrorInvalidValue;
   // four waves a block: one per SIMD, so that blocks pack by registers alone
   // (blocks of six waves left a compute unit with one block: 100 us at band 64)
   const dim3 grid(nblk((long long)d.M[0] * tiles16(d.M[1]), 4), nf), block(256);
@@ -533,6 +535,7 @@ __global__ void __launch_bounds__(64 * NW, 4) k_column_chain(ColJobs jobs, Frags
 
 hipError_t launch_column_chain(const ColJobs& jobs, int njobs, const Dims& d, const Frags& frM, const Frags& frN,
                                const float* Lsym, const float* Ksym, float invG, hipStream_t st) {
+  if (!frM.inv0 || !frM.fwd0 || !frM.fwd1 || !frN.inv0) return hipErrorInvalidValue;
   for (int i = 0; i < njobs; ++i)
     if ((!jobs.j[i].a && (!jobs.j[i].base || jobs.j[i].b)) || (jobs.j[i].a && !jobs.j[i].out)) return hipErrorInvalidValue;
   const int M0p = 16 * tiles16(d.M[0]), K0p = 16 * tiles16(d.K[0]);
@@ -541,6 +544,283 @@ hipError_t launch_column_chain(const ColJobs& jobs, int njobs, const Dims& d, co
   const BandDyn sh{d.K[0], d.K[1], d.Kh, d.M[0], d.M[1], d.M[2]};
   LAUNCH_TIMED(column_family(jobs), (k_column_chain<8>), grid, dim3(512), shm, st, jobs, frM, frN, Lsym, Ksym, sh, invG);
   return hipGetLastError();
+}
+
+// ------------------------------------------------------------- grid step
+// One block of four waves per (x0, 16 x1): inverse stage 1 (k1 -> x1) of the
+// three velocity components from their stage-0 output, one 16 x 16 (kh, x1)
+// tile per wave and step, straight from memory; its result meets in LDS
+// (3 Khp rows, 6 KB at 16 kh), and stage 2 (half spectrum -> real x2) gives each
+// wave whole tiles of 16 x2 with all components, from which
+//   the source is formed with four consecutive points of a row per lane (rows
+//   x2 of the product, 16-byte loads and stores of m, dm and q; the loads are
+//   issued before the products of the stage before them);
+//   the velocity is stored, and the transport step done, with 16 consecutive
+//   points of a row per 16 lanes (rows x1 of the product), so that the eight
+//   gathers of a point meet those of its neighbours in a cache line.
+// The transport from the registers saves reading the velocity back (12 of the 20
+// bytes per point of a separate step) and, where no later call needs it,
+// storing it.
+// Measured, transport form: 180x210x180 / band 32, with the velocity stored, 125
+// (grid step out of scalar sums 77, transport 48) -> 64 us; 160x192x160 without
+// it 56 -> 35 us, of which the gathers are 10; source form 128^3 / band 64 117 ->
+// 30 us alone.  Points along x2 per lane instead (16-byte stores, each
+// gather over 16 rows) took the transport form from 35 to 51 us.
+// Sums: with SEP the four real sums of a complex product are formed apart
+// (order "rows", the instantiated grids), else in "pairs" order (all others,
+// FP32 in both precisions).
+template <class G>
+__device__ __forceinline__ float4 row4(const float* p, int x2, G gs) {  // p[x2 .. x2 + 3], repeating inside the row past its end
+  const int N2 = gs.N2();
+  if (N2 % 4 == 0) return *reinterpret_cast<const float4*>(p + min(x2, N2 - 4));
+  const int at = min(x2, N2 - 4), o = x2 - at;
+  const float4 v = ldu4(p + at);
+  if (o == 0) return v;
+  return make_float4(o == 1 ? v.y : o == 2 ? v.z : v.w, o == 1 ? v.z : v.w, v.w, v.w);
+}
+template <class G>
+__device__ __forceinline__ void put4(float* p, int x2, float4 v, G gs) {
+  const int N2 = gs.N2();
+  if (x2 >= N2) return;
+  if (N2 % 4 == 0) {
+    *reinterpret_cast<float4*>(p + x2) = v;
+  } else if (x2 + 3 < N2) {
+    f4_u4 u = {v.x, v.y, v.z, v.w};
+    *reinterpret_cast<f4_u4*>(p + x2) = u;
+  } else {
+    p[x2] = v.x;
+    if (x2 + 1 < N2) p[x2 + 1] = v.y;
+    if (x2 + 2 < N2) p[x2 + 2] = v.z;
+  }
+}
+
+template <int KT, int OP, bool SEP, bool BF3, class G>
+__global__ void __launch_bounds__(256, 4) k_gridstep(GridStepArgs a, const float4* __restrict__ f1,
+                                                     const float4* __restrict__ f2, G gs) {
+  using O = Op<BF3>;
+  constexpr int S = SEP ? 48 : 32;  // floats per kh row of the stage-1 result: (re | im) of 16 x1
+  __shared__ float t2[3 * 16 * KT * S];
+  const int N0 = gs.N0(), N1 = gs.N1(), N2 = gs.N2(), K1 = gs.K1(), Kh = gs.Kh();
+  const int X2T = (N2 + 15) / 16, KQ = (K1 + 15) / 16, J1 = (K1 + 7) / 8, J2 = (Kh + 7) / 8;
+  // the row tiles of one plane read the same stage-0 input: one XCD each
+  const uint3 lb = xcd_block3<false>();
+  const int x0 = lb.y, x1t = lb.x;
+  const int wave = wave_id(), lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int h = lk >> 1, part = lk & 1;
+  const unsigned neg = part ? 0x80000000u : 0u;
+  const int x1 = 16 * x1t + li, x1c = min(x1, N1 - 1);  // of the source's points
+
+  struct Near { float4 c, p0, m0, p1, m1, dm; float lo, hi; } near, nxt;
+  auto fetch = [&](int x2t, Near& o) {
+    const size_t NN = (size_t)N1 * N2;
+    const float* mp = a.m + x0 * NN;
+    const float* mp0 = a.m + (x0 + 1 == N0 ? 0 : x0 + 1) * NN;
+    const float* mm0 = a.m + (x0 == 0 ? N0 - 1 : x0 - 1) * NN;
+    const int x2 = 16 * x2t + 4 * lk;
+    const unsigned r = x1c * N2, rp = (x1c + 1 == N1 ? 0 : x1c + 1) * N2, rm = (x1c == 0 ? N1 - 1 : x1c - 1) * N2;
+    o.c = row4(mp + r, x2, gs);
+    o.lo = mp[r + (x2 == 0 ? N2 - 1 : min(x2, N2) - 1)];
+    o.hi = mp[r + (x2 + 4 < N2 ? x2 + 4 : 0)];
+    o.p0 = row4(mp0 + r, x2, gs);
+    o.m0 = row4(mm0 + r, x2, gs);
+    o.p1 = row4(mp + rp, x2, gs);
+    o.m1 = row4(mp + rm, x2, gs);
+    o.dm = a.dm ? row4(a.dm + x0 * NN + r, x2, gs) : make_float4(0.f, 0.f, 0.f, 0.f);
+  };
+  if constexpr (OP == GRID_SOURCE)
+    if (wave < X2T) fetch(wave, near);
+
+  for (int un = wave; un < 3 * KT; un += 4) {
+    const int c = un % 3, kt = un / 3;
+    // rows past Kh repeat the last one: they meet zero table entries
+    const unsigned row = min(16 * kt + 4 * (li & 3) + (li >> 2), Kh - 1) * K1;
+    const float2* plane = a.t1 + ((size_t)c * N0 + x0) * Kh * K1;
+    floatx4 re, im;
+    if constexpr (SEP) {
+      floatx4 s0 = zero4(), s1 = zero4(), s2 = zero4(), s3 = zero4();
+#pragma unroll 2
+      for (int q = 0; q < KQ; ++q) {
+        const float4 w0 = (f1 + ((size_t)x1t * 2 * KQ + q) * 64)[lane], w1 = (f1 + ((size_t)(x1t * 2 + 1) * KQ + q) * 64)[lane];
+        float2 t[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) t[u] = plane[row + min(16 * q + 4 * u + lk, K1 - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const typename O::T tr = O::b(t[u].x), ti = O::b(t[u].y), wr = O::a(elem(w0, u)), wi = O::a(elem(w1, u));
+          s0 = O::mma_t(tr, wr, s0);
+          s1 = O::mma_t(ti, wi, s1);
+          s2 = O::mma_t(ti, wr, s2);
+          s3 = O::mma_t(tr, wi, s3);
+        }
+      }
+      re = s0 + s1;  // wi holds -im w
+      im = s2 - s3;
+    } else {
+      re = im = zero4();
+      for (int j0 = 0; j0 < J1; j0 += 4) {
+        float4 w[4];
+        float2 t[4][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int j = min(j0 + q, J1 - 1);
+          w[q] = (f1 + ((size_t)x1t * J1 + j) * 64)[lane];
+#pragma unroll
+          for (int u = 0; u < 4; u += 2) {
+            const float4 v = ldu4(reinterpret_cast<const float*>(plane + (row + min(2 * (4 * j + u) + 2 * h, K1 - 2))));
+            t[q][u] = make_float2(v.x, v.y);
+            t[q][u + 1] = make_float2(v.z, v.w);
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (j0 + q >= J1) break;
+#pragma unroll
+          for (int u = 0; u < 4; u += 2) {
+            swap_halves(t[q][u].x, t[q][u + 1].x);
+            swap_halves(t[q][u].y, t[q][u + 1].y);
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float wi = elem(w[q], u), wr = flip(wi, neg);
+            re = Op<false>::mma(part ? t[q][u].y : t[q][u].x, wr, re);
+            im = Op<false>::mma(part ? t[q][u].x : t[q][u].y, wi, im);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float* d = t2 + (c * 16 * KT + 16 * kt + 4 * r + lk) * S + li;
+      d[0] = re[r];
+      d[16] = im[r];
+    }
+  }
+  __syncthreads();
+
+  const size_t nN = (size_t)N0 * N1 * N2, plane0 = (size_t)x0 * N1 * N2;
+  // table times stage-1 result: rows x2 and columns x1 for the source, rows x1
+  // and columns x2 otherwise
+  auto product = [&](float w, float t, floatx4 acc) {
+    if constexpr (OP == GRID_SOURCE)
+      return O::mma(O::a(w), O::b(t), acc);
+    else
+      return O::mma_t(O::b(t), O::a(w), acc);
+  };
+  float4 w[KT][2], wn[KT][2];
+  auto table = [&](int x2t, float4 (&o)[KT][2]) {
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        if constexpr (SEP) o[kt][q] = (f2 + ((size_t)(x2t * 2 + q) * KT + kt) * 64)[lane];
+        else o[kt][q] = (f2 + ((size_t)x2t * J2 + min(2 * kt + q, J2 - 1)) * 64)[lane];
+  };
+  table(min(wave, X2T - 1), w);
+  for (int x2t = wave; x2t < X2T; x2t += 4) {
+    table(min(x2t + 4, X2T - 1), wn);
+    if constexpr (OP == GRID_SOURCE)
+      if (x2t + 4 < X2T) fetch(x2t + 4, nxt);
+    floatx4 vel[3];
+    if constexpr (SEP) {
+      floatx4 acc[3][2];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) acc[c][0] = acc[c][1] = zero4();
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const float* t = t2 + (c * 16 * KT + 16 * kt + 4 * u + lk) * S + li;
+            acc[c][0] = product(elem(w[kt][0], u), t[0], acc[c][0]);
+            acc[c][1] = product(elem(w[kt][1], u), t[16], acc[c][1]);
+          }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) vel[c] = acc[c][0] + acc[c][1];
+    } else {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) vel[c] = zero4();
+#pragma unroll
+      for (int j = 0; j < 2 * KT; ++j) {
+        if (j >= J2) break;
+        const float4 wj = w[j >> 1][j & 1];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int c = 0; c < 3; ++c)
+            vel[c] = product(elem(wj, u), t2[(c * 16 * KT + 2 * (4 * j + u) + h) * S + part * 16 + li], vel[c]);
+      }
+    }
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) w[kt][q] = wn[kt][q];
+    if constexpr (OP != GRID_SOURCE) {
+      const int i2 = 16 * x2t + li;
+      if (i2 >= N2) continue;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i1 = 16 * x1t + 4 * lk + r;
+        if (i1 >= N1) continue;
+        const unsigned o = i1 * N2 + i2;
+        if (OP == GRID_VELOCITY || a.vout) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) (a.vout + c * nN + plane0)[o] = vel[c][r];
+        }
+        if constexpr (OP == GRID_TRANSPORT)
+          (a.dst + plane0)[o] =
+              trilinear(a.src, (float)x0 - a.dt * vel[0][r] * (float)N0, (float)i1 - a.dt * vel[1][r] * (float)N1,
+                        (float)i2 - a.dt * vel[2][r] * (float)N2, x0, i1, i2, gs);
+      }
+      continue;
+    }
+    const int x2 = 16 * x2t + 4 * lk;
+    if (x1 < N1) {
+      const float cc[6] = {near.lo, near.c.x, near.c.y, near.c.z, near.c.w, near.hi};
+      const float p0[4] = {near.p0.x, near.p0.y, near.p0.z, near.p0.w}, m0[4] = {near.m0.x, near.m0.y, near.m0.z, near.m0.w};
+      const float p1[4] = {near.p1.x, near.p1.y, near.p1.z, near.p1.w}, m1[4] = {near.m1.x, near.m1.y, near.m1.z, near.m1.w};
+      const float dm[4] = {near.dm.x, near.dm.y, near.dm.z, near.dm.w};
+      float q[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float up = (x2 + e + 1 < N2) ? cc[e + 2] : near.hi;  // the row's last point: its first
+        const float g0 = (p0[e] - m0[e]) * (0.5f * N0);
+        const float g1 = (p1[e] - m1[e]) * (0.5f * N1);
+        const float g2 = (up - cc[e]) * (0.5f * N2);
+        const float dot = g0 * vel[0][e] + g1 * vel[1][e] + g2 * vel[2][e];
+        q[e] = fmaf(-a.dt, dot, dm[e]);
+      }
+      put4(a.q + plane0 + (size_t)x1 * N2, x2, make_float4(q[0], q[1], q[2], q[3]), gs);
+    }
+    near = nxt;
+  }
+}
+
+hipError_t launch_gridstep_chain(const GridStepArgs& a, const Dims& d, const Frags& fr, hipStream_t st) {
+  if (grid_instantiated(d) ? (!fr.row1 || !fr.row2) : (!fr.inv1 || !fr.inv2)) return hipErrorInvalidValue;
+  const dim3 grid(tiles16(d.N[1]), d.N[0]);
+  return with_grid(d, [&](auto gs) -> hipError_t {
+    using G = decltype(gs);
+    if constexpr (G::kStatic) {
+      if (a.op != GRID_TRANSPORT) return hipErrorInvalidValue;
+      if (d.prec)
+        LAUNCH_TIMED(KF_GRID, (k_gridstep<1, GRID_TRANSPORT, true, true, G>), grid, dim3(256), 0, st, a, fr.row1, fr.row2, gs);
+      else
+        LAUNCH_TIMED(KF_GRID, (k_gridstep<1, GRID_TRANSPORT, true, false, G>), grid, dim3(256), 0, st, a, fr.row1, fr.row2, gs);
+      return hipGetLastError();
+    } else {
+      return with_int<2>(tiles16(d.Kh), [&](auto kt) {
+        constexpr int KT = decltype(kt)::value;
+        if (a.op == GRID_VELOCITY)
+          LAUNCH_TIMED(KF_GRID, (k_gridstep<KT, GRID_VELOCITY, false, false, G>), grid, dim3(256), 0, st, a, fr.inv1, fr.inv2, gs);
+        else if (a.op == GRID_SOURCE)
+          LAUNCH_TIMED(KF_GRID, (k_gridstep<KT, GRID_SOURCE, false, false, G>), grid, dim3(256), 0, st, a, fr.inv1, fr.inv2, gs);
+        else
+          LAUNCH_TIMED(KF_GRID, (k_gridstep<KT, GRID_TRANSPORT, false, false, G>), grid, dim3(256), 0, st, a, fr.inv1, fr.inv2, gs);
+        return hipGetLastError();
+      });
+    }
+  });
 }
 
 }  // namespace lddmm

@@ -63,6 +63,8 @@ struct TableJobs { TableJob j[kMaxTables]; };
 struct Frags {
   const float4* row1;   // inverse axis 1 and axis 2
   const float4* row2;
+  const float4* inv1;   // pairs: inverse axis 1 and (half) axis 2
+  const float4* inv2;
   const float4* inv0;   // pairs: inverse axis 0, forward axes 0 and 1
   const float4* fwd0;
   const float4* fwd1;
@@ -175,13 +177,20 @@ struct Fwd0Job {
 };
 struct Fwd0Jobs { Fwd0Job j[kMaxJobs]; };
 
+enum GridOp {
+  GRID_VELOCITY = 0,   // vout = the velocity
+  GRID_SOURCE = 1,     // q = dm_n - dt grad_h m_n . velocity
+  GRID_TRANSPORT = 2   // dst(x) = src(x - dt velocity(x)), and the velocity to vout when given
+};
 struct GridStepArgs {
   const float2* t1;   // [3][N0][Kh][K1]
-  int op;             // 0: write the velocity; 1: incremental-state source
-  float* vout;        // op 0: [3][nN]
-  const float* m;     // op 1: state m_n
-  const float* dm;    // op 1: incremental state dm_n (null: zero)
-  float* q;           // op 1: dm_n - dt grad_h m_n . dv_n
+  int op;
+  float* vout;        // [3][nN]
+  const float* m;     // source: state m_n
+  const float* dm;    // source: incremental state dm_n (null: zero)
+  float* q;
+  const float* src;   // transport
+  float* dst;
   float dt;
 };
 
@@ -222,7 +231,8 @@ hipError_t launch_fwd1(const Fwd1Jobs& jobs, int njobs, const float2* tw, int G0
                        int Kh, hipStream_t st);
 hipError_t launch_fwd0(const Fwd0Jobs& jobs, int njobs, const float2* tw, const float* Ksym, int G0,
                        int K0, int K1, int Kh, float invG, hipStream_t st);
-hipError_t launch_gridstep(const GridStepArgs& a, const Dims& d, const Twiddles& tw, hipStream_t st);
+hipError_t launch_gridstep(const GridStepArgs& a, const Dims& d, const Twiddles& tw, const Frags& fr, hipStream_t st);
+hipError_t launch_gridstep_chain(const GridStepArgs& a, const Dims& d, const Frags& fr, hipStream_t st);
 hipError_t launch_sl(const float* src, const float* vel, float* dst, float dt, const Dims& d,
                      hipStream_t st);
 // One transport step with midpoint departure points: vel is the mid-step

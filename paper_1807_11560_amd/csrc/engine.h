@@ -126,7 +126,8 @@ class Engine {
   hipError_t tail(const float* a, const float* b, const float* r, float coef, float2* out,
                   const float2* zero_band, hipStream_t s);
   hipError_t grid_t1(int n, const float2* band, hipStream_t s);
-  hipError_t grid_velocity(int n, float* out, hipStream_t s);
+  hipError_t grid_transport(const float2* band, bool stage0, float2* t1n, const float* src, float* dst, float* vout,
+                            float dt, hipStream_t s);
   hipError_t grid_source(int n, const float* dmn, hipStream_t s);
   // deformation state (paper §3.3)
   hipError_t forward_def(const float* I0);

@@ -33,9 +33,15 @@ int t16(int n) { return (n + 15) / 16; }
 size_t row_inv(int K, int G) { return (size_t)2 * t16(G) * t16(K) * 128; }
 size_t pair_inv(int K, int G) { return (size_t)2 * t16(G) * ((K + 7) / 8) * 64; }
 size_t pair_fwd(int K, int G) { return (size_t)t16(K) * ((G + 7) / 8) * 64; }
-size_t frag_count(const Dims& d) {
+// of the padded grid (shapes without instantiated band kernels), and of the
+// image grid: the grid step's, and axis 0 for the column step of those shapes
+size_t frag_count_m(const Dims& d) {
   return row_inv(d.K[1], d.M[1]) + row_inv(d.Kh, d.M[2]) + pair_inv(d.K[0], d.M[0]) + pair_fwd(d.K[0], d.M[0]) +
          pair_fwd(d.K[1], d.M[1]) + pair_inv(d.K[0], d.N[0]) / 2;
+}
+size_t frag_count_n(const Dims& d) {
+  return grid_instantiated(d) ? (row_inv(d.K[1], d.N[1]) + row_inv(d.Kh, d.N[2])) / 2
+                              : (pair_inv(d.K[1], d.N[1]) + pair_inv(d.Kh, d.N[2])) / 2;
 }
 }  // namespace
 
@@ -147,13 +153,16 @@ void Engine::layout(Carver& c) {
     // the workspace of a problem (and with it what lddmm_shoot_static takes)
     // does not depend on which kernels serve it.
     auto tables = [&](Carver& r, bool inst) {
-      twbuf_ = r.take<float2>((inst ? twiddle_count(d.M, d) : (size_t)d.Kh * d.M[2]) + twiddle_count(d.N, d));
+      twbuf_ = r.take<float2>((inst ? 2 * (size_t)d.M[0] * d.K[0] : 0) + (size_t)d.Kh * d.M[2] +
+                              twiddle_count(d.N, d));
       synth_tab_ = inst ? r.take<float>(synth_table_floats(d)) : nullptr;
       col_tab_ = inst ? r.take<float2>(col_table_count(d)) : nullptr;
-      frag_ = inst ? nullptr : r.take<float4>(frag_count(d));
+      frag_ = r.take<float4>((inst ? 0 : frag_count_m(d)) + frag_count_n(d));
     };
     Carver a{nullptr}, b{nullptr};
-    tables(a, true);
+    a.take<float2>(twiddle_count(d.M, d) + twiddle_count(d.N, d));
+    a.take<float>(synth_table_floats(d));
+    a.take<float2>(col_table_count(d));
     tables(b, band_instantiated(d));
     Carver r{c.take<char>(std::max(a.off, b.off))};
     tables(r, band_instantiated(d));
@@ -197,16 +206,14 @@ Engine::Engine(const Dims& d, void* ws, hipStream_t st)
     : d_(d), st_(st), fuse_grid0_(colstep_fuses_grid0(d) && d.ckpt == 0) {
   Carver c{static_cast<char*>(ws)};
   layout(c);
-  // table views (of the padded grid's plain tables only the last where its
-  // kernels read fragment tables)
   const bool inst = band_instantiated(d);
   float2* t = twbuf_;
   for (int pass = 0; pass < 2; ++pass) {
     Twiddles& tw = pass == 0 ? twM_ : twN_;
     const int* G = pass == 0 ? d.M : d.N;
     for (int j = 0; j < 3; ++j) tw.G[j] = G[j];
-    if (pass == 1 || inst) {
-      tw.inv0 = t; t += 2 * (size_t)G[0] * d.K[0];
+    if (pass == 1 || inst) { tw.inv0 = t; t += 2 * (size_t)G[0] * d.K[0]; }
+    if (pass == 1) {
       tw.inv1 = t; t += 2 * (size_t)G[1] * d.K[1];
       tw.inv2 = t; t += 2 * (size_t)G[2] * d.Kh;
       tw.fwd0 = t; t += (size_t)d.K[0] * G[0];
@@ -214,14 +221,23 @@ Engine::Engine(const Dims& d, void* ws, hipStream_t st)
     }
     tw.fwd2 = t; t += (size_t)d.Kh * G[2];
   }
-  if (inst) return;
   const float4* f = frag_;
-  frM_.row1 = f; f += row_inv(d.K[1], d.M[1]);
-  frM_.row2 = f; f += row_inv(d.Kh, d.M[2]);
-  frM_.inv0 = f; f += pair_inv(d.K[0], d.M[0]);
-  frM_.fwd0 = f; f += pair_fwd(d.K[0], d.M[0]);
-  frM_.fwd1 = f; f += pair_fwd(d.K[1], d.M[1]);
-  frN_.inv0 = f;
+  auto view = [&](const float4*& p, size_t n) { p = f; f += n; };
+  if (!inst) {
+    view(frM_.row1, row_inv(d.K[1], d.M[1]));
+    view(frM_.row2, row_inv(d.Kh, d.M[2]));
+    view(frM_.inv0, pair_inv(d.K[0], d.M[0]));
+    view(frM_.fwd0, pair_fwd(d.K[0], d.M[0]));
+    view(frM_.fwd1, pair_fwd(d.K[1], d.M[1]));
+    view(frN_.inv0, pair_inv(d.K[0], d.N[0]) / 2);
+  }
+  if (grid_instantiated(d)) {
+    view(frN_.row1, row_inv(d.K[1], d.N[1]) / 2);
+    view(frN_.row2, row_inv(d.Kh, d.N[2]) / 2);
+  } else {
+    view(frN_.inv1, pair_inv(d.K[1], d.N[1]) / 2);
+    view(frN_.inv2, pair_inv(d.Kh, d.N[2]) / 2);
+  }
 }
 
 size_t Engine::workspace_bytes(const Dims& d) {
@@ -244,9 +260,11 @@ hipError_t Engine::init_tables() {
     const Twiddles& tw = pass == 0 ? twM_ : twN_;
     const int* G = tw.G;
     if (pass == 1 || inst) add(tw.inv0, TAB_INV, K[0], G[0], 2 * (size_t)G[0] * K[0]);
-    if (pass == 1) {
+    if (pass == 1 && grid_instantiated(d_)) {
       add(tw.inv1, TAB_INV, K[1], G[1], 2 * (size_t)G[1] * K[1]);
       add(tw.inv2, TAB_INV_HALF, K[2], G[2], 2 * (size_t)G[2] * d_.Kh);
+    }
+    if (pass == 1) {
       add(tw.fwd0, TAB_FWD, K[0], G[0], (size_t)K[0] * G[0]);
       add(tw.fwd1, TAB_FWD, K[1], G[1], (size_t)K[1] * G[1]);
     }
@@ -262,6 +280,13 @@ hipError_t Engine::init_tables() {
     add(frM_.fwd0, TAB_PAIR_FWD, K[0], d_.M[0], 4 * pair_fwd(K[0], d_.M[0]));
     add(frM_.fwd1, TAB_PAIR_FWD, K[1], d_.M[1], 4 * pair_fwd(K[1], d_.M[1]));
     add(frN_.inv0, TAB_PAIR_INV, K[0], d_.N[0], 2 * pair_inv(K[0], d_.N[0]));
+  }
+  if (grid_instantiated(d_)) {
+    add(frN_.row1, TAB_ROW_INV, K[1], d_.N[1], 2 * row_inv(K[1], d_.N[1]));
+    add(frN_.row2, TAB_ROW_INV_HALF, d_.Kh, d_.N[2], 2 * row_inv(d_.Kh, d_.N[2]));
+  } else {
+    add(frN_.inv1, TAB_PAIR_INV, K[1], d_.N[1], 2 * pair_inv(K[1], d_.N[1]));
+    add(frN_.inv2, TAB_PAIR_INV_HALF, d_.Kh, d_.N[2], 2 * pair_inv(d_.Kh, d_.N[2]));
   }
   add(count, TAB_ZERO, 0, 0, 64);
   add(Lsym, TAB_SYMBOLS, K[0], K[1], d_.nb);
@@ -417,14 +442,20 @@ hipError_t Engine::grid_t1(int n, const float2* band, hipStream_t s) {
   return hipSuccess;
 }
 
-// Grid velocity of time step n (band field V[n]) on stream s.
-hipError_t Engine::grid_velocity(int n, float* out, hipStream_t s) {
-  TRY(grid_t1(n, V[n], s));
+// One transport step of time step n on stream s: dst(x) = src(x - dt v_n(x)),
+// v_n on the grid to vout when given; t1n: the stage-0 buffer of the step,
+// formed here when `stage0`.
+hipError_t Engine::grid_transport(const float2* band, bool stage0, float2* t1n, const float* src, float* dst,
+                                  float* vout, float dt, hipStream_t s) {
+  if (stage0) TRY(grid_stage0(band, t1n, s));
   GridStepArgs a{};
-  a.t1 = T1N[n];
-  a.op = 0;
-  a.vout = out;
-  return launch_gridstep(a, d_, twN_, s);
+  a.t1 = t1n;
+  a.op = GRID_TRANSPORT;
+  a.vout = vout;
+  a.src = src;
+  a.dst = dst;
+  a.dt = dt;
+  return launch_gridstep(a, d_, twN_, frN_, s);
 }
 
 // Incremental transport source q = dm_n - dt grad_h m_n . dv_n of time step n
@@ -433,12 +464,12 @@ hipError_t Engine::grid_source(int n, const float* dmn, hipStream_t s) {
   TRY(grid_t1(n, dV[n], s));
   GridStepArgs a{};
   a.t1 = T1N[n];
-  a.op = 1;
+  a.op = GRID_SOURCE;
   a.m = m[n];
   a.dm = dmn;
   a.q = q;
   a.dt = 1.0f / d_.nt;
-  return launch_gridstep(a, d_, twN_, s);
+  return launch_gridstep(a, d_, twN_, frN_, s);
 }
 
 // t = 1 tail: out = K~ pi(coef [(a - b) grad_h m_nt + r grad_h a]) (b, r may be null), then the
@@ -502,8 +533,7 @@ hipError_t Engine::forward(const float* I0) {
     if (n >= nt) return hipSuccess;
     TRY(wait(aux_, n));
     if (n == 0) TRY(launch_copy(I0, m[0], d_.nN, aux_));
-    TRY(grid_velocity(n, vg[n], aux_));
-    return launch_sl(m[n], vg[n], m[n + 1], dt, d_, aux_);
+    return grid_transport(V[n], n == 0 || !fuse_grid0_, T1N[n], m[n], m[n + 1], vg[n], dt, aux_);
   };
   TRY(grid_step(0));
   TRY(shoot_band(true, grid_step));
@@ -529,9 +559,8 @@ hipError_t Engine::forward_light(const float* I0, const float** m_out) {
   auto grid_step = [&](int n) -> hipError_t {
     if (n >= nt) return hipSuccess;
     TRY(wait(aux_, n));
-    TRY(grid_velocity(n, vg[0], aux_));
     float* dst = mlight[n & 1];
-    TRY(launch_sl(cur, vg[0], dst, dt, d_, aux_));
+    TRY(grid_transport(V[n], n == 0 || !fuse_grid0_, T1N[n], cur, dst, nullptr, dt, aux_));
     cur = dst;
     return hipSuccess;
   };
@@ -594,9 +623,9 @@ hipError_t Engine::forward_rk(const float* I0, const float** m_out) {
     TRY(grid_stage0(vmid, T1N[0], st_));
     GridStepArgs a{};
     a.t1 = T1N[0];
-    a.op = 0;
+    a.op = GRID_VELOCITY;
     a.vout = vg[0];
-    TRY(launch_gridstep(a, d_, twN_, st_));
+    TRY(launch_gridstep(a, d_, twN_, frN_, st_));
     float* dst = mlight[n & 1];
     TRY(launch_sl_rk2(cur, vg[0], dst, dt, d_, st_));
     cur = dst;
@@ -756,9 +785,9 @@ hipError_t Engine::grid_velocity_ckpt(int n, float* out, hipStream_t s) {
   TRY(grid_stage0(V[n], T1N[0], s));
   GridStepArgs a{};
   a.t1 = T1N[0];
-  a.op = 0;
+  a.op = GRID_VELOCITY;
   a.vout = out;
-  return launch_gridstep(a, d_, twN_, s);
+  return launch_gridstep(a, d_, twN_, frN_, s);
 }
 
 hipError_t Engine::forward_ckpt(const float* I0) {
@@ -771,8 +800,7 @@ hipError_t Engine::forward_ckpt(const float* I0) {
     if (n >= nt) return hipSuccess;
     TRY(wait(aux_, n));
     if (n == 0) TRY(launch_copy(I0, m[0], d_.nN, aux_));
-    TRY(grid_velocity_ckpt(n, vg[0], aux_));
-    return launch_sl(ckpt_state(n), vg[0], ckpt_state(n + 1), dt, d_, aux_);
+    return grid_transport(V[n], true, T1N[0], ckpt_state(n), ckpt_state(n + 1), nullptr, dt, aux_);
   };
   TRY(grid_step(0));
   TRY(shoot_band(true, grid_step));
@@ -801,9 +829,9 @@ hipError_t Engine::hessvec_exact(const float2* dvh, float2* out) {
     TRY(grid_t1(n, dV[n], st_));
     GridStepArgs ga{};
     ga.t1 = T1N[n];
-    ga.op = 0;
+    ga.op = GRID_VELOCITY;
     ga.vout = dvg_;
-    TRY(launch_gridstep(ga, d_, twN_, st_));
+    TRY(launch_gridstep(ga, d_, twN_, frN_, st_));
     TRY(launch_sl_tangent(n == 0 ? nullptr : dm[cur], m[n], vg[n], dvg_, dm[1 - cur], dt, d_, st_));
     cur = 1 - cur;
     if (n == nt - 1) break;
@@ -837,10 +865,8 @@ hipError_t Engine::adjoint_exact(int cur) {
       // entering a segment from its end: transport its states again
       const int s0 = (n / c) * c;
       if (n == nt - 1 || n % c == c - 1)
-        for (int k = s0; k < n; ++k) {
-          TRY(grid_velocity_ckpt(k, vg[0], st_));
-          TRY(launch_sl(ckpt_state(k), vg[0], mseg_[(k + 1) - s0], dt, d_, st_));
-        }
+        for (int k = s0; k < n; ++k)
+          TRY(grid_transport(V[k], true, T1N[0], ckpt_state(k), mseg_[(k + 1) - s0], nullptr, dt, st_));
       mn = ckpt_state(n);
       TRY(grid_velocity_ckpt(n, vg[0], st_));
       vn = vg[0];
@@ -919,9 +945,9 @@ hipError_t Engine::grid_field(const float2* band, bool have_t1n, float* out, hip
   if (!have_t1n) TRY(grid_stage0(band, T1NA_, s));
   GridStepArgs a{};
   a.t1 = T1NA_;
-  a.op = 0;
+  a.op = GRID_VELOCITY;
   a.vout = out;
-  return launch_gridstep(a, d_, twN_, s);
+  return launch_gridstep(a, d_, twN_, frN_, s);
 }
 
 // Forward stages 1 and 0 of the three fields in S1N: pi(s) into `plain` and
@@ -986,8 +1012,7 @@ hipError_t Engine::forward_def(const float* I0) {
     return colstep_on(jobs, 3, aux_);
   };
   TRY(shoot_band(true, chain));
-  TRY(grid_field(Phi[nt], nt > 1 && fuse_grid0_, ug, aux_));
-  TRY(launch_sl(I0c, ug, m1, -1.0f, d_, aux_));
+  TRY(grid_transport(Phi[nt], !(nt > 1 && fuse_grid0_), T1NA_, I0c, m1, ug, -1.0f, aux_));
   TRY(record(aux_, nt + 1));
   return wait(st_, nt + 1);
 }

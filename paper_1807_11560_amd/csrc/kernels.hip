@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "launch.h"
+#include "sample.h"
 #include "shapes.h"
 
 namespace lddmm {
@@ -1215,12 +1216,8 @@ __global__ void __launch_bounds__(128) k_fwd0(Fwd0Jobs jobs, const float2* __res
   }
 }
 
-// ----------------------------------------------------- grid step (N)
-// One block per (x0, 16 consecutive x1 rows), 256 threads = 16 rows x 16
-// lanes: inverse stage 1 of the three velocity components from their
-// stage-0 output, then stage 2 register-blocked (lane l owns x2 = l + 16 j),
-// then either the velocity itself or the incremental-state source.
-constexpr int kGridRows = 16;
+// ----------------------------------------------------- grid kernels (N)
+constexpr int kGridRows = 16;  // rows of x1 per block of the source kernels
 
 __device__ __forceinline__ float central_diff(const float* __restrict__ m, int x0, int x1, int x2,
                                               int N0, int N1, int N2, int axis) {
@@ -1236,89 +1233,8 @@ __device__ __forceinline__ float central_diff(const float* __restrict__ m, int x
   return (m[((long long)x0 * N1 + x1) * N2 + p] - m[((long long)x0 * N1 + x1) * N2 + q]) * (0.5f * N2);
 }
 
-template <int JN, class G>
-__global__ void __launch_bounds__(256) k_gridstep(GridStepArgs a, Twiddles tw, G gs) {
-  extern __shared__ float2 sh2[];
-  const int N0 = gs.N0(), N1 = gs.N1(), N2 = gs.N2(), K1 = gs.K1(), Kh = gs.Kh();
-  constexpr int R = kGridRows;
-  const int C = K1 * Kh;
-  const int x0 = blockIdx.y;
-  const int x1b = blockIdx.x * R;
-  float2* t1s = sh2;                 // [3][K1][Kh]
-  float2* t2s = t1s + 3 * C;         // [3][R][Kh]
-  float2* w1s = t2s + 3 * R * Kh;    // [R][K1]
-  float2* w2t = w1s + R * K1;        // [Kh][N2]
-  batched_fill<float2>(3 * C, [&](int i) {  // global [c][x0][kh][k1] -> t1s[c][k1][kh]
-    return a.t1[((size_t)(i / C) * N0 + x0) * C + i % C];
-  }, [&](int i, float2 v) {
-    const int c = i / C, kh = (i % C) / K1, k1 = i % K1;
-    t1s[(size_t)c * C + k1 * Kh + kh] = v;
-  });
-  batched_fill<float2>(R * K1, [&](int i) {
-    int r = i / K1, k = i % K1;
-    int x1 = x1b + r;
-    return (x1 < N1) ? tw.inv1[(size_t)x1 * K1 + k] : make_float2(0.f, 0.f);
-  }, [&](int i, float2 v) { w1s[i] = v; });
-  batched_fill<float2>(N2 * Kh, [&](int i) {
-    int kh = i / N2, x2 = i % N2;
-    return tw.inv2[(size_t)x2 * Kh + kh];
-  }, [&](int i, float2 v) { w2t[i] = v; });
-  __syncthreads();
-  for (int i = threadIdx.x; i < 3 * R * Kh; i += blockDim.x) {
-    int c = i / (R * Kh), r = (i / Kh) % R, kh = i % Kh;
-    float2 acc = make_float2(0.f, 0.f);
-    const float2* wr = w1s + (size_t)r * K1;
-    const float2* tc = t1s + (size_t)c * C + kh;
-    for (int k = 0; k < K1; ++k) cmac(acc, wr[k], tc[(size_t)k * Kh]);
-    t2s[i] = acc;
-  }
-  __syncthreads();
-  const int r = threadIdx.x >> 4, lane = threadIdx.x & 15;
-  const int x1 = x1b + r;
-  float acc[3][JN];
-#pragma unroll
-  for (int c = 0; c < 3; ++c)
-#pragma unroll
-    for (int j = 0; j < JN; ++j) acc[c][j] = 0.f;
-  for (int kh = 0; kh < Kh; ++kh) {
-    float2 t[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) t[c] = t2s[((size_t)c * R + r) * Kh + kh];
-    const float2* w = w2t + (size_t)kh * N2;
-#pragma unroll
-    for (int j = 0; j < JN; ++j) {
-      int x2 = lane + 16 * j;
-      float2 ww = (x2 < N2) ? w[x2] : make_float2(0.f, 0.f);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        acc[c][j] = fmaf(t[c].x, ww.x, acc[c][j]);
-        acc[c][j] = fmaf(-t[c].y, ww.y, acc[c][j]);
-      }
-    }
-  }
-  if (x1 >= N1) return;
-  const long long nN = (long long)N0 * N1 * N2;
-#pragma unroll
-  for (int j = 0; j < JN; ++j) {
-    const int x2 = lane + 16 * j;
-    if (x2 >= N2) continue;
-    const long long gi = ((long long)x0 * N1 + x1) * N2 + x2;
-    if (a.op == 0) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) a.vout[(size_t)c * nN + gi] = acc[c][j];
-    } else {
-      float g0 = central_diff(a.m, x0, x1, x2, N0, N1, N2, 0);
-      float g1 = central_diff(a.m, x0, x1, x2, N0, N1, N2, 1);
-      float g2 = central_diff(a.m, x0, x1, x2, N0, N1, N2, 2);
-      float dot = g0 * acc[0][j] + g1 * acc[1][j] + g2 * acc[2][j];
-      float base = a.dm ? a.dm[gi] : 0.f;
-      a.q[gi] = fmaf(-a.dt, dot, base);
-    }
-  }
-}
-
-// Grid step on the matrix cores (tuned shapes): same contract as
-// k_gridstep.  Stage 1 is a complex GEMM per component (16 rows x Kh),
+// Grid step on the matrix cores (tuned shapes): the velocity or the
+// incremental-state source.  Stage 1 is a complex GEMM per component (16 rows x Kh),
 // stage 2 the real part of a complex GEMM per (component, 16-column tile);
 // a wave owns the three components of its column tiles, so the source
 // term is formed in registers.
@@ -1468,61 +1384,11 @@ __global__ void __launch_bounds__(256) k_sl(const float* __restrict__ src,
                                             float dt, G gs) {
   const int N0 = gs.N0(), N1 = gs.N1(), N2 = gs.N2();
   const long long nN = (long long)N0 * N1 * N2;
-  long long gi = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gi >= nN) return;
-  int i2 = (int)(gi % N2);
-  int i1 = (int)((gi / N2) % N1);
-  int i0 = (int)(gi / ((long long)N1 * N2));
-  float X0 = (float)i0 - dt * vel[gi] * (float)N0;
-  float X1 = (float)i1 - dt * vel[nN + gi] * (float)N1;
-  float X2 = (float)i2 - dt * vel[2 * nN + gi] * (float)N2;
-  // a non-finite velocity must not turn into an out-of-range index
-  if (!isfinite(X0)) X0 = (float)i0;
-  if (!isfinite(X1)) X1 = (float)i1;
-  if (!isfinite(X2)) X2 = (float)i2;
-  float f0 = floorf(X0), f1 = floorf(X1), f2 = floorf(X2);
-  float w0 = X0 - f0, w1 = X1 - f1, w2 = X2 - f2;
-  int a0 = (int)f0 % N0; if (a0 < 0) a0 += N0;
-  int a1 = (int)f1 % N1; if (a1 < 0) a1 += N1;
-  int a2 = (int)f2 % N2; if (a2 < 0) a2 += N2;
-  int b0 = (a0 + 1 == N0) ? 0 : a0 + 1;
-  int b1 = (a1 + 1 == N1) ? 0 : a1 + 1;
-  int b2 = (a2 + 1 == N2) ? 0 : a2 + 1;
-  auto at = [&](int u, int v, int w) { return src[((long long)u * N1 + v) * N2 + w]; };
-  float c00 = at(a0, a1, a2) + w2 * (at(a0, a1, b2) - at(a0, a1, a2));
-  float c01 = at(a0, b1, a2) + w2 * (at(a0, b1, b2) - at(a0, b1, a2));
-  float c10 = at(b0, a1, a2) + w2 * (at(b0, a1, b2) - at(b0, a1, a2));
-  float c11 = at(b0, b1, a2) + w2 * (at(b0, b1, b2) - at(b0, b1, a2));
-  float c0 = c00 + w1 * (c01 - c00);
-  float c1 = c10 + w1 * (c11 - c10);
-  dst[gi] = c0 + w0 * (c1 - c0);
-}
-
-// Periodic trilinear interpolation of f at voxel coordinates X (floor cell).
-template <class G>
-__device__ __forceinline__ float trilinear(const float* __restrict__ f, float X0, float X1, float X2, int i0,
-                                           int i1, int i2, G gs) {
-  const int N0 = gs.N0(), N1 = gs.N1(), N2 = gs.N2();
-  // a non-finite coordinate must not turn into an out-of-range index
-  if (!isfinite(X0)) X0 = (float)i0;
-  if (!isfinite(X1)) X1 = (float)i1;
-  if (!isfinite(X2)) X2 = (float)i2;
-  const float f0 = floorf(X0), f1 = floorf(X1), f2 = floorf(X2);
-  const float w0 = X0 - f0, w1 = X1 - f1, w2 = X2 - f2;
-  int a0 = (int)f0 % N0; if (a0 < 0) a0 += N0;
-  int a1 = (int)f1 % N1; if (a1 < 0) a1 += N1;
-  int a2 = (int)f2 % N2; if (a2 < 0) a2 += N2;
-  const int b0 = (a0 + 1 == N0) ? 0 : a0 + 1;
-  const int b1 = (a1 + 1 == N1) ? 0 : a1 + 1;
-  const int b2 = (a2 + 1 == N2) ? 0 : a2 + 1;
-  auto at = [&](int u, int v, int w) { return f[((long long)u * N1 + v) * N2 + w]; };
-  const float c00 = at(a0, a1, a2) + w2 * (at(a0, a1, b2) - at(a0, a1, a2));
-  const float c01 = at(a0, b1, a2) + w2 * (at(a0, b1, b2) - at(a0, b1, a2));
-  const float c10 = at(b0, a1, a2) + w2 * (at(b0, a1, b2) - at(b0, a1, a2));
-  const float c11 = at(b0, b1, a2) + w2 * (at(b0, b1, b2) - at(b0, b1, a2));
-  const float c0 = c00 + w1 * (c01 - c00);
-  const float c1 = c10 + w1 * (c11 - c10);
-  return c0 + w0 * (c1 - c0);
+  int i0, i1, i2;
+  long long gi;
+  if (!plane_point(gs, &i0, &i1, &i2, &gi)) return;
+  dst[gi] = trilinear(src, (float)i0 - dt * vel[gi] * (float)N0, (float)i1 - dt * vel[nN + gi] * (float)N1,
+                      (float)i2 - dt * vel[2 * nN + gi] * (float)N2, i0, i1, i2, gs);
 }
 
 // One transport step with midpoint departure points: X_h = x - dt/2 v(x),
@@ -1532,9 +1398,9 @@ __global__ void __launch_bounds__(256) k_sl_rk2(const float* __restrict__ src, c
                                                 float* __restrict__ dst, float dt, G gs) {
   const int N0 = gs.N0(), N1 = gs.N1(), N2 = gs.N2();
   const long long nN = (long long)N0 * N1 * N2;
-  const long long gi = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gi >= nN) return;
-  const int i2 = (int)(gi % N2), i1 = (int)((gi / N2) % N1), i0 = (int)(gi / ((long long)N1 * N2));
+  int i0, i1, i2;
+  long long gi;
+  if (!plane_point(gs, &i0, &i1, &i2, &gi)) return;
   const float h0 = (float)i0 - 0.5f * dt * vel[gi] * (float)N0;
   const float h1 = (float)i1 - 0.5f * dt * vel[nN + gi] * (float)N1;
   const float h2 = (float)i2 - 0.5f * dt * vel[2 * nN + gi] * (float)N2;
@@ -1615,44 +1481,19 @@ __global__ void __launch_bounds__(256) k_sl_tangent(const float* __restrict__ dm
                                                     float dt, G gs) {
   const int N0 = gs.N0(), N1 = gs.N1(), N2 = gs.N2();
   const long long nN = (long long)N0 * N1 * N2;
-  const long long gi = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gi >= nN) return;
-  const int i2 = (int)(gi % N2), i1 = (int)((gi / N2) % N1), i0 = (int)(gi / ((long long)N1 * N2));
-  float X0 = (float)i0 - dt * vel[gi] * (float)N0;
-  float X1 = (float)i1 - dt * vel[nN + gi] * (float)N1;
-  float X2 = (float)i2 - dt * vel[2 * nN + gi] * (float)N2;
-  if (!isfinite(X0)) X0 = (float)i0;
-  if (!isfinite(X1)) X1 = (float)i1;
-  if (!isfinite(X2)) X2 = (float)i2;
-  const float f0 = floorf(X0), f1 = floorf(X1), f2 = floorf(X2);
-  const float w0 = X0 - f0, w1 = X1 - f1, w2 = X2 - f2;
-  int a0 = (int)f0 % N0; if (a0 < 0) a0 += N0;
-  int a1 = (int)f1 % N1; if (a1 < 0) a1 += N1;
-  int a2 = (int)f2 % N2; if (a2 < 0) a2 += N2;
-  const int b0 = (a0 + 1 == N0) ? 0 : a0 + 1;
-  const int b1 = (a1 + 1 == N1) ? 0 : a1 + 1;
-  const int b2 = (a2 + 1 == N2) ? 0 : a2 + 1;
-  auto idx = [&](int u, int v, int w) { return ((long long)u * N1 + v) * N2 + w; };
-  const float m000 = m[idx(a0, a1, a2)], m001 = m[idx(a0, a1, b2)];
-  const float m010 = m[idx(a0, b1, a2)], m011 = m[idx(a0, b1, b2)];
-  const float m100 = m[idx(b0, a1, a2)], m101 = m[idx(b0, a1, b2)];
-  const float m110 = m[idx(b0, b1, a2)], m111 = m[idx(b0, b1, b2)];
-  const float c00 = m000 + w2 * (m001 - m000), c01 = m010 + w2 * (m011 - m010);
-  const float c10 = m100 + w2 * (m101 - m100), c11 = m110 + w2 * (m111 - m110);
-  const float c0 = c00 + w1 * (c01 - c00), c1 = c10 + w1 * (c11 - c10);
-  const float d0 = c1 - c0;
-  const float d1 = (c01 - c00) + w0 * ((c11 - c10) - (c01 - c00));
-  const float e00 = m001 - m000, e01 = m011 - m010, e10 = m101 - m100, e11 = m111 - m110;
-  const float e0 = e00 + w1 * (e01 - e00), e1 = e10 + w1 * (e11 - e10);
-  const float d2 = e0 + w0 * (e1 - e0);
+  int i0, i1, i2;
+  long long gi;
+  if (!plane_point(gs, &i0, &i1, &i2, &gi)) return;
+  const Cell c = cell_at((float)i0 - dt * vel[gi] * (float)N0, (float)i1 - dt * vel[nN + gi] * (float)N1,
+                         (float)i2 - dt * vel[2 * nN + gi] * (float)N2, i0, i1, i2, gs);
+  float v[8], d0, d1, d2;
+  corners(m, c, v, gs);
+  slopes8(v, c, &d0, &d1, &d2);
   float r = -dt * ((float)N0 * d0 * dvel[gi] + (float)N1 * d1 * dvel[nN + gi] + (float)N2 * d2 * dvel[2 * nN + gi]);
   if (dm) {
-    const float q00 = dm[idx(a0, a1, a2)] + w2 * (dm[idx(a0, a1, b2)] - dm[idx(a0, a1, a2)]);
-    const float q01 = dm[idx(a0, b1, a2)] + w2 * (dm[idx(a0, b1, b2)] - dm[idx(a0, b1, a2)]);
-    const float q10 = dm[idx(b0, a1, a2)] + w2 * (dm[idx(b0, a1, b2)] - dm[idx(b0, a1, a2)]);
-    const float q11 = dm[idx(b0, b1, a2)] + w2 * (dm[idx(b0, b1, b2)] - dm[idx(b0, b1, a2)]);
-    const float q0 = q00 + w1 * (q01 - q00), q1 = q10 + w1 * (q11 - q10);
-    r += q0 + w0 * (q1 - q0);
+    float q[8];
+    corners(dm, c, q, gs);
+    r += lerp8(q, c);
   }
   out[gi] = r;
 }
@@ -1692,49 +1533,27 @@ __global__ void __launch_bounds__(256) k_adj_src_fwd2(const float* __restrict__ 
     float g0 = 0.f, g1 = 0.f, g2 = 0.f;
     if (r < rv) {
       const long long gi = ((long long)x0 * N1 + x1) * N2 + x2;
-      float X0 = (float)x0 - dt * vel[gi] * (float)N0;
-      float X1 = (float)x1 - dt * vel[nN + gi] * (float)N1;
-      float X2 = (float)x2 - dt * vel[2 * nN + gi] * (float)N2;
-      if (!isfinite(X0)) X0 = (float)x0;
-      if (!isfinite(X1)) X1 = (float)x1;
-      if (!isfinite(X2)) X2 = (float)x2;
-      const float f0 = floorf(X0), f1 = floorf(X1), f2 = floorf(X2);
-      const float w0 = X0 - f0, w1 = X1 - f1, w2 = X2 - f2;
-      int a0 = (int)f0 % N0; if (a0 < 0) a0 += N0;
-      int a1 = (int)f1 % N1; if (a1 < 0) a1 += N1;
-      int a2 = (int)f2 % N2; if (a2 < 0) a2 += N2;
-      const int b0 = (a0 + 1 == N0) ? 0 : a0 + 1;
-      const int b1 = (a1 + 1 == N1) ? 0 : a1 + 1;
-      const int b2 = (a2 + 1 == N2) ? 0 : a2 + 1;
-      auto idx = [&](int u, int v, int w) { return ((long long)u * N1 + v) * N2 + w; };
-      const float m000 = m[idx(a0, a1, a2)], m001 = m[idx(a0, a1, b2)];
-      const float m010 = m[idx(a0, b1, a2)], m011 = m[idx(a0, b1, b2)];
-      const float m100 = m[idx(b0, a1, a2)], m101 = m[idx(b0, a1, b2)];
-      const float m110 = m[idx(b0, b1, a2)], m111 = m[idx(b0, b1, b2)];
-      // the interpolant's slopes in the cell (lerps of the edge differences)
-      const float c00 = m000 + w2 * (m001 - m000), c01 = m010 + w2 * (m011 - m010);
-      const float c10 = m100 + w2 * (m101 - m100), c11 = m110 + w2 * (m111 - m110);
-      const float c0 = c00 + w1 * (c01 - c00), c1 = c10 + w1 * (c11 - c10);
-      const float d0 = c1 - c0;
-      const float d1 = (c01 - c00) + w0 * ((c11 - c10) - (c01 - c00));
-      const float e00 = m001 - m000, e01 = m011 - m010, e10 = m101 - m100, e11 = m111 - m110;
-      const float e0 = e00 + w1 * (e01 - e00), e1 = e10 + w1 * (e11 - e10);
-      const float d2 = e0 + w0 * (e1 - e0);
+      const Cell c = cell_at((float)x0 - dt * vel[gi] * (float)N0, (float)x1 - dt * vel[nN + gi] * (float)N1,
+                             (float)x2 - dt * vel[2 * nN + gi] * (float)N2, x0, x1, x2, gs);
+      float v[8], d0, d1, d2;
+      corners(m, c, v, gs);
+      slopes8(v, c, &d0, &d1, &d2);
       const float l = lam[gi];
       const float s = -dt * coef * l;
       g0 = s * (float)N0 * d0;
       g1 = s * (float)N1 * d1;
       g2 = s * (float)N2 * d2;
       // transpose of the interpolation
-      const float u0 = 1.f - w0, u1 = 1.f - w1, u2 = 1.f - w2;
-      atomicAdd(lam_out + idx(a0, a1, a2), l * u0 * u1 * u2);
-      atomicAdd(lam_out + idx(a0, a1, b2), l * u0 * u1 * w2);
-      atomicAdd(lam_out + idx(a0, b1, a2), l * u0 * w1 * u2);
-      atomicAdd(lam_out + idx(a0, b1, b2), l * u0 * w1 * w2);
-      atomicAdd(lam_out + idx(b0, a1, a2), l * w0 * u1 * u2);
-      atomicAdd(lam_out + idx(b0, a1, b2), l * w0 * u1 * w2);
-      atomicAdd(lam_out + idx(b0, b1, a2), l * w0 * w1 * u2);
-      atomicAdd(lam_out + idx(b0, b1, b2), l * w0 * w1 * w2);
+      const float w0 = c.w0, w1 = c.w1, w2 = c.w2, u0 = 1.f - w0, u1 = 1.f - w1, u2 = 1.f - w2;
+      const int b2 = (c.a2 + 1 == N2) ? 0 : c.a2 + 1;
+      atomicAdd(lam_out + (c.r[0] + c.a2), l * u0 * u1 * u2);
+      atomicAdd(lam_out + (c.r[0] + b2), l * u0 * u1 * w2);
+      atomicAdd(lam_out + (c.r[1] + c.a2), l * u0 * w1 * u2);
+      atomicAdd(lam_out + (c.r[1] + b2), l * u0 * w1 * w2);
+      atomicAdd(lam_out + (c.r[2] + c.a2), l * w0 * u1 * u2);
+      atomicAdd(lam_out + (c.r[2] + b2), l * w0 * u1 * w2);
+      atomicAdd(lam_out + (c.r[3] + c.a2), l * w0 * w1 * u2);
+      atomicAdd(lam_out + (c.r[3] + b2), l * w0 * w1 * w2);
     }
     vals[p] = g0;
     vals[P + p] = g1;
@@ -1830,9 +1649,7 @@ __global__ void __launch_bounds__(256) k_rho_fwd2(RhoArgs a, float2* __restrict_
       if (!isfinite(X2)) X2 = (float)x2;
       const float f0 = floorf(X0), f1 = floorf(X1), f2 = floorf(X2);
       const float w0 = X0 - f0, w1 = X1 - f1, w2 = X2 - f2;
-      int a0 = (int)f0 % N0; if (a0 < 0) a0 += N0;
-      int a1 = (int)f1 % N1; if (a1 < 0) a1 += N1;
-      int a2 = (int)f2 % N2; if (a2 < 0) a2 += N2;
+      const int a0 = wrap((int)f0, N0), a1 = wrap((int)f1, N1), a2 = wrap((int)f2, N2);
       const int b0 = (a0 + 1 == N0) ? 0 : a0 + 1;
       const int b1 = (a1 + 1 == N1) ? 0 : a1 + 1;
       const int b2 = (a2 + 1 == N2) ? 0 : a2 + 1;
@@ -2393,28 +2210,6 @@ __global__ void k_pcg_update_d(const double* sc, const float2* r, float2* dv, in
 }
 
 // ================================================= launch wrappers
-static bool grid_iso(const Dims& d, int N, int K) {
-  return d.N[0] == N && d.N[1] == N && d.N[2] == N && d.K[1] == K && d.K[2] == K;
-}
-static bool grid_is(const Dims& d, int A, int B, int C, int K) {
-  return d.N[0] == A && d.N[1] == B && d.N[2] == C && d.K[1] == K && d.K[2] == K;
-}
-template <class F>
-static hipError_t with_grid(const Dims& d, F&& f) {
-  // the measured volume, the 64^3 problem and the grids of the atlas
-  // batch and of the differentiation volume, with bands 24^3 and 32^3
-  if (grid_iso(d, 128, 32)) return f(GridIso<128, 32>{});
-  if (grid_iso(d, 64, 16)) return f(GridIso<64, 16>{});
-  if (grid_iso(d, 128, 24)) return f(GridIso<128, 24>{});
-  if (grid_iso(d, 96, 24)) return f(GridIso<96, 24>{});
-  if (grid_iso(d, 96, 32)) return f(GridIso<96, 32>{});
-  if (grid_is(d, 144, 176, 144, 24)) return f(GridShape<144, 176, 144, 24>{});
-  if (grid_is(d, 144, 176, 144, 32)) return f(GridShape<144, 176, 144, 32>{});
-  if (grid_is(d, 160, 192, 160, 24)) return f(GridShape<160, 192, 160, 24>{});
-  if (grid_is(d, 160, 192, 160, 32)) return f(GridShape<160, 192, 160, 32>{});
-  return f(GridDyn{d.N[0], d.N[1], d.N[2], d.K[1], d.Kh});
-}
-
 hipError_t launch_full_to_half(const float2* full, float2* half, const Dims& d, hipStream_t st) {
   hipLaunchKernelGGL(k_full_to_half, dim3(nblk(3LL * d.nb, 256)), dim3(256), 0, st, full, half,
                      d.K[0], d.K[1], d.K[2]);
@@ -2748,6 +2543,8 @@ hipError_t launch_fwd0(const Fwd0Jobs& jobs, int njobs, const float2* tw, const 
   return hipGetLastError();
 }
 
+// Limits on the problem sizes (validated at the boundary): the LDS tiles of a
+// grid step with all its tables, and of the image-term sources.
 size_t gridstep_shared_bytes(const Dims& d) {
   const int C = d.K[1] * d.Kh;
   return (3 * (size_t)C + 3 * (size_t)kGridRows * d.Kh + (size_t)kGridRows * d.K[1] +
@@ -2759,46 +2556,28 @@ size_t src_shared_bytes(const Dims& d) {
          (size_t)d.Kh * d.N[2] * sizeof(float2);
 }
 
-hipError_t launch_gridstep(const GridStepArgs& a, const Dims& d, const Twiddles& tw, hipStream_t st) {
-  const int C = d.K[1] * d.Kh;
-  dim3 grid(nblk(d.N[1], kGridRows), d.N[0]);
-  size_t shm = gridstep_shared_bytes(d);
+hipError_t launch_gridstep(const GridStepArgs& a, const Dims& d, const Twiddles& tw, const Frags& fr, hipStream_t st) {
   {
-    const double nN = (double)d.nN;
-    double fl = 3.0 * d.N[0] * d.N[1] * d.Kh * d.K[1] * 8.0 + 3.0 * nN * d.Kh * 4.0 + (a.op ? 15.0 * nN : 0.0);
-    double by = 3.0 * d.N[0] * (double)C * 8.0 + (a.op ? (a.dm ? 12.0 : 8.0) * nN : 12.0 * nN);
-    timer_work(KF_GRID, fl, by);
+    const double nN = (double)d.nN, C = (double)d.K[1] * d.Kh;
+    const double fl = 3.0 * d.N[0] * d.N[1] * C * 8.0 + 3.0 * nN * d.Kh * 4.0 +
+                      (a.op == GRID_SOURCE ? 15.0 * nN : a.op == GRID_TRANSPORT ? 40.0 * nN : 0.0);
+    const double pts = a.op == GRID_SOURCE ? (a.dm ? 12.0 : 8.0) : (a.vout ? 12.0 : 0.0) + (a.op == GRID_TRANSPORT ? 8.0 : 0.0);
+    timer_work(KF_GRID, fl, 3.0 * d.N[0] * C * 8.0 + pts * nN);
   }
-  hipError_t e;
-  // the compile-time grid shapes take the matrix-core kernel
-  bool done = false;
-  e = with_grid(d, [&](auto gs) -> hipError_t {
+  if (a.op == GRID_TRANSPORT || !grid_instantiated(d)) return launch_gridstep_chain(a, d, fr, st);
+  if (!tw.inv1 || !tw.inv2) return hipErrorInvalidValue;
+  const dim3 grid(d.N[1] / kGridRows, d.N[0]);
+  return with_grid(d, [&](auto gs) -> hipError_t {
     using G = decltype(gs);
     if constexpr (G::kStatic) {
       static_assert(G::N1() % kGridRows == 0 && G::N2() % 16 == 0 && G::K1() % 4 == 0, "matrix-core grid shape");
-      done = true;
       if (d.prec)
         LAUNCH_TIMED(KF_GRID, (k_gridstep_mfma<G, true>), grid, dim3(256), 0, st, a, tw);
       else
         LAUNCH_TIMED(KF_GRID, (k_gridstep_mfma<G, false>), grid, dim3(256), 0, st, a, tw);
-      return hipGetLastError();
     }
-    return hipSuccess;
+    return hipGetLastError();
   });
-  if (!done) {
-    const int jn = (d.N[2] + 15) / 16;
-    GridDyn gs{d.N[0], d.N[1], d.N[2], d.K[1], d.Kh};
-    if (jn <= 2)
-      LAUNCH_TIMED(KF_GRID, (k_gridstep<2, GridDyn>), grid, dim3(256), shm, st, a, tw, gs);
-    else if (jn <= 4)
-      LAUNCH_TIMED(KF_GRID, (k_gridstep<4, GridDyn>), grid, dim3(256), shm, st, a, tw, gs);
-    else if (jn <= 8)
-      LAUNCH_TIMED(KF_GRID, (k_gridstep<8, GridDyn>), grid, dim3(256), shm, st, a, tw, gs);
-    else
-      LAUNCH_TIMED(KF_GRID, (k_gridstep<16, GridDyn>), grid, dim3(256), shm, st, a, tw, gs);
-    e = hipGetLastError();
-  }
-  return e;
 }
 
 hipError_t launch_sl(const float* src, const float* vel, float* dst, float dt, const Dims& d,
@@ -2806,7 +2585,7 @@ hipError_t launch_sl(const float* src, const float* vel, float* dst, float dt, c
   timer_work(KF_SL, 40.0 * (double)d.nN, 20.0 * (double)d.nN);
   const int T = (d.tile_sl == 64 || d.tile_sl == 128) ? d.tile_sl : 256;
   hipError_t e = with_grid(d, [&](auto gs) {
-    LAUNCH_TIMED(KF_SL, (k_sl<decltype(gs)>), dim3(nblk(d.nN, T)), dim3(T), 0, st, src, vel, dst, dt, gs);
+    LAUNCH_TIMED(KF_SL, (k_sl<decltype(gs)>), dim3(nblk((long long)d.N[1] * d.N[2], T), d.N[0]), dim3(T), 0, st, src, vel, dst, dt, gs);
     return hipGetLastError();
   });
   return e;
@@ -2816,7 +2595,7 @@ hipError_t launch_sl_rk2(const float* src, const float* vel, float* dst, float d
                          hipStream_t st) {
   timer_work(KF_SL, 140.0 * (double)d.nN, 20.0 * (double)d.nN);
   return with_grid(d, [&](auto gs) {
-    LAUNCH_TIMED(KF_SL, (k_sl_rk2<decltype(gs)>), dim3(nblk(d.nN, 256)), dim3(256), 0, st, src, vel, dst, dt, gs);
+    LAUNCH_TIMED(KF_SL, (k_sl_rk2<decltype(gs)>), dim3(nblk((long long)d.N[1] * d.N[2], 256), d.N[0]), dim3(256), 0, st, src, vel, dst, dt, gs);
     return hipGetLastError();
   });
 }
@@ -2842,7 +2621,7 @@ hipError_t launch_sl_tangent(const float* dm, const float* m, const float* vel, 
                              float dt, const Dims& d, hipStream_t st) {
   timer_work(KF_SL, 90.0 * (double)d.nN, ((dm ? 8.0 : 4.0) + 12.0 + 12.0 + 4.0) * (double)d.nN);
   return with_grid(d, [&](auto gs) {
-    LAUNCH_TIMED(KF_SL, (k_sl_tangent<decltype(gs)>), dim3(nblk(d.nN, 256)), dim3(256), 0, st, dm, m, vel, dvel,
+    LAUNCH_TIMED(KF_SL, (k_sl_tangent<decltype(gs)>), dim3(nblk((long long)d.N[1] * d.N[2], 256), d.N[0]), dim3(256), 0, st, dm, m, vel, dvel,
                  out, dt, gs);
     return hipGetLastError();
   });

@@ -53,6 +53,8 @@ struct Op<false> {
   static __device__ __forceinline__ floatx4 mma(float x, float y, floatx4 acc) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, acc, 0, 0, 0);
   }
+  // the B form as the first operand: the transposed tile
+  static __device__ __forceinline__ floatx4 mma_t(float y, float x, floatx4 acc) { return mma(y, x, acc); }
 };
 template <>
 struct Op<true> {
@@ -60,6 +62,7 @@ struct Op<true> {
   static __device__ __forceinline__ shortx4 a(float x) { return bf3_a(x); }
   static __device__ __forceinline__ shortx4 b(float x) { return bf3_b(x); }
   static __device__ __forceinline__ floatx4 mma(shortx4 x, shortx4 y, floatx4 acc) { return mma_bf3(x, y, acc); }
+  static __device__ __forceinline__ floatx4 mma_t(shortx4 y, shortx4 x, floatx4 acc) { return mma_bf3(y, x, acc); }
 };
 
 // Index of this wave in its block, as a value the compiler knows to be the same

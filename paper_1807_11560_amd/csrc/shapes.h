@@ -81,4 +81,33 @@ hipError_t with_band(const Dims& d, F&& f) {
   if (band_iso(d, 24, 36)) return f(BandIso<24, 36>{});
   return f(BandDyn{d.K[0], d.K[1], d.Kh, d.M[0], d.M[1], d.M[2]});
 }
+inline bool grid_iso(const Dims& d, int N, int K) {
+  return d.N[0] == N && d.N[1] == N && d.N[2] == N && d.K[1] == K && d.K[2] == K;
+}
+inline bool grid_is(const Dims& d, int A, int B, int C, int K) {
+  return d.N[0] == A && d.N[1] == B && d.N[2] == C && d.K[1] == K && d.K[2] == K;
+}
+template <class F>
+hipError_t with_grid(const Dims& d, F&& f) {
+  // the measured volume, the 64^3 problem and the grids of the atlas
+  // batch and of the differentiation volume, with bands 24^3 and 32^3
+  if (grid_iso(d, 128, 32)) return f(GridIso<128, 32>{});
+  if (grid_iso(d, 64, 16)) return f(GridIso<64, 16>{});
+  if (grid_iso(d, 128, 24)) return f(GridIso<128, 24>{});
+  if (grid_iso(d, 96, 24)) return f(GridIso<96, 24>{});
+  if (grid_iso(d, 96, 32)) return f(GridIso<96, 32>{});
+  if (grid_is(d, 144, 176, 144, 24)) return f(GridShape<144, 176, 144, 24>{});
+  if (grid_is(d, 144, 176, 144, 32)) return f(GridShape<144, 176, 144, 32>{});
+  if (grid_is(d, 160, 192, 160, 24)) return f(GridShape<160, 192, 160, 24>{});
+  if (grid_is(d, 160, 192, 160, 32)) return f(GridShape<160, 192, 160, 32>{});
+  return f(GridDyn{d.N[0], d.N[1], d.N[2], d.K[1], d.Kh});
+}
+inline bool grid_instantiated(const Dims& d) {
+  bool is = false;
+  (void)with_grid(d, [&](auto gs) {
+    is = decltype(gs)::kStatic;
+    return hipSuccess;
+  });
+  return is;
+}
 }  // namespace lddmm
