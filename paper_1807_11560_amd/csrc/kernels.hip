@@ -1115,123 +1115,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))
   }
 }
 
-// ----------------------------------------------- forward stage 1 (x1)
-template <int QT>
-__global__ void __launch_bounds__(128) k_fwd1(Fwd1Jobs jobs, const float2* __restrict__ tw, int G0,
-                                              int G1, int K1, int Kh) {
-  extern __shared__ float2 sh[];
-  const Fwd1Job job = jobs.j[blockIdx.z];
-  const int qb = blockIdx.y * QT;
-  batched_fill<float2>(QT * G1, [&](int i) {
-    int t = i / G1, x = i % G1;
-    int q = qb + t;
-    return (q < K1) ? tw[(size_t)q * G1 + x] : make_float2(0.f, 0.f);
-  }, [&](int i, float2 v) { sh[i] = v; });
-  __syncthreads();
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;  // (x0, kh)
-  if (e >= G0 * Kh) return;
-  const int x0 = e / Kh, kh = e % Kh;
-  float2 acc[QT];
-#pragma unroll
-  for (int t = 0; t < QT; ++t) acc[t] = make_float2(0.f, 0.f);
-  const float2* src = job.in + (size_t)x0 * G1 * Kh + kh;
-  for (int x = 0; x < G1; ++x) {
-    float2 val = src[(size_t)x * Kh];
-#pragma unroll
-    for (int t = 0; t < QT; ++t) cmac(acc[t], sh[t * G1 + x], val);
-  }
-#pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    int q = qb + t;
-    if (q < K1) job.out[((size_t)x0 * Kh + kh) * K1 + q] = acc[t];
-  }
-}
-
-// ------------------------------------- forward stage 0 (x0) + epilogue
-template <int QT>
-__global__ void __launch_bounds__(128) k_fwd0(Fwd0Jobs jobs, const float2* __restrict__ tw,
-                                              const float* __restrict__ Ksym, int G0, int K0,
-                                              int K1, int Kh, float invG) {
-  extern __shared__ float2 sh[];
-  const Fwd0Job job = jobs.j[blockIdx.z];
-  const int qb = blockIdx.y * QT;
-  batched_fill<float2>(QT * G0, [&](int i) {
-    int t = i / G0, x = i % G0;
-    int q = qb + t;
-    return (q < K0) ? tw[(size_t)q * G0 + x] : make_float2(0.f, 0.f);
-  }, [&](int i, float2 v) { sh[i] = v; });
-  __syncthreads();
-  const int C = K1 * Kh;
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= C) return;
-  float2 aa[QT], bb[QT];
-#pragma unroll
-  for (int t = 0; t < QT; ++t) { aa[t] = make_float2(0.f, 0.f); bb[t] = make_float2(0.f, 0.f); }
-  for (int x = 0; x < G0; ++x) {
-    float2 va = job.a[(size_t)x * C + c];
-#pragma unroll
-    for (int t = 0; t < QT; ++t) cmac(aa[t], sh[t * G0 + x], va);
-  }
-  if (job.b) {
-    for (int x = 0; x < G0; ++x) {
-      float2 vb = job.b[(size_t)x * C + c];
-#pragma unroll
-      for (int t = 0; t < QT; ++t) cmac(bb[t], sh[t * G0 + x], vb);
-    }
-  }
-  const int q1 = c % K1, kh = c / K1;  // input column c = kh K1 + q1
-#pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    int q0 = qb + t;
-    if (q0 >= K0) continue;
-    size_t idx = ((size_t)kh * K0 + q0) * K1 + q1;
-    float2 r = make_float2(0.f, 0.f);
-    if (q0 != K0 / 2 && q1 != K1 / 2) {
-      if (job.base) r = job.base[idx];
-      float ks = Ksym[idx];
-      float sa = job.ca * invG * (job.syma ? ks : 1.f);
-      r.x = fmaf(sa, aa[t].x, r.x);
-      r.y = fmaf(sa, aa[t].y, r.y);
-      if (job.b) {
-        float sb = job.cb * invG * (job.symb ? ks : 1.f);
-        r.x = fmaf(sb, bb[t].x, r.x);
-        r.y = fmaf(sb, bb[t].y, r.y);
-      }
-      if (job.extra) {
-        float2 e = job.extra[idx];
-        r.x = fmaf(job.ce, e.x, r.x);
-        r.y = fmaf(job.ce, e.y, r.y);
-      }
-    }
-    job.out[idx] = r;
-    if (job.out2) {
-      float2 r2 = make_float2(0.f, 0.f);
-      if (q0 != K0 / 2 && q1 != K1 / 2) {
-        const float s2 = job.ca * invG * Ksym[idx];
-        r2.x = fmaf(s2, aa[t].x, 0.f);
-        r2.y = fmaf(s2, aa[t].y, 0.f);
-      }
-      job.out2[idx] = r2;
-    }
-  }
-}
-
 // ----------------------------------------------------- grid kernels (N)
 constexpr int kGridRows = 16;  // rows of x1 per block of the source kernels
-
-__device__ __forceinline__ float central_diff(const float* __restrict__ m, int x0, int x1, int x2,
-                                              int N0, int N1, int N2, int axis) {
-  if (axis == 0) {
-    int p = (x0 + 1 == N0) ? 0 : x0 + 1, q = (x0 == 0) ? N0 - 1 : x0 - 1;
-    return (m[((long long)p * N1 + x1) * N2 + x2] - m[((long long)q * N1 + x1) * N2 + x2]) * (0.5f * N0);
-  }
-  if (axis == 1) {
-    int p = (x1 + 1 == N1) ? 0 : x1 + 1, q = (x1 == 0) ? N1 - 1 : x1 - 1;
-    return (m[((long long)x0 * N1 + p) * N2 + x2] - m[((long long)x0 * N1 + q) * N2 + x2]) * (0.5f * N1);
-  }
-  int p = (x2 + 1 == N2) ? 0 : x2 + 1, q = (x2 == 0) ? N2 - 1 : x2 - 1;
-  return (m[((long long)x0 * N1 + x1) * N2 + p] - m[((long long)x0 * N1 + x1) * N2 + q]) * (0.5f * N2);
-}
 
 // Grid step on the matrix cores (tuned shapes): the velocity or the
 // incremental-state source.  Stage 1 is a complex GEMM per component (16 rows x Kh),
@@ -1411,64 +1296,6 @@ __global__ void __launch_bounds__(256) k_sl_rk2(const float* __restrict__ src, c
                       (float)i2 - dt * v2 * (float)N2, i0, i1, i2, gs);
 }
 
-// ------------------- image-term source and forward stage 2 (N grid)
-// s_j = coef * [(a - b) * d_j m + res * d_j a] (periodic central
-// differences; b and res may be null) at the points of 16 x1 rows of plane x0, contracted
-// over x2: s1[j][x0][x1][kh].
-template <class G>
-__global__ void __launch_bounds__(256) k_src_fwd2(const float* __restrict__ a,
-                                                  const float* __restrict__ b,
-                                                  const float* __restrict__ res,
-                                                  const float* __restrict__ m, float coef,
-                                                  float2* __restrict__ s1, Twiddles tw, G gs) {
-  extern __shared__ float shs[];
-  const int N0 = gs.N0(), N1 = gs.N1(), N2 = gs.N2(), Kh = gs.Kh();
-  constexpr int R = kGridRows;
-  const int x0 = blockIdx.y;
-  const int x1b = blockIdx.x * R;
-  const int rv = min(R, N1 - x1b);
-  const int P = R * N2;
-  float* vals = shs;                                   // [3][R][N2]
-  float2* wfx = (float2*)(vals + ((3 * P + 3) & ~3));  // [N2][Kh]
-  batched_fill<float2>(Kh * N2, [&](int i) {
-    int x2 = i / Kh, kh = i % Kh;
-    return tw.fwd2[(size_t)kh * N2 + x2];
-  }, [&](int i, float2 v) { wfx[i] = v; });
-  for (int p = threadIdx.x; p < R * N2; p += blockDim.x) {
-    int r = p / N2, x2 = p % N2;
-    int x1 = x1b + r;
-    float v0 = 0.f, v1 = 0.f, v2 = 0.f;
-    if (r < rv) {
-      long long gi = ((long long)x0 * N1 + x1) * N2 + x2;
-      float s = coef * (a[gi] - (b ? b[gi] : 0.f));
-      v0 = s * central_diff(m, x0, x1, x2, N0, N1, N2, 0);
-      v1 = s * central_diff(m, x0, x1, x2, N0, N1, N2, 1);
-      v2 = s * central_diff(m, x0, x1, x2, N0, N1, N2, 2);
-      if (res) {
-        const float t = coef * res[gi];
-        v0 = fmaf(t, central_diff(a, x0, x1, x2, N0, N1, N2, 0), v0);
-        v1 = fmaf(t, central_diff(a, x0, x1, x2, N0, N1, N2, 1), v1);
-        v2 = fmaf(t, central_diff(a, x0, x1, x2, N0, N1, N2, 2), v2);
-      }
-    }
-    vals[p] = v0;
-    vals[P + p] = v1;
-    vals[2 * P + p] = v2;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 3 * rv * Kh; i += blockDim.x) {
-    int j = i / (rv * Kh), r = (i / Kh) % rv, kh = i % Kh;
-    const float* row = vals + (size_t)j * P + r * N2;
-    float2 acc = make_float2(0.f, 0.f);
-    for (int x2 = 0; x2 < N2; ++x2) {
-      float2 w = wfx[(size_t)x2 * Kh + kh];
-      acc.x = fmaf(row[x2], w.x, acc.x);
-      acc.y = fmaf(row[x2], w.y, acc.y);
-    }
-    s1[(((size_t)j * N0 + x0) * N1 + x1b + r) * Kh + kh] = acc;
-  }
-}
-
 // ------------------------------ tangent of one semi-Lagrangian step (N)
 // The derivative of m_{n+1}(x) = I[m_n](X(x)), X(x) = x - dt v(x), in the
 // direction (dm_n, dv): dm_{n+1}(x) = I[dm_n](X) - dt sum_j N_j
@@ -1496,81 +1323,6 @@ __global__ void __launch_bounds__(256) k_sl_tangent(const float* __restrict__ dm
     r += lerp8(q, c);
   }
   out[gi] = r;
-}
-
-// ----------- exact adjoint of one semi-Lagrangian step, forward stage 2
-// The reverse of m_{n+1}(x) = I[m_n](X(x)), X(x) = x - dt v(x) (voxels per
-// axis, the departure point k_sl computes).  For the state adjoint lam of
-// m_{n+1} (held as lam / coef): the transpose of the interpolation scatters
-// lam(x) with the trilinear weights onto the eight corners of X(x) in
-// lam_out (zero on entry; atomic adds), and the derivative with respect to
-// the grid velocity, s_j(x) = -dt N_j coef lam(x) (d_j I[m_n])(X(x)) with the
-// interpolant's exact slope in the cell of X, is contracted over x2 as in
-// k_src_fwd2: s1[j][x0][x1][kh].
-template <class G>
-__global__ void __launch_bounds__(256) k_adj_src_fwd2(const float* __restrict__ lam,
-                                                      const float* __restrict__ m,
-                                                      const float* __restrict__ vel,
-                                                      float* __restrict__ lam_out, float coef, float dt,
-                                                      float2* __restrict__ s1, Twiddles tw, G gs) {
-  extern __shared__ float shs[];
-  const int N0 = gs.N0(), N1 = gs.N1(), N2 = gs.N2(), Kh = gs.Kh();
-  const long long nN = (long long)N0 * N1 * N2;
-  constexpr int R = kGridRows;
-  const int x0 = blockIdx.y;
-  const int x1b = blockIdx.x * R;
-  const int rv = min(R, N1 - x1b);
-  const int P = R * N2;
-  float* vals = shs;                                   // [3][R][N2]
-  float2* wfx = (float2*)(vals + ((3 * P + 3) & ~3));  // [N2][Kh]
-  batched_fill<float2>(Kh * N2, [&](int i) {
-    int x2 = i / Kh, kh = i % Kh;
-    return tw.fwd2[(size_t)kh * N2 + x2];
-  }, [&](int i, float2 v) { wfx[i] = v; });
-  for (int p = threadIdx.x; p < R * N2; p += blockDim.x) {
-    const int r = p / N2, x2 = p % N2;
-    const int x1 = x1b + r;
-    float g0 = 0.f, g1 = 0.f, g2 = 0.f;
-    if (r < rv) {
-      const long long gi = ((long long)x0 * N1 + x1) * N2 + x2;
-      const Cell c = cell_at((float)x0 - dt * vel[gi] * (float)N0, (float)x1 - dt * vel[nN + gi] * (float)N1,
-                             (float)x2 - dt * vel[2 * nN + gi] * (float)N2, x0, x1, x2, gs);
-      float v[8], d0, d1, d2;
-      corners(m, c, v, gs);
-      slopes8(v, c, &d0, &d1, &d2);
-      const float l = lam[gi];
-      const float s = -dt * coef * l;
-      g0 = s * (float)N0 * d0;
-      g1 = s * (float)N1 * d1;
-      g2 = s * (float)N2 * d2;
-      // transpose of the interpolation
-      const float w0 = c.w0, w1 = c.w1, w2 = c.w2, u0 = 1.f - w0, u1 = 1.f - w1, u2 = 1.f - w2;
-      const int b2 = (c.a2 + 1 == N2) ? 0 : c.a2 + 1;
-      atomicAdd(lam_out + (c.r[0] + c.a2), l * u0 * u1 * u2);
-      atomicAdd(lam_out + (c.r[0] + b2), l * u0 * u1 * w2);
-      atomicAdd(lam_out + (c.r[1] + c.a2), l * u0 * w1 * u2);
-      atomicAdd(lam_out + (c.r[1] + b2), l * u0 * w1 * w2);
-      atomicAdd(lam_out + (c.r[2] + c.a2), l * w0 * u1 * u2);
-      atomicAdd(lam_out + (c.r[2] + b2), l * w0 * u1 * w2);
-      atomicAdd(lam_out + (c.r[3] + c.a2), l * w0 * w1 * u2);
-      atomicAdd(lam_out + (c.r[3] + b2), l * w0 * w1 * w2);
-    }
-    vals[p] = g0;
-    vals[P + p] = g1;
-    vals[2 * P + p] = g2;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 3 * rv * Kh; i += blockDim.x) {
-    int j = i / (rv * Kh), r = (i / Kh) % rv, kh = i % Kh;
-    const float* row = vals + (size_t)j * P + r * N2;
-    float2 acc = make_float2(0.f, 0.f);
-    for (int x2 = 0; x2 < N2; ++x2) {
-      float2 w = wfx[(size_t)x2 * Kh + kh];
-      acc.x = fmaf(row[x2], w.x, acc.x);
-      acc.y = fmaf(row[x2], w.y, acc.y);
-    }
-    s1[(((size_t)j * N0 + x0) * N1 + x1b + r) * Kh + kh] = acc;
-  }
 }
 
 // ------------- deformation-state image term and forward stage 2 (N grid)
@@ -1608,105 +1360,6 @@ __global__ void __launch_bounds__(256) k_image_derivs(const float* __restrict__ 
   reinterpret_cast<float4*>(H)[2 * gi + 1] =
       make_float4((at(0, 1, 1) - at(0, 1, -1) - at(0, -1, 1) + at(0, -1, -1)) * (0.25f * n[1] * n[2]),
                   (at(0, 0, 2) - 2.f * c + at(0, 0, -2)) * (0.25f * n[2] * n[2]), 0.f, 0.f);
-}
-
-// At phi(x) = x + u(x) (voxel coordinates x_j + N_j u_j) the periodic
-// trilinear interpolation of I0, of its central-difference gradient G and
-// (full Newton) of its central-difference Hessian H gives m, g and h.
-// op 0: s_j = coef (m - I1) g_j.  op 1: s_j = coef (g . du) g_j
-// [+ coef res (h du)_j when res is set].  Then forward stage 2 of the three
-// sources like k_src_fwd2.
-template <class G>
-__global__ void __launch_bounds__(256) k_rho_fwd2(RhoArgs a, float2* __restrict__ s1, Twiddles tw, G gs) {
-  extern __shared__ float shs[];
-  const int N0 = gs.N0(), N1 = gs.N1(), N2 = gs.N2(), Kh = gs.Kh();
-  const long long nN = (long long)N0 * N1 * N2;
-  constexpr int R = kGridRows;
-  const int x0 = blockIdx.y;
-  const int x1b = blockIdx.x * R;
-  const int rv = min(R, N1 - x1b);
-  const int P = R * N2;
-  float* vals = shs;                                   // [3][R][N2]
-  float2* wfx = (float2*)(vals + ((3 * P + 3) & ~3));  // [N2][Kh]
-  batched_fill<float2>(Kh * N2, [&](int i) {
-    int x2 = i / Kh, kh = i % Kh;
-    return tw.fwd2[(size_t)kh * N2 + x2];
-  }, [&](int i, float2 v) { wfx[i] = v; });
-  // two points per iteration, so that two chains of dependent loads are in flight
-#pragma unroll 2
-  for (int p = threadIdx.x; p < R * N2; p += blockDim.x) {
-    const int r = p / N2, x2 = p % N2;
-    const int x1 = x1b + r;
-    float v0 = 0.f, v1 = 0.f, v2 = 0.f;
-    if (r < rv) {
-      const long long gi = ((long long)x0 * N1 + x1) * N2 + x2;
-      float X0 = (float)x0 + a.u[gi] * (float)N0;
-      float X1 = (float)x1 + a.u[nN + gi] * (float)N1;
-      float X2 = (float)x2 + a.u[2 * nN + gi] * (float)N2;
-      // a non-finite displacement must not turn into an out-of-range index
-      if (!isfinite(X0)) X0 = (float)x0;
-      if (!isfinite(X1)) X1 = (float)x1;
-      if (!isfinite(X2)) X2 = (float)x2;
-      const float f0 = floorf(X0), f1 = floorf(X1), f2 = floorf(X2);
-      const float w0 = X0 - f0, w1 = X1 - f1, w2 = X2 - f2;
-      const int a0 = wrap((int)f0, N0), a1 = wrap((int)f1, N1), a2 = wrap((int)f2, N2);
-      const int b0 = (a0 + 1 == N0) ? 0 : a0 + 1;
-      const int b1 = (a1 + 1 == N1) ? 0 : a1 + 1;
-      const int b2 = (a2 + 1 == N2) ? 0 : a2 + 1;
-      const long long r00 = ((long long)a0 * N1 + a1) * N2, r01 = ((long long)a0 * N1 + b1) * N2;
-      const long long r10 = ((long long)b0 * N1 + a1) * N2, r11 = ((long long)b0 * N1 + b1) * N2;
-      // the four (or eight) channels of a point are one 16-byte load per corner
-      auto lerp4 = [](float4 p, float4 q, float w) {
-        return make_float4(p.x + w * (q.x - p.x), p.y + w * (q.y - p.y), p.z + w * (q.z - p.z),
-                           p.w + w * (q.w - p.w));
-      };
-      auto interp4 = [&](const float4* f, int stride) {
-        const float4 c00 = lerp4(f[stride * (r00 + a2)], f[stride * (r00 + b2)], w2);
-        const float4 c01 = lerp4(f[stride * (r01 + a2)], f[stride * (r01 + b2)], w2);
-        const float4 c10 = lerp4(f[stride * (r10 + a2)], f[stride * (r10 + b2)], w2);
-        const float4 c11 = lerp4(f[stride * (r11 + a2)], f[stride * (r11 + b2)], w2);
-        return lerp4(lerp4(c00, c01, w1), lerp4(c10, c11, w1), w0);
-      };
-      const float4 ig = interp4(reinterpret_cast<const float4*>(a.G), 1);  // (I0, d0, d1, d2)
-      const float g0 = ig.y, g1 = ig.z, g2 = ig.w;
-      if (a.op == 0) {
-        const float l = a.coef * (ig.x - a.I1[gi]);
-        v0 = l * g0;
-        v1 = l * g1;
-        v2 = l * g2;
-      } else {
-        const float du0 = a.du[gi], du1 = a.du[nN + gi], du2 = a.du[2 * nN + gi];
-        const float l = a.coef * (g0 * du0 + g1 * du1 + g2 * du2);
-        v0 = l * g0;
-        v1 = l * g1;
-        v2 = l * g2;
-        if (a.res) {
-          const float4 ha = interp4(reinterpret_cast<const float4*>(a.H), 2);      // (00, 01, 02, 11)
-          const float4 hb = interp4(reinterpret_cast<const float4*>(a.H) + 1, 2);  // (12, 22, -, -)
-          const float h00 = ha.x, h01 = ha.y, h02 = ha.z, h11 = ha.w, h12 = hb.x, h22 = hb.y;
-          const float t = a.coef * a.res[gi];
-          v0 = fmaf(t, h00 * du0 + h01 * du1 + h02 * du2, v0);
-          v1 = fmaf(t, h01 * du0 + h11 * du1 + h12 * du2, v1);
-          v2 = fmaf(t, h02 * du0 + h12 * du1 + h22 * du2, v2);
-        }
-      }
-    }
-    vals[p] = v0;
-    vals[P + p] = v1;
-    vals[2 * P + p] = v2;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 3 * rv * Kh; i += blockDim.x) {
-    int j = i / (rv * Kh), r = (i / Kh) % rv, kh = i % Kh;
-    const float* row = vals + (size_t)j * P + r * N2;
-    float2 acc = make_float2(0.f, 0.f);
-    for (int x2 = 0; x2 < N2; ++x2) {
-      float2 w = wfx[(size_t)x2 * Kh + kh];
-      acc.x = fmaf(row[x2], w.x, acc.x);
-      acc.y = fmaf(row[x2], w.y, acc.y);
-    }
-    s1[(((size_t)j * N0 + x0) * N1 + x1b + r) * Kh + kh] = acc;
-  }
 }
 
 // ------------------------------------------------- fused t = 1 tail (tuned)
@@ -2509,40 +2162,6 @@ hipError_t launch_colstep(const ColJobs& jobs, int njobs, const Dims& d, const T
   return e;
 }
 
-hipError_t launch_fwd1(const Fwd1Jobs& jobs, int njobs, const float2* tw, int G0, int G1, int K1,
-                       int Kh, hipStream_t st) {
-  constexpr int QT = 2;
-  const int T = 128;
-  dim3 grid(nblk((long long)G0 * Kh, T), nblk(K1, QT), njobs);
-  size_t shm = QT * G1 * sizeof(float2);
-  timer_work(KF_FWD1_GRID, njobs * 8.0 * G0 * Kh * (double)K1 * G1,
-             njobs * 8.0 * ((double)G0 * G1 * Kh + (double)G0 * K1 * Kh));
-  LAUNCH_TIMED(KF_FWD1_GRID, (k_fwd1<QT>), grid, dim3(T), shm, st, jobs, tw, G0, G1, K1, Kh);
-  return hipGetLastError();
-}
-
-hipError_t launch_fwd0(const Fwd0Jobs& jobs, int njobs, const float2* tw, const float* Ksym, int G0,
-                       int K0, int K1, int Kh, float invG, hipStream_t st) {
-  constexpr int QT = 2;
-  const int T = 128;
-  dim3 grid(nblk((long long)K1 * Kh, T), nblk(K0, QT), njobs);
-  size_t shm = QT * G0 * sizeof(float2);
-  {
-    const double C = (double)K1 * Kh;
-    double fl = 0, by = 0;
-    for (int i = 0; i < njobs; ++i) {
-      const Fwd0Job& j = jobs.j[i];
-      int terms = 1 + (j.b != nullptr);
-      fl += terms * 8.0 * K0 * C * G0;
-      by += terms * 8.0 * G0 * C +
-            8.0 * K0 * C * (1 + (j.base != nullptr) + (j.extra != nullptr) + (j.out2 != nullptr)) + 4.0 * K0 * C;
-    }
-    timer_work(KF_FWD0_GRID, fl, by);
-  }
-  LAUNCH_TIMED(KF_FWD0_GRID, (k_fwd0<QT>), grid, dim3(T), shm, st, jobs, tw, Ksym, G0, K0, K1, Kh, invG);
-  return hipGetLastError();
-}
-
 // Limits on the problem sizes (validated at the boundary): the LDS tiles of a
 // grid step with all its tables, and of the image-term sources.
 size_t gridstep_shared_bytes(const Dims& d) {
@@ -2600,23 +2219,6 @@ hipError_t launch_sl_rk2(const float* src, const float* vel, float* dst, float d
   });
 }
 
-hipError_t launch_src_fwd2(const float* a, const float* b, const float* r, const float* m, float coef,
-                           float2* s1, const Dims& d, const Twiddles& tw, hipStream_t st) {
-  dim3 grid(nblk(d.N[1], kGridRows), d.N[0]);
-  size_t shm = src_shared_bytes(d);
-  {
-    // gradient of m (6 flops / point / axis), the source, forward stage 2 of 3 fields
-    const double nN = (double)d.nN;
-    timer_work(KF_SRC, 3.0 * nN * d.Kh * 4.0 + (r ? 43.0 : 25.0) * nN,
-               (b ? 12.0 : 8.0) * nN + (r ? 4.0 : 0.0) * nN + 3.0 * d.N[0] * (double)d.N[1] * d.Kh * 8.0);
-  }
-  hipError_t e = with_grid(d, [&](auto gs) {
-    LAUNCH_TIMED(KF_SRC, (k_src_fwd2<decltype(gs)>), grid, dim3(256), shm, st, a, b, r, m, coef, s1, tw, gs);
-    return hipGetLastError();
-  });
-  return e;
-}
-
 hipError_t launch_sl_tangent(const float* dm, const float* m, const float* vel, const float* dvel, float* out,
                              float dt, const Dims& d, hipStream_t st) {
   timer_work(KF_SL, 90.0 * (double)d.nN, ((dm ? 8.0 : 4.0) + 12.0 + 12.0 + 4.0) * (double)d.nN);
@@ -2627,49 +2229,11 @@ hipError_t launch_sl_tangent(const float* dm, const float* m, const float* vel, 
   });
 }
 
-hipError_t launch_adj_src_fwd2(const float* lam, const float* m, const float* vel, float* lam_out, float coef,
-                               float dt, float2* s1, const Dims& d, const Twiddles& tw, hipStream_t st) {
-  dim3 grid(nblk(d.N[1], kGridRows), d.N[0]);
-  size_t shm = src_shared_bytes(d);
-  {
-    // departure point, 8 gathers, slopes, 8 scattered weights, forward stage 2 of 3 fields
-    const double nN = (double)d.nN;
-    timer_work(KF_SRC, 3.0 * nN * d.Kh * 4.0 + 80.0 * nN,
-               (4.0 + 12.0 + 4.0 + 8.0 * 4.0) * nN + 3.0 * d.N[0] * (double)d.N[1] * d.Kh * 8.0);
-  }
-  hipError_t e = with_grid(d, [&](auto gs) {
-    LAUNCH_TIMED(KF_SRC, (k_adj_src_fwd2<decltype(gs)>), grid, dim3(256), shm, st, lam, m, vel, lam_out, coef, dt,
-                 s1, tw, gs);
-    return hipGetLastError();
-  });
-  return e;
-}
-
 hipError_t launch_image_derivs(const float* I0, float* G, float* H, const Dims& d, hipStream_t st) {
   return with_grid(d, [&](auto gs) {
     hipLaunchKernelGGL((k_image_derivs<decltype(gs)>), dim3(nblk(d.nN, 256)), dim3(256), 0, st, I0, G, H, gs);
     return hipGetLastError();
   });
-}
-
-hipError_t launch_rho_fwd2(const RhoArgs& a, float2* s1, const Dims& d, const Twiddles& tw, hipStream_t st) {
-  dim3 grid(nblk(d.N[1], kGridRows), d.N[0]);
-  size_t shm = src_shared_bytes(d);
-  {
-    // trilinear interpolation of 4 (op 0), 3 or 9 (op 1) fields, the source,
-    // forward stage 2 of 3 fields; point reads u (3) and I1 | du (3), res
-    const double nN = (double)d.nN;
-    const bool full = a.op == 1 && a.res;
-    const double nf = a.op == 0 ? 4.0 : (full ? 9.0 : 3.0);
-    const double rd = a.op == 0 ? 4.0 : (full ? 7.0 : 6.0);
-    timer_work(KF_SRC, 3.0 * nN * d.Kh * 4.0 + (nf * 14.0 + (full ? 30.0 : 12.0)) * nN,
-               (nf + rd) * 4.0 * nN + 3.0 * d.N[0] * (double)d.N[1] * d.Kh * 8.0);
-  }
-  hipError_t e = with_grid(d, [&](auto gs) {
-    LAUNCH_TIMED(KF_SRC, (k_rho_fwd2<decltype(gs)>), grid, dim3(256), shm, st, a, s1, tw, gs);
-    return hipGetLastError();
-  });
-  return e;
 }
 
 bool tail_fused(const Dims& d) {

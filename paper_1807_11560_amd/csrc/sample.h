@@ -16,10 +16,11 @@ __device__ __forceinline__ int wrap(int a, int N) {
 
 // The cell of voxel coordinates X (floor, periodic): the offsets of its four
 // rows, (a0, a1), (a0, b1), (b0, a1), (b0, b1) with b = a + 1, its first column
-// a2 and the fractional parts.  (Products of 24 bits: N0, N1 <= 2048, N2 <= 256.)
+// a2, the floors as they are, and the fractional parts.  (Products of 24 bits: N0, N1 <= 2048, N2 <= 256.)
 struct Cell {
   unsigned r[4];
   int a2;
+  int f0, f1, f2;
   float w0, w1, w2;
 };
 template <class G>
@@ -40,6 +41,9 @@ __device__ __forceinline__ Cell cell_at(float X0, float X1, float X2, int i0, in
   c.r[2] = __umul24(p1 + a1, N2);
   c.r[3] = __umul24(p1 + b1, N2);
   c.a2 = wrap((int)f2, N2);
+  c.f0 = (int)f0;
+  c.f1 = (int)f1;
+  c.f2 = (int)f2;
   c.w0 = X0 - f0;
   c.w1 = X1 - f1;
   c.w2 = X2 - f2;
