@@ -10,7 +10,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "liblddmm.so")
-SOURCES = ["kernels.hip", "chain.hip", "source.hip", "engine.hip", "abi.hip"]
+SOURCES = ["kernels.hip", "chain.hip", "source.hip", "step.hip", "engine.hip", "abi.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "-O3", "-std=c++20", "-fPIC", "-shared", "--offload-arch=gfx950",

@@ -95,21 +95,6 @@ __global__ void k_tables(TableJobs jobs) {
         static_cast<float*>(j.dst)[i] = (lk & 1) ? w.y : w.x;
         break;
       }
-      case TAB_SYNTH1: {  // [2][rows][2K]: re | -im
-        const int rows = (G + 15) & ~15, k = i % (2 * K), x = (i / (2 * K)) % rows;
-        float2 w = make_float2(0.f, 0.f);
-        if (x < G) w = inverse_entry(k % K, K, x, G, i / (rows * 2 * K), false);
-        static_cast<float*>(j.dst)[i] = k < K ? w.x : -w.y;
-        break;
-      }
-      case TAB_SYNTH2: {  // [2][2 Khp][columns]: re ; -im
-        const int Kh = K / 2, Khp = (Kh + 7) & ~7, cols = (G + 15) & ~15;
-        const int x = i % cols, q = (i / cols) % (2 * Khp), kh = q % Khp;
-        float2 w = make_float2(0.f, 0.f);
-        if (x < G && kh < Kh) w = inverse_entry(kh, K, x, G, i / (2 * Khp * cols), true);
-        static_cast<float*>(j.dst)[i] = q < Khp ? w.x : -w.y;
-        break;
-      }
       case TAB_COL1: {  // [x][Kp]
         const int Kp = (K + 15) & ~15, k = i % Kp;
         static_cast<float2*>(j.dst)[i] = k < K ? forward_entry(k, K, i / Kp, G, false) : make_float2(0.f, 0.f);

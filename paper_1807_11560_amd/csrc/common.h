@@ -46,7 +46,7 @@ enum TableKind {
   TAB_INV = 0, TAB_INV_HALF = 1, TAB_FWD = 2, TAB_FWD_HALF = 3,  // plain
   TAB_ROW_INV = 4, TAB_ROW_INV_HALF = 5,                         // fragment order, see mfma.h
   TAB_PAIR_INV = 6, TAB_PAIR_INV_HALF = 7, TAB_PAIR_FWD = 8,
-  TAB_SYNTH1 = 9, TAB_SYNTH2 = 10, TAB_COL1 = 11, TAB_COL0 = 12, TAB_COL0_INV = 13,  // instantiated shapes
+  TAB_COL1 = 11, TAB_COL0 = 12, TAB_COL0_INV = 13,  // instantiated shapes
   TAB_SYMBOLS = 14,                                              // L~ to dst, K~ to dst2 (K = K0, G = K1)
   TAB_ZERO = 15                                                  // unsigned zeros
 };
@@ -125,12 +125,20 @@ struct ProdArgs {
   int nout, prog;
 };
 
-// Synthesis of one or two groups (k_synth)
+// Synthesis and products of a step in one launch (k_step): stage-0 output
+// of the new groups, where they are kept (or null), the cached groups.
+constexpr int kStepM2 = 48;  // most columns of the padded grid
+struct StepArgs {
+  const float2* t1[2];
+  float* dst[2];
+  const float* cached[6];
+  float2* s1;
+};
+
+// Synthesis of one or two groups (k_synth_chain)
 struct SynthArgs {
   const float2* t1[2];  // stage-0 output of group g: [3][2][M0][K1*Kh]
   float* dst[2];        // fields of group g: [3][nM][4] (value, d0, d1, d2)
-  const float* w1a;     // [2][M1p][2K1]    real block form of the stage-1 twiddles
-  const float* w2b;     // [2][2Khp][M2p]   real block form of the stage-2 twiddles
 };
 
 // Band-side step of one output component (the column kernels): forward stages
@@ -206,18 +214,21 @@ hipError_t launch_half_to_full(const float2* a, const float2* b, float cb, float
 // Output [nvar][G0][Kh][K1]; image_grid selects the timer family of the launch.
 hipError_t launch_inv0(const Inv0Jobs& jobs, int njobs, int nvar, const float2* tw, const float* Lsym,
                        int K0, int C, int G0, int Kh, bool image_grid, hipStream_t st);
-// Table jobs of the instantiated shapes' synthesis and column step; return their number.
-int synth_table_jobs(TableJob* j, float* tables, const Dims& d);
+// Table jobs of the instantiated shapes' column step; returns their number.
 int col_table_jobs(TableJob* j, float2* tab, const Dims& d);
 size_t synth_table_floats(const Dims& d);
 size_t synth_shared_bytes(const Dims& d);
 // Synthesis of group 0 and, when t1g1 is set, group 1.
 hipError_t launch_synth(const float2* t1g0, const float2* t1g1, float* dst0, float* dst1,
-                        const float* tables, const Frags& fr, const Dims& d, hipStream_t st);
-// The shapes without instantiated kernels (chain.hip): nf new fields.
+                        const Frags& fr, const Dims& d, hipStream_t st);
+// nf new fields.
 hipError_t launch_synth_chain(const SynthArgs& a, int nf, const Frags& fr, const Dims& d, hipStream_t st);
 hipError_t launch_column_chain(const ColJobs& jobs, int njobs, const Dims& d, const Frags& frM, const Frags& frN,
                                const float* Lsym, const float* Ksym, float invG, hipStream_t st);
+// Whether a step's synthesis and products run in one launch, and that launch.
+bool step_fused(const Dims& d);
+hipError_t launch_step(int prog, const StepArgs& a, const Frags& fr, const Twiddles& tw, const Dims& d,
+                       hipStream_t st);
 size_t prods_shared_bytes(const Dims& d, int nout);
 hipError_t launch_prods(const ProdArgs& a, const Dims& d, const Twiddles& tw, hipStream_t st);
 hipError_t launch_colstep(const ColJobs& jobs, int njobs, const Dims& d, const Twiddles& tw,

@@ -114,6 +114,8 @@ class Engine {
   const float2* s2n(int o) const;
   hipError_t inv0_groups(const float2* in0, int l0, const float2* in1, int l1);
   hipError_t mstep(int prog, int nout, float* store0, float* store1, const float* const* cached);
+  hipError_t mstep1(int prog, int nout, const float2* g, float* kept, float* scratch, const float* const* cached,
+                    int ncached, float2* s1, hipStream_t s);
   ColJob col_job(int c, int oa, float ca, int syma, int ob, float cb, int symb, const float2* base,
                  const float2* extra, float ce, float2* out, int g0, int l0, int g1, int l1,
                  float2* t1n = nullptr) const;
@@ -166,7 +168,6 @@ class Engine {
   // reverse sweep of backward_exact from the state adjoint (over coef) in dm[cur]
   hipError_t adjoint_exact(int cur);
   float* dvg_ = nullptr;  // grid velocity increment of one step [3][nN] (exact product)
-  float* synth_tab_ = nullptr;  // MFMA-form stage-1/2 twiddles of the padded grid
   float2* col_tab_ = nullptr;   // MFMA-form twiddles of the column step
   float4* frag_ = nullptr;      // fragment tables of both grids
   Frags frM_{}, frN_{};

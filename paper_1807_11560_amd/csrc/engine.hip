@@ -39,6 +39,7 @@ size_t frag_count_m(const Dims& d) {
   return row_inv(d.K[1], d.M[1]) + row_inv(d.Kh, d.M[2]) + pair_inv(d.K[0], d.M[0]) + pair_fwd(d.K[0], d.M[0]) +
          pair_fwd(d.K[1], d.M[1]) + pair_inv(d.K[0], d.N[0]) / 2;
 }
+size_t frag_count_synth(const Dims& d) { return row_inv(d.K[1], d.M[1]) + row_inv(d.Kh, d.M[2]); }
 size_t frag_count_n(const Dims& d) {
   return grid_instantiated(d) ? (row_inv(d.K[1], d.N[1]) + row_inv(d.Kh, d.N[2])) / 2
                               : (pair_inv(d.K[1], d.N[1]) + pair_inv(d.Kh, d.N[2])) / 2;
@@ -153,11 +154,12 @@ void Engine::layout(Carver& c) {
     // the workspace of a problem (and with it what lddmm_shoot_static takes)
     // does not depend on which kernels serve it.
     auto tables = [&](Carver& r, bool inst) {
-      twbuf_ = r.take<float2>((inst ? 2 * (size_t)d.M[0] * d.K[0] : 0) + (size_t)d.Kh * d.M[2] +
-                              twiddle_count(d.N, d));
-      synth_tab_ = inst ? r.take<float>(synth_table_floats(d)) : nullptr;
+      twbuf_ = r.take<float2>((inst ? 2 * ((size_t)d.M[0] + d.N[0]) * d.K[0] : 0) +
+                              (grid_instantiated(d) ? 2 * ((size_t)d.N[1] * d.K[1] + (size_t)d.N[2] * d.Kh) : 0) +
+                              (size_t)d.K[0] * d.N[0] + (size_t)d.K[1] * d.N[1] +
+                              (size_t)d.Kh * ((size_t)d.M[2] + d.N[2]));
       col_tab_ = inst ? r.take<float2>(col_table_count(d)) : nullptr;
-      frag_ = r.take<float4>((inst ? 0 : frag_count_m(d)) + frag_count_n(d));
+      frag_ = r.take<float4>((inst ? frag_count_synth(d) : frag_count_m(d)) + frag_count_n(d));
     };
     Carver a{nullptr}, b{nullptr};
     a.take<float2>(twiddle_count(d.M, d) + twiddle_count(d.N, d));
@@ -212,10 +214,12 @@ Engine::Engine(const Dims& d, void* ws, hipStream_t st)
     Twiddles& tw = pass == 0 ? twM_ : twN_;
     const int* G = pass == 0 ? d.M : d.N;
     for (int j = 0; j < 3; ++j) tw.G[j] = G[j];
-    if (pass == 1 || inst) { tw.inv0 = t; t += 2 * (size_t)G[0] * d.K[0]; }
-    if (pass == 1) {
+    if (inst) { tw.inv0 = t; t += 2 * (size_t)G[0] * d.K[0]; }
+    if (pass == 1 && grid_instantiated(d)) {
       tw.inv1 = t; t += 2 * (size_t)G[1] * d.K[1];
       tw.inv2 = t; t += 2 * (size_t)G[2] * d.Kh;
+    }
+    if (pass == 1) {
       tw.fwd0 = t; t += (size_t)d.K[0] * G[0];
       tw.fwd1 = t; t += (size_t)d.K[1] * G[1];
     }
@@ -223,9 +227,9 @@ Engine::Engine(const Dims& d, void* ws, hipStream_t st)
   }
   const float4* f = frag_;
   auto view = [&](const float4*& p, size_t n) { p = f; f += n; };
+  view(frM_.row1, row_inv(d.K[1], d.M[1]));
+  view(frM_.row2, row_inv(d.Kh, d.M[2]));
   if (!inst) {
-    view(frM_.row1, row_inv(d.K[1], d.M[1]));
-    view(frM_.row2, row_inv(d.Kh, d.M[2]));
     view(frM_.inv0, pair_inv(d.K[0], d.M[0]));
     view(frM_.fwd0, pair_fwd(d.K[0], d.M[0]));
     view(frM_.fwd1, pair_fwd(d.K[1], d.M[1]));
@@ -259,7 +263,7 @@ hipError_t Engine::init_tables() {
   for (int pass = 0; pass < 2; ++pass) {
     const Twiddles& tw = pass == 0 ? twM_ : twN_;
     const int* G = tw.G;
-    if (pass == 1 || inst) add(tw.inv0, TAB_INV, K[0], G[0], 2 * (size_t)G[0] * K[0]);
+    if (inst) add(tw.inv0, TAB_INV, K[0], G[0], 2 * (size_t)G[0] * K[0]);
     if (pass == 1 && grid_instantiated(d_)) {
       add(tw.inv1, TAB_INV, K[1], G[1], 2 * (size_t)G[1] * K[1]);
       add(tw.inv2, TAB_INV_HALF, K[2], G[2], 2 * (size_t)G[2] * d_.Kh);
@@ -270,12 +274,11 @@ hipError_t Engine::init_tables() {
     }
     add(tw.fwd2, TAB_FWD_HALF, K[2], G[2], (size_t)d_.Kh * G[2]);
   }
+  add(frM_.row1, TAB_ROW_INV, K[1], d_.M[1], 4 * row_inv(K[1], d_.M[1]));
+  add(frM_.row2, TAB_ROW_INV_HALF, d_.Kh, d_.M[2], 4 * row_inv(d_.Kh, d_.M[2]));
   if (inst) {
-    n += synth_table_jobs(jobs.j + n, synth_tab_, d_);
     n += col_table_jobs(jobs.j + n, col_tab_, d_);
   } else {
-    add(frM_.row1, TAB_ROW_INV, K[1], d_.M[1], 4 * row_inv(K[1], d_.M[1]));
-    add(frM_.row2, TAB_ROW_INV_HALF, d_.Kh, d_.M[2], 4 * row_inv(d_.Kh, d_.M[2]));
     add(frM_.inv0, TAB_PAIR_INV, K[0], d_.M[0], 4 * pair_inv(K[0], d_.M[0]));
     add(frM_.fwd0, TAB_PAIR_FWD, K[0], d_.M[0], 4 * pair_fwd(K[0], d_.M[0]));
     add(frM_.fwd1, TAB_PAIR_FWD, K[1], d_.M[1], 4 * pair_fwd(K[1], d_.M[1]));
@@ -348,7 +351,18 @@ hipError_t Engine::mstep(int prog, int nout, float* store0, float* store1, const
   const size_t nM = (size_t)d_.nM;
   float* g0 = store0 ? store0 : NG_;
   float* g1 = store1 ? store1 : NG_ + 12 * nM;
-  TRY(launch_synth(t1(0, 0), t1(1, 0), g0, g1, synth_tab_, frM_, d_, st_));
+  if (nout > 0 && step_fused(d_)) {
+    StepArgs a{};
+    a.t1[0] = t1(0, 0);
+    a.t1[1] = t1(1, 0);
+    a.dst[0] = store0;
+    a.dst[1] = store1;
+    if (cached)
+      for (int k = 0; k < 6; ++k) a.cached[k] = cached[k];
+    a.s1 = S1_;
+    return launch_step(prog, a, frM_, twM_, d_, st_);
+  }
+  TRY(launch_synth(t1(0, 0), t1(1, 0), g0, g1, frM_, d_, st_));
   if (nout == 0) return hipSuccess;
   ProdArgs a{};
   a.g[0] = g0;
@@ -359,6 +373,28 @@ hipError_t Engine::mstep(int prog, int nout, float* store0, float* store1, const
   a.nout = nout;
   a.prog = prog;
   return launch_prods(a, d_, twM_, st_);
+}
+
+// The same with one new group (stage-0 buffer g), kept where `kept` is set, in
+// `scratch` where the products run apart.
+hipError_t Engine::mstep1(int prog, int nout, const float2* g, float* kept, float* scratch, const float* const* cached,
+                          int ncached, float2* s1, hipStream_t s) {
+  if (step_fused(d_)) {
+    StepArgs a{};
+    a.t1[0] = g;
+    a.dst[0] = kept;
+    for (int k = 0; k < ncached; ++k) a.cached[k] = cached[k];
+    a.s1 = s1;
+    return launch_step(prog, a, frM_, twM_, d_, s);
+  }
+  TRY(launch_synth(g, nullptr, scratch, nullptr, frM_, d_, s));
+  ProdArgs a{};
+  a.g[0] = scratch;
+  for (int k = 0; k < ncached; ++k) a.g[1 + k] = cached[k];
+  a.s1 = s1;
+  a.nout = nout;
+  a.prog = prog;
+  return launch_prods(a, d_, twM_, s);
 }
 
 // One column job: out_c = base + ca S F(s1[oa]) (+ cb S F(s1[ob])) + ce extra;
@@ -888,15 +924,8 @@ hipError_t Engine::adjoint_exact(int cur) {
   TRY(launch_fill(reinterpret_cast<float*>(W[nt]), 6LL * d_.nb, 0.f, st_));
   TRY(inv0_group(W[nt], 0, 0, st_));
   for (int n = nt - 1; n >= 0; --n) {
-    TRY(launch_synth(t1(0, 0), nullptr, NG_, nullptr, synth_tab_, frM_, d_, st_));
-    ProdArgs a{};
-    a.g[0] = NG_;
-    a.g[1] = VG[n];
-    a.g[2] = VG[n] + 12 * nM;
-    a.s1 = S1_;
-    a.nout = 6;
-    a.prog = PROG_ADJ;
-    TRY(launch_prods(a, d_, twM_, st_));
+    const float* cached[2] = {VG[n], VG[n] + 12 * nM};
+    TRY(mstep1(PROG_ADJ, 6, t1(0, 0), nullptr, NG_, cached, 2, S1_, st_));
     const bool next = n > 0;
     ColJob jobs[3];
     for (int k = 0; k < 3; ++k)
@@ -999,9 +1028,8 @@ hipError_t Engine::forward_def(const float* I0) {
       TRY(launch_axpy_band(Phi[0], V[0], -dt, Phi[1], 3 * d_.nb, aux_));
       return inv0_group(Phi[1], 2, 0, aux_);
     }
-    TRY(launch_synth(t1(2, 0), nullptr, PG[k], nullptr, synth_tab_, frM_, d_, aux_));
-    const float* g[2] = {PG[k], VG[k]};
-    TRY(prods_on(PROG_DEF_FWD, g, 2, S1A_, aux_));
+    const float* cached[1] = {VG[k]};
+    TRY(mstep1(PROG_DEF_FWD, 3, t1(2, 0), PG[k], PG[k], cached, 1, S1A_, aux_));
     const bool last = k + 1 == nt;
     ColJob jobs[3];
     for (int c = 0; c < 3; ++c) {
@@ -1031,7 +1059,7 @@ hipError_t Engine::tail_def(const float* I1) {
   TRY(launch_rho_fwd2(ra, S1N_, d_, twN_, st_));
   TRY(band_pair(R, KR, st_));
   TRY(inv0_group(R, 3, 0, st_));
-  TRY(launch_synth(t1(2, 0), t1(3, 0), PG[nt], RG, synth_tab_, frM_, d_, st_));
+  TRY(launch_synth(t1(2, 0), t1(3, 0), PG[nt], RG, frM_, d_, st_));
   const float* g[2] = {PG[nt], RG};
   return def_head(PROG_DEF_TAIL, g, 2, KR, U[nt]);
 }
@@ -1056,9 +1084,8 @@ hipError_t Engine::hessvec_def(const float2* dvh, float2* out) {
       TRY(launch_axpy_band(Phi[0], dV[0], -dt, dPhi[0], 3 * d_.nb, aux_));
       return inv0_group(dPhi[0], 2, 0, aux_);
     }
-    TRY(launch_synth(t1(2, 0), nullptr, NGA_, nullptr, synth_tab_, frM_, d_, aux_));
-    const float* g[4] = {NGA_, VG[k], PG[k], dVG[k]};
-    TRY(prods_on(PROG_DEF_H, g, 4, S1A_, aux_));
+    const float* cached[3] = {VG[k], PG[k], dVG[k]};
+    TRY(mstep1(PROG_DEF_H, 3, t1(2, 0), nullptr, NGA_, cached, 3, S1A_, aux_));
     const bool last = k + 1 == nt;
     ColJob jobs[3];
     for (int c = 0; c < 3; ++c) {
@@ -1104,11 +1131,11 @@ hipError_t Engine::hessvec_def(const float2* dvh, float2* out) {
   // dU_nt = K~ drho~ + K~ ((D~u_nt)^T * drho~ [+ (D~du_nt)^T * rho~, full Newton])
   TRY(launch_fill(reinterpret_cast<float*>(dW[0]), 6LL * d_.nb, 0.f, st_));
   if (d_.hessian != 2) {
-    TRY(launch_synth(t1(3, 0), nullptr, NGA_, nullptr, synth_tab_, frM_, d_, st_));
+    TRY(launch_synth(t1(3, 0), nullptr, NGA_, nullptr, frM_, d_, st_));
     const float* g[2] = {PG[nt], NGA_};
     TRY(def_head(PROG_DEF_TAIL, g, 2, KdR, dU[0]));
   } else {
-    TRY(launch_synth(t1(2, 0), t1(3, 0), NGA_, NGA_ + 12 * nM, synth_tab_, frM_, d_, st_));
+    TRY(launch_synth(t1(2, 0), t1(3, 0), NGA_, NGA_ + 12 * nM, frM_, d_, st_));
     const float* g[4] = {NGA_, NGA_ + 12 * nM, PG[nt], RG};
     TRY(def_head(PROG_DEF_HTAIL, g, 4, KdR, dU[0]));
   }

@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "launch.h"
+#include "lie.h"
 #include "sample.h"
 #include "shapes.h"
 
@@ -200,260 +201,14 @@ __global__ void __launch_bounds__(128) k_inv0(Inv0Jobs jobs, const float2* __res
     }
 }
 
-// --------------------------------------------- band Lie algebra products
-// Group layout: 12 scalar fields of one vector field f: f_c at index c,
-// d_i f_c at index 3 + 3c + i.
-// (ad*_a mu)_i = sum_j (d_i a_j) mu_j + (d_j mu_i) a_j + mu_i (d_j a_j)
-__device__ __forceinline__ void adstar_acc(float* o, const float* a, const float* mu, float s) {
-  const float diva = a[3] + a[7] + a[11];
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    float r = mu[i] * diva;
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      r = fmaf(a[3 + 3 * j + i], mu[j], r);
-      r = fmaf(mu[3 + 3 * i + j], a[j], r);
-    }
-    o[i] = fmaf(s, r, o[i]);
-  }
-}
-
-// (ad_a b)_i = sum_j (d_j a_i) b_j - (d_j b_i) a_j
-__device__ __forceinline__ void ad_acc(float* o, const float* a, const float* b, float s) {
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    float r = 0.f;
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      r = fmaf(a[3 + 3 * i + j], b[j], r);
-      r = fmaf(-b[3 + 3 * i + j], a[j], r);
-    }
-    o[i] = fmaf(s, r, o[i]);
-  }
-}
-
-// (D~a * b)_i += sum_j (d_j a_i) b_j; ja[3 i + j] = d_j a_i
-__device__ __forceinline__ void jac_acc(float* o, const float* ja, const float* b) {
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) o[i] = fmaf(ja[3 * i + j], b[j], o[i]);
-}
-
-// ((D~a)^T * r)_j += sum_i (d_j a_i) r_i
-__device__ __forceinline__ void jact_acc(float* o, const float* ja, const float* r) {
-#pragma unroll
-  for (int j = 0; j < 3; ++j)
-#pragma unroll
-    for (int i = 0; i < 3; ++i) o[j] = fmaf(ja[3 * i + j], r[i], o[j]);
-}
-
-// ------------------------------------------- MFMA synthesis on the padded grid
-// One block per (x0 plane, new field (g, c)), four waves.  The inverse
-// stages 1 (k1 -> x1, complex) and 2 (half spectrum k2 -> real x2) are two
-// real GEMMs on the matrix cores (v_mfma_f32_16x16x4f32, FP32 in, FP32
-// accumulate):
-//   T2 = [W1r | -W1i] [[T1r, T1i], [T1i, -T1r]]        rows x1, cols (kh re | kh im)
-//   f  = [T2r | T2i] [[w2r], [-w2i]]                   rows x1, cols x2
-// for the variants value, d/dx2 (pp with the derivative stage-2 table), d/dx1
-// (stage-1 derivative table) and d/dx0 (stage-0 derivative input).  The
-// four results go to the group's field array [3][nM][4]: per component and
-// padded-grid point (value, d/dx0, d/dx1, d/dx2).
-constexpr int kSynthW2Pre = 16;
-constexpr int kSynthT = 3;  // tiles a wave computes together
-template <class S, bool BF3>
-__global__ void __launch_bounds__(256) k_synth(SynthArgs a, S sh) {
-  extern __shared__ float sms[];
-  const int M0 = sh.M0(), M1 = sh.M1(), M2 = sh.M2(), K1 = sh.K1(), Kh = sh.Kh();
-  const int M1p = (M1 + 15) & ~15, M2p = (M2 + 15) & ~15, Khp = (Kh + 7) & ~7;
-  const int x0 = blockIdx.x;
-  const int g = blockIdx.y / 3, c = blockIdx.y % 3;
-  const int rt = blockIdx.z;  // 16-row tile of x1
-  const int C = K1 * Kh;
-  const int K2r = 2 * K1;    // GEMM1 depth
-  const int N1 = 2 * Khp;    // GEMM1 width = GEMM2 depth
-  // LDS strides: the 16 rows an MFMA operand reads lie in distinct banks
-  // (row strides of 2 mod 4 floats for operands read along rows, 16 mod 32
-  // for the stage-2 table read across rows)
-  const int lda1 = K2r + 2, ldt2 = N1 + 2, ldbT = K2r + 2;
-  const int ldw2 = (M2p % 32 == 0) ? M2p + 16 : M2p;
-  const int nbt = 2 * N1 * (ldbT > ldw2 ? ldbT : ldw2);
-  float* w1s = sms;                          // [2][16][lda1]   stage-1 rows of this tile
-  float* bt1 = w1s + 2 * 16 * lda1;          // [2][N1][ldbT]   stage-0 input, transposed; then [2][N1][ldw2]
-  float* t2s = bt1 + nbt;                    // [3][16][ldt2]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  (void)M1p;
-  // The stage-2 table w2b [2][N1][M2p] is loaded into registers during GEMM1
-  // (issued after the first barrier, which then waits for GEMM1's operands
-  // alone) and put into the LDS of bt1 once GEMM1 has consumed it (when it
-  // fits; else GEMM2 reads it from global memory).
-  const int nw2 = 2 * N1 * M2p;
-  const bool w2_lds = nw2 <= 256 * kSynthW2Pre;
-  RegStage<kSynthW2Pre / 4, float4> rw2;
-  const float2* src = a.t1[g] + (size_t)c * 2 * M0 * C;
-  auto put_t1 = [&](int vs, int k1, int kh, float2 t) {  // B[k][col] kept as bT[col][k]
-    float* b = bt1 + (size_t)vs * N1 * ldbT;
-    b[(size_t)kh * ldbT + k1] = t.x;
-    b[(size_t)(Khp + kh) * ldbT + k1] = t.y;
-    b[(size_t)kh * ldbT + K1 + k1] = t.y;
-    b[(size_t)(Khp + kh) * ldbT + K1 + k1] = -t.x;
-  };
-  // stage-1 table rows of this tile: w1a [2][M1p][K2r]
-  const float* w1rows = a.w1a + (size_t)rt * 16 * K2r;
-  {
-    // the loads of GEMM1's operands in flight at once, four floats per load
-    constexpr int sM1p = (S::M1() + 15) & ~15, sK1 = S::K1(), sKh = S::Kh(), sKhp = (sKh + 7) & ~7;
-    constexpr int sK2r = 2 * sK1, KP = sK1 / 2, R4 = sK2r / 4;
-    constexpr int NW1 = 2 * 16 * R4, NT1 = 2 * sKhp * KP;
-    static_assert(sK1 % 2 == 0, "pairs of k1 per load");
-    RegStage<(NW1 + 255) / 256, float4> rw1;
-    RegStage<(NT1 + 255) / 256, float4> rt1;
-    rw1.load(NW1, [&](int i) {
-      const int vv = i / (16 * R4), row = (i / R4) % 16, k = 4 * (i % R4);
-      return *reinterpret_cast<const float4*>(w1rows + vv * (size_t)sM1p * sK2r + (size_t)row * sK2r + k);
-    });
-    // the padding columns kh >= Kh load a valid row and are zeroed when stored
-    // (a load under a per-lane condition would wait for every load in flight)
-    rt1.load(NT1, [&](int i) {
-      const int vs = i / (sKhp * KP), kh = (i / KP) % sKhp, k1 = 2 * (i % KP);
-      return ld4(src + ((size_t)vs * M0 + x0) * C + (size_t)(kh < sKh ? kh : sKh - 1) * sK1 + k1);
-    });
-    rw1.store(NW1, [&](int i, float4 v) {
-      const int vv = i / (16 * R4), row = (i / R4) % 16, k = 4 * (i % R4);
-      float* d = w1s + ((size_t)vv * 16 + row) * lda1 + k;
-      d[0] = v.x;
-      d[1] = v.y;
-      d[2] = v.z;
-      d[3] = v.w;
-    });
-    rt1.store(NT1, [&](int i, float4 v) {
-      const int vs = i / (sKhp * KP), kh = (i / KP) % sKhp, k1 = 2 * (i % KP);
-      if (kh >= sKh) v = make_float4(0.f, 0.f, 0.f, 0.f);
-      put_t1(vs, k1, kh, make_float2(v.x, v.y));
-      put_t1(vs, k1 + 1, kh, make_float2(v.z, v.w));
-    });
-  }
-  __syncthreads();
-  if (w2_lds) rw2.load(nw2 / 4, [&](int i) { return reinterpret_cast<const float4*>(a.w2b)[i]; });
-  // GEMM1 on this tile's 16 rows: var 0 = pp (plain stage 0, plain stage 1),
-  // 1 = p1 (d1), 2 = 0p (d0 input).  Wave w takes tiles w, w + 4, w + 8, ...
-  // and runs up to kSynthT of them at once, their matrix instructions
-  // interleaved, operands fetched four k-steps ahead.
-  const int tj1 = N1 / 16, nj1 = 3 * tj1;
-  auto gemm1 = [&](auto TT, int j0) {
-    constexpr int T = decltype(TT)::value;
-    const float* A[T];
-    const float* B[T];
-    floatx4 acc[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int job = j0 + 4 * t;
-      const int var = job / tj1, tj = job % tj1;
-      const int vs = (var == 2), vt = (var == 1);
-      A[t] = w1s + ((size_t)vt * 16 + li) * lda1 + lk;
-      B[t] = bt1 + ((size_t)vs * N1 + tj * 16 + li) * ldbT + lk;
-      acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
-    for (int k0 = 0; k0 < K2r / 4; k0 += 4) {
-      float av[T][4], bv[T][4];
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int ks = k0 + u;
-          av[t][u] = (ks < K2r / 4) ? A[t][4 * ks] : 0.f;
-          bv[t][u] = (ks < K2r / 4) ? B[t][4 * ks] : 0.f;
-        }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-          acc[t] = mma<BF3>(av[t][u], bv[t][u], acc[t]);
-    }
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int job = j0 + 4 * t;
-      const int var = job / tj1, tj = job % tj1;
-      float* Tp = t2s + ((size_t)var * 16 + 4 * lk) * ldt2 + tj * 16 + li;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) Tp[(size_t)r * ldt2] = acc[t][r];
-    }
-  };
-  static_assert(kSynthT == 3, "tile groups of one to three");
-  for (int j0 = wave; j0 < nj1; j0 += 4 * kSynthT) {
-    const int cnt = min(kSynthT, (nj1 - j0 + 3) / 4);
-    if (cnt == 3)
-      gemm1(std::integral_constant<int, 3>{}, j0);
-    else if (cnt == 2)
-      gemm1(std::integral_constant<int, 2>{}, j0);
-    else
-      gemm1(std::integral_constant<int, 1>{}, j0);
-  }
-  __syncthreads();
-  const float* w2src = a.w2b;
-  int w2ld = M2p;
-  if (w2_lds) {
-    rw2.store(nw2 / 4, [&](int i, float4 v) {
-      *reinterpret_cast<float4*>(bt1 + (size_t)((4 * i) / M2p) * ldw2 + (4 * i) % M2p) = v;
-    });
-    __syncthreads();
-    w2src = bt1;
-    w2ld = ldw2;
-  }
-  // GEMM2: ov 0 = value (pp, plain), 1 = d2 (pp, derivative table), 2 = d1 (p1), 3 = d0 (0p).
-  // A wave forms all four for one 16-column tile, so that each point's
-  // (value, d0, d1, d2) leaves as one 16-byte store.
-  const int tj2 = M2p / 16;
-  const long long nM = (long long)M0 * M1 * M2;
-  float* out = a.dst[g] + (size_t)c * nM * 4;
-  for (int tj = wave; tj < tj2; tj += 4) {
-    const float* A[4];
-    const float* B[4];
-    floatx4 acc[4];
-#pragma unroll
-    for (int ov = 0; ov < 4; ++ov) {
-      const int srcv = (ov <= 1) ? 0 : (ov == 2 ? 1 : 2);
-      const int wv = (ov == 1);
-      A[ov] = t2s + ((size_t)srcv * 16 + li) * ldt2 + lk;
-      B[ov] = w2src + ((size_t)wv * N1 + lk) * w2ld + tj * 16 + li;
-      acc[ov] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
-    for (int k0 = 0; k0 < N1 / 4; k0 += 4) {
-      float av[4][4], bv[4][4];
-#pragma unroll
-      for (int ov = 0; ov < 4; ++ov)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int ks = k0 + u;
-          bv[ov][u] = (ks < N1 / 4) ? B[ov][(size_t)4 * ks * w2ld] : 0.f;
-          av[ov][u] = (ks < N1 / 4) ? A[ov][4 * ks] : 0.f;
-        }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int ov = 0; ov < 4; ++ov)
-          acc[ov] = mma<BF3>(av[ov][u], bv[ov][u], acc[ov]);
-    }
-    const int x2 = tj * 16 + li;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int x1 = rt * 16 + 4 * lk + r;
-      if (x1 < M1 && x2 < M2)
-        *reinterpret_cast<float4*>(out + 4 * (((long long)x0 * M1 + x1) * M2 + x2)) =
-            make_float4(acc[0][r], acc[3][r], acc[2][r], acc[1][r]);
-    }
-  }
-}
-
 // ------------------------------------------------ Lie products on the padded grid
 // One block per (x0, R rows), one thread per point (R*M2 threads).  Reads
 // the new and cached groups, forms the products of the program and
 // contracts them over x2 (forward stage 2) into s1[o][kh][x0][x1]: on the
 // matrix cores when M2 % 4 == 0 (rows (o, r) x columns (kh re | kh im), depth
 // x2), else one thread per output.
-template <class S, bool BF3>
-__global__ void __launch_bounds__(256) k_prods(ProdArgs a, Twiddles tw, S sh, int R) {
+template <bool BF3>
+__global__ void __launch_bounds__(256) k_prods(ProdArgs a, Twiddles tw, BandDyn sh, int R) {
   // R: padded-grid rows of this block (R M2 <= blockDim.x rounded to waves)
   extern __shared__ float smp[];
   const int M0 = sh.M0(), M1 = sh.M1(), M2 = sh.M2(), Kh = sh.Kh();
@@ -1879,6 +1634,7 @@ hipError_t launch_half_to_full(const float2* a, const float2* b, float cb, float
 
 hipError_t launch_inv0(const Inv0Jobs& jobs, int njobs, int nvar, const float2* tw, const float* Lsym,
                        int K0, int C, int G0, int Kh, bool image_grid, hipStream_t st) {
+  if (!tw) return hipErrorInvalidValue;
   const int fam = image_grid ? KF_INV0_GRID : KF_INV0;
   const int T = 128;
   {
@@ -1934,46 +1690,18 @@ size_t synth_shared_bytes(const Dims& d) {
          sizeof(float);
 }
 
-// MFMA-friendly real forms of the stage-1 and stage-2 inverse twiddles:
-// w1a [2][M1p][2 K1] = (re | -im), w2b [2][2 Khp][M2p] = (re ; -im), padding zero.
-int synth_table_jobs(TableJob* j, float* tables, const Dims& d) {
-  int M1p, M2p, Khp;
-  synth_padding(d, &M1p, &M2p, &Khp);
-  float* w2b = tables + 2 * (size_t)M1p * 2 * d.K[1];
-  j[0] = TableJob{tables, nullptr, TAB_SYNTH1, d.K[1], d.M[1], 2 * M1p * 2 * d.K[1], 0, 0.0};
-  j[1] = TableJob{w2b, nullptr, TAB_SYNTH2, d.K[2], d.M[2], 2 * 2 * Khp * M2p, 0, 0.0};
-  return 2;
-}
-
-hipError_t launch_synth(const float2* t1g0, const float2* t1g1, float* dst0, float* dst1,
-                        const float* tables, const Frags& fr, const Dims& d, hipStream_t st) {
-  int M1p, M2p, Khp;
-  synth_padding(d, &M1p, &M2p, &Khp);
+hipError_t launch_synth(const float2* t1g0, const float2* t1g1, float* dst0, float* dst1, const Frags& fr,
+                        const Dims& d, hipStream_t st) {
   SynthArgs a{};
   a.t1[0] = t1g0;
   a.t1[1] = t1g1;
   a.dst[0] = dst0;
   a.dst[1] = dst1;
-  a.w1a = tables;
-  a.w2b = tables + 2 * (size_t)M1p * 2 * d.K[1];
   const double nM = (double)d.nM;
   const int nf = t1g1 ? 6 : 3;  // new fields (group, component)
   timer_work(KF_SYNTH, nf * (3.0 * d.M[0] * d.M[1] * d.Kh * d.K[1] * 8.0 + 4.0 * nM * d.Kh * 4.0),
              nf * (2.0 * d.M[0] * d.K[1] * d.Kh * 8.0 + 4.0 * nM * 4.0));
-  (void)Khp;
-  (void)M2p;
-  return with_band(d, [&](auto sh) {
-    if constexpr (decltype(sh)::kStatic) {
-      const dim3 grid(d.M[0], nf, M1p / 16);
-      if (d.prec)
-        LAUNCH_TIMED(KF_SYNTH, (k_synth<decltype(sh), true>), grid, dim3(256), synth_shared_bytes(d), st, a, sh);
-      else
-        LAUNCH_TIMED(KF_SYNTH, (k_synth<decltype(sh), false>), grid, dim3(256), synth_shared_bytes(d), st, a, sh);
-      return hipGetLastError();
-    } else {
-      return launch_synth_chain(a, nf, fr, d, st);
-    }
-  });
+  return launch_synth_chain(a, nf, fr, d, st);
 }
 
 int prod_rows_max(const Dims& d) {
@@ -2006,16 +1734,12 @@ hipError_t launch_prods(const ProdArgs& a, const Dims& d, const Twiddles& tw, hi
   }
   int threads = ((R * d.M[2] + 63) / 64) * 64;
   if (threads > 256) threads = 256;
-  hipError_t e = with_band(d, [&](auto sh) {
-    do {
-      if (d.prec)
-        LAUNCH_TIMED(KF_PRODS, (k_prods<decltype(sh), true>), grid, dim3(threads), shm, st, a, tw, sh, R);
-      else
-        LAUNCH_TIMED(KF_PRODS, (k_prods<decltype(sh), false>), grid, dim3(threads), shm, st, a, tw, sh, R);
-    } while (0);
-    return hipGetLastError();
-  });
-  return e;
+  const BandDyn sh{d.K[0], d.K[1], d.Kh, d.M[0], d.M[1], d.M[2]};
+  if (d.prec)
+    LAUNCH_TIMED(KF_PRODS, k_prods<true>, grid, dim3(threads), shm, st, a, tw, sh, R);
+  else
+    LAUNCH_TIMED(KF_PRODS, k_prods<false>, grid, dim3(threads), shm, st, a, tw, sh, R);
+  return hipGetLastError();
 }
 
 // Limit on the problem sizes (validated at the boundary): the LDS tile of a
@@ -2058,7 +1782,9 @@ hipError_t launch_colstep(const ColJobs& jobs, int njobs, const Dims& d, const T
                           const float2* coltab, const Frags& frM, const Frags& frN, const float* Lsym,
                           const float* Ksym, hipStream_t st) {
   for (int i = 0; i < njobs; ++i) {
-    if (jobs.j[i].t1n && (!colstep_fuses_grid0(d) || jobs.N0 != d.N[0] || !jobs.w0n)) return hipErrorInvalidValue;
+    if (jobs.j[i].t1n && (!colstep_fuses_grid0(d) || jobs.N0 != d.N[0] ||
+                           (band_instantiated(d) ? !jobs.w0n : !frN.inv0)))
+      return hipErrorInvalidValue;
     // the tuned kernel takes products only, and loads pairs of complex values
     if (band_instantiated(d) && !jobs.j[i].a) return hipErrorInvalidValue;
     if (band_instantiated(d) && (((uintptr_t)jobs.j[i].a | (uintptr_t)jobs.j[i].b | (uintptr_t)coltab |
