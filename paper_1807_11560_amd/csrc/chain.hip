@@ -60,9 +60,6 @@ __global__ void k_tables(TableJobs jobs) {
       case TAB_INV:
         static_cast<float2*>(j.dst)[i] = inverse_entry(i % K, K, (i / K) % G, G, i / (G * K), false);
         break;
-      case TAB_INV_HALF:
-        static_cast<float2*>(j.dst)[i] = inverse_entry(i % (K / 2), K, (i / (K / 2)) % G, G, i / (G * (K / 2)), true);
-        break;
       case TAB_FWD:
       case TAB_FWD_HALF:
         static_cast<float2*>(j.dst)[i] = forward_entry(i / G, K, i % G, G, j.kind == TAB_FWD_HALF);

@@ -43,7 +43,7 @@ int prod_rows_max(const Dims& d);
 // ---------------------------------------------------------------- tables
 // One table of k_tables (see there for the kinds): `total` elements at dst.
 enum TableKind {
-  TAB_INV = 0, TAB_INV_HALF = 1, TAB_FWD = 2, TAB_FWD_HALF = 3,  // plain
+  TAB_INV = 0, TAB_FWD = 2, TAB_FWD_HALF = 3,  // plain
   TAB_ROW_INV = 4, TAB_ROW_INV_HALF = 5,                         // fragment order, see mfma.h
   TAB_PAIR_INV = 6, TAB_PAIR_INV_HALF = 7, TAB_PAIR_FWD = 8,
   TAB_COL1 = 11, TAB_COL0 = 12, TAB_COL0_INV = 13,  // instantiated shapes
@@ -73,8 +73,6 @@ struct Frags {
 // Twiddle tables for one transform direction set (grid G = M or N).
 struct Twiddles {
   const float2* inv0;  // [2][G0][K0]  exp(+2 pi i k x/G), variant 1 times 2 pi i k
-  const float2* inv1;  // [2][G1][K1]
-  const float2* inv2;  // [2][G2][Kh]  weight 1 (k2 = 0) or 2 folded in
   const float2* fwd0;  // [K0][G0]     exp(-2 pi i k x/G)
   const float2* fwd1;  // [K1][G1]
   const float2* fwd2;  // [Kh][G2]
@@ -242,7 +240,7 @@ hipError_t launch_fwd1(const Fwd1Jobs& jobs, int njobs, const float2* tw, int G0
                        int Kh, hipStream_t st);
 hipError_t launch_fwd0(const Fwd0Jobs& jobs, int njobs, const float2* tw, const float* Ksym, int G0,
                        int K0, int K1, int Kh, float invG, hipStream_t st);
-hipError_t launch_gridstep(const GridStepArgs& a, const Dims& d, const Twiddles& tw, const Frags& fr, hipStream_t st);
+hipError_t launch_gridstep(const GridStepArgs& a, const Dims& d, const Frags& fr, hipStream_t st);
 hipError_t launch_gridstep_chain(const GridStepArgs& a, const Dims& d, const Frags& fr, hipStream_t st);
 hipError_t launch_sl(const float* src, const float* vel, float* dst, float dt, const Dims& d,
                      hipStream_t st);

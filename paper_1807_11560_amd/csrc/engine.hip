@@ -155,7 +155,6 @@ void Engine::layout(Carver& c) {
     // does not depend on which kernels serve it.
     auto tables = [&](Carver& r, bool inst) {
       twbuf_ = r.take<float2>((inst ? 2 * ((size_t)d.M[0] + d.N[0]) * d.K[0] : 0) +
-                              (grid_instantiated(d) ? 2 * ((size_t)d.N[1] * d.K[1] + (size_t)d.N[2] * d.Kh) : 0) +
                               (size_t)d.K[0] * d.N[0] + (size_t)d.K[1] * d.N[1] +
                               (size_t)d.Kh * ((size_t)d.M[2] + d.N[2]));
       col_tab_ = inst ? r.take<float2>(col_table_count(d)) : nullptr;
@@ -215,10 +214,6 @@ Engine::Engine(const Dims& d, void* ws, hipStream_t st)
     const int* G = pass == 0 ? d.M : d.N;
     for (int j = 0; j < 3; ++j) tw.G[j] = G[j];
     if (inst) { tw.inv0 = t; t += 2 * (size_t)G[0] * d.K[0]; }
-    if (pass == 1 && grid_instantiated(d)) {
-      tw.inv1 = t; t += 2 * (size_t)G[1] * d.K[1];
-      tw.inv2 = t; t += 2 * (size_t)G[2] * d.Kh;
-    }
     if (pass == 1) {
       tw.fwd0 = t; t += (size_t)d.K[0] * G[0];
       tw.fwd1 = t; t += (size_t)d.K[1] * G[1];
@@ -264,10 +259,6 @@ hipError_t Engine::init_tables() {
     const Twiddles& tw = pass == 0 ? twM_ : twN_;
     const int* G = tw.G;
     if (inst) add(tw.inv0, TAB_INV, K[0], G[0], 2 * (size_t)G[0] * K[0]);
-    if (pass == 1 && grid_instantiated(d_)) {
-      add(tw.inv1, TAB_INV, K[1], G[1], 2 * (size_t)G[1] * K[1]);
-      add(tw.inv2, TAB_INV_HALF, K[2], G[2], 2 * (size_t)G[2] * d_.Kh);
-    }
     if (pass == 1) {
       add(tw.fwd0, TAB_FWD, K[0], G[0], (size_t)K[0] * G[0]);
       add(tw.fwd1, TAB_FWD, K[1], G[1], (size_t)K[1] * G[1]);
@@ -491,7 +482,7 @@ hipError_t Engine::grid_transport(const float2* band, bool stage0, float2* t1n, 
   a.src = src;
   a.dst = dst;
   a.dt = dt;
-  return launch_gridstep(a, d_, twN_, frN_, s);
+  return launch_gridstep(a, d_, frN_, s);
 }
 
 // Incremental transport source q = dm_n - dt grad_h m_n . dv_n of time step n
@@ -505,7 +496,7 @@ hipError_t Engine::grid_source(int n, const float* dmn, hipStream_t s) {
   a.dm = dmn;
   a.q = q;
   a.dt = 1.0f / d_.nt;
-  return launch_gridstep(a, d_, twN_, frN_, s);
+  return launch_gridstep(a, d_, frN_, s);
 }
 
 // t = 1 tail: out = K~ pi(coef [(a - b) grad_h m_nt + r grad_h a]) (b, r may be null), then the
@@ -661,7 +652,7 @@ hipError_t Engine::forward_rk(const float* I0, const float** m_out) {
     a.t1 = T1N[0];
     a.op = GRID_VELOCITY;
     a.vout = vg[0];
-    TRY(launch_gridstep(a, d_, twN_, frN_, st_));
+    TRY(launch_gridstep(a, d_, frN_, st_));
     float* dst = mlight[n & 1];
     TRY(launch_sl_rk2(cur, vg[0], dst, dt, d_, st_));
     cur = dst;
@@ -823,7 +814,7 @@ hipError_t Engine::grid_velocity_ckpt(int n, float* out, hipStream_t s) {
   a.t1 = T1N[0];
   a.op = GRID_VELOCITY;
   a.vout = out;
-  return launch_gridstep(a, d_, twN_, frN_, s);
+  return launch_gridstep(a, d_, frN_, s);
 }
 
 hipError_t Engine::forward_ckpt(const float* I0) {
@@ -867,7 +858,7 @@ hipError_t Engine::hessvec_exact(const float2* dvh, float2* out) {
     ga.t1 = T1N[n];
     ga.op = GRID_VELOCITY;
     ga.vout = dvg_;
-    TRY(launch_gridstep(ga, d_, twN_, frN_, st_));
+    TRY(launch_gridstep(ga, d_, frN_, st_));
     TRY(launch_sl_tangent(n == 0 ? nullptr : dm[cur], m[n], vg[n], dvg_, dm[1 - cur], dt, d_, st_));
     cur = 1 - cur;
     if (n == nt - 1) break;
@@ -976,7 +967,7 @@ hipError_t Engine::grid_field(const float2* band, bool have_t1n, float* out, hip
   a.t1 = T1NA_;
   a.op = GRID_VELOCITY;
   a.vout = out;
-  return launch_gridstep(a, d_, twN_, frN_, s);
+  return launch_gridstep(a, d_, frN_, s);
 }
 
 // Forward stages 1 and 0 of the three fields in S1N: pi(s) into `plain` and

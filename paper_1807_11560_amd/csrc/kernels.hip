@@ -878,18 +878,23 @@ constexpr int kGridRows = 16;  // rows of x1 per block of the source kernels
 // stage 2 the real part of a complex GEMM per (component, 16-column tile);
 // a wave owns the three components of its column tiles, so the source
 // term is formed in registers.
+// Both tables come from memory as fragments: staged in LDS they took 20 of 50 KB
+// and a block's third of the launch, with three blocks a compute unit; without,
+// five fit (four by registers) and the measured grids leave no ragged last wave
+// of blocks.  Source form: 144x176x144 / band 24 29 -> 22 us, 160x192x160 / band
+// 32 27 -> 22.5 us, 128^3 / band 32 14.3 -> 12.8 us.
 template <class G, bool BF3>
-__global__ void __launch_bounds__(256) k_gridstep_mfma(GridStepArgs a, Twiddles tw) {
+__global__ void __launch_bounds__(256, BF3 && G::N2() > 128 ? 3 : 4) k_gridstep_mfma(GridStepArgs a, const float4* __restrict__ f1,
+                                                          const float4* __restrict__ f2) {
+  using O = Op<BF3>;
   constexpr int N0 = G::N0(), N1 = G::N1(), N2 = G::N2(), K1 = G::K1(), Kh = G::Kh();
   constexpr int R = kGridRows;
   constexpr int Khp = (Kh + 15) & ~15;  // half-spectrum columns padded to whole tiles (zero)
-  constexpr int LT1 = Khp + 2, LW1 = K1 + 1, LT2 = Khp + 1, LW2 = N2 + 2;  // A operands: odd strides
-  constexpr int KP = K1 / 2, KHP = Kh / 2;
+  constexpr int LT1 = Khp + 2, LT2 = Khp + 1;  // A operands: odd strides
+  constexpr int KP = K1 / 2, KQ = (K1 + 15) / 16, KT = Khp / 16;
   static_assert(K1 % 4 == 0 && Kh % 2 == 0 && N2 % 16 == 0, "tuned grid shape");
   __shared__ __align__(16) float2 t1s[3][K1][LT1];
-  __shared__ __align__(16) float2 w1s[R][LW1];
   __shared__ __align__(16) float2 t2s[3][R][LT2];
-  __shared__ __align__(16) float2 w2t[Khp][LW2];
   // source: rows x1b - 1 .. x1b + R of m in plane x0 (periodic), for the x1
   // and x2 differences; the x0 differences are read directly
   constexpr int LM = N2 + 4;
@@ -905,17 +910,10 @@ __global__ void __launch_bounds__(256) k_gridstep_mfma(GridStepArgs a, Twiddles 
   // plane, the stage-1 rows, the stage-2 table, and (source) the neighbours
   // of the points this lane will write
   RegStage<(3 * Kh * KP + 255) / 256, float4> rt;
-  RegStage<(R * KP + 255) / 256, float4> rw1;
-  RegStage<(N2 * KHP + 255) / 256, float4> rw2;
   rt.load(3 * Kh * KP, [&](int i) {
     const int c = i / (Kh * KP), kh = (i / KP) % Kh, k1 = 2 * (i % KP);
     return ld4(a.t1 + (((size_t)c * N0 + x0) * Kh + kh) * K1 + k1);
   });
-  rw1.load(R * KP, [&](int i) {  // rows past N1 load a valid row and are zeroed when stored
-    const int x1 = x1b + i / KP;
-    return ld4(tw.inv1 + (size_t)(x1 < N1 ? x1 : N1 - 1) * K1 + 2 * (i % KP));
-  });
-  rw2.load(N2 * KHP, [&](int i) { return ld4(tw.inv2 + (size_t)(i / KHP) * Kh + 2 * (i % KHP)); });
   constexpr int NTJ = N2 / 16, TPW = (NTJ + 3) / 4, NM4 = (R + 2) * N2 / 4;
   RegStage<(NM4 + 255) / 256, float4> rm;
   if (a.op == 1) rm.load(NM4, [&](int i) {
@@ -945,30 +943,47 @@ __global__ void __launch_bounds__(256) k_gridstep_mfma(GridStepArgs a, Twiddles 
     t1s[c][k1][kh] = make_float2(v.x, v.y);
     t1s[c][k1 + 1][kh] = make_float2(v.z, v.w);
   });
-  rw1.store(R * KP, [&](int i, float4 v) { st22(&w1s[i / KP][2 * (i % KP)], x1b + i / KP < N1 ? v : z4); });
-  rw2.store(N2 * KHP, [&](int i, float4 v) {
-    const int x2 = i / KHP, kh = 2 * (i % KHP);
-    w2t[kh][x2] = make_float2(v.x, v.y);
-    w2t[kh + 1][x2] = make_float2(v.z, v.w);
-  });
   if (a.op == 1) rm.store(NM4, [&](int i, float4 v) {
     *reinterpret_cast<float4*>(&mrow[i / (N2 / 4)][4 * (i % (N2 / 4))]) = v;
   });
+  // the tables come as fragments: stage 1's with the block's loads, stage 2's
+  // for this wave's column tiles during stage 1
+  float4 w1[KQ][2], w2[TPW][KT][2];
+#pragma unroll
+  for (int g = 0; g < KQ; ++g)
+#pragma unroll
+    for (int p = 0; p < 2; ++p) w1[g][p] = (f1 + ((lb.x * 2 + p) * KQ + g) * 64)[lane];
   if constexpr (Khp > Kh) {  // zero padding columns of the half spectrum
     for (int i = threadIdx.x; i < 3 * K1 * (Khp - Kh); i += 256)
       t1s[i / (K1 * (Khp - Kh))][(i / (Khp - Kh)) % K1][Kh + i % (Khp - Kh)] = make_float2(0.f, 0.f);
-    for (int i = threadIdx.x; i < (Khp - Kh) * N2; i += 256) w2t[Kh + i / N2][i % N2] = make_float2(0.f, 0.f);
   }
   __syncthreads();
-  // stage 1: one 16 x Kh complex tile per component (waves 0..2 when Kh = 16)
+#pragma unroll
+  for (int q = 0; q < TPW; ++q)
+#pragma unroll
+    for (int g = 0; g < KT; ++g)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) w2[q][g][p] = (f2 + ((min(wave + 4 * q, NTJ - 1) * 2 + p) * KT + g) * 64)[lane];
+  // stage 1: one 16 x Kh complex tile per component (waves 0..2 when Kh = 16);
+  // the tables' second part is -im
   for (int jb = wave; jb < 3 * (Khp / 16); jb += 4) {
     const int c = jb % 3, tj = jb / 3;
     floatx4 acc[4];
     zero_acc(acc, 4);
-    ctile<K1 / 4, BF3>(&w1s[0][0], LW1, &t1s[c][0][tj * 16], LT1, acc);
+    const float2* B = &t1s[c][lk][tj * 16 + li];
+#pragma unroll
+    for (int ks = 0; ks < K1 / 4; ++ks) {
+      const float2 bv = B[4 * ks * LT1];
+      const typename O::T wr = O::a(elem(w1[ks / 4][0], ks % 4)), wi = O::a(elem(w1[ks / 4][1], ks % 4));
+      const typename O::T br = O::b(bv.x), bi = O::b(bv.y);
+      acc[0] = O::mma(wr, br, acc[0]);
+      acc[1] = O::mma(wi, bi, acc[1]);
+      acc[2] = O::mma(wr, bi, acc[2]);
+      acc[3] = O::mma(wi, br, acc[3]);
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      t2s[c][4 * lk + r][tj * 16 + li] = make_float2(acc[0][r] - acc[1][r], acc[2][r] + acc[3][r]);
+      t2s[c][4 * lk + r][tj * 16 + li] = make_float2(acc[0][r] + acc[1][r], acc[2][r] - acc[3][r]);
   }
   __syncthreads();
   // stage 2 + epilogue: a wave takes whole column tiles (all components)
@@ -982,16 +997,15 @@ __global__ void __launch_bounds__(256) k_gridstep_mfma(GridStepArgs a, Twiddles 
     for (int c = 0; c < 3; ++c) {
       floatx4 acc[4];
       zero_acc(acc, 4);
-      // only the real part is needed: acc0 - acc1
+      // only the real part is needed
       const float2* A = &t2s[c][0][0] + li * LT2 + lk;
-      const float2* B = &w2t[0][0] + lk * LW2 + tj * 16 + li;
 #pragma unroll
       for (int ks = 0; ks < Khp / 4; ++ks) {
-        const float2 av = A[4 * ks], bv = B[4 * ks * LW2];
-        acc[0] = mma<BF3>(av.x, bv.x, acc[0]);
-        acc[1] = mma<BF3>(av.y, bv.y, acc[1]);
+        const float2 av = A[4 * ks];
+        acc[0] = mma<BF3>(av.x, elem(w2[q][ks / 4][0], ks % 4), acc[0]);
+        acc[1] = mma<BF3>(av.y, elem(w2[q][ks / 4][1], ks % 4), acc[1]);
       }
-      vel[c] = acc[0] - acc[1];
+      vel[c] = acc[0] + acc[1];
     }
     const int x2 = tj * 16 + li;
 #pragma unroll
@@ -1901,7 +1915,7 @@ size_t src_shared_bytes(const Dims& d) {
          (size_t)d.Kh * d.N[2] * sizeof(float2);
 }
 
-hipError_t launch_gridstep(const GridStepArgs& a, const Dims& d, const Twiddles& tw, const Frags& fr, hipStream_t st) {
+hipError_t launch_gridstep(const GridStepArgs& a, const Dims& d, const Frags& fr, hipStream_t st) {
   {
     const double nN = (double)d.nN, C = (double)d.K[1] * d.Kh;
     const double fl = 3.0 * d.N[0] * d.N[1] * C * 8.0 + 3.0 * nN * d.Kh * 4.0 +
@@ -1910,16 +1924,16 @@ hipError_t launch_gridstep(const GridStepArgs& a, const Dims& d, const Twiddles&
     timer_work(KF_GRID, fl, 3.0 * d.N[0] * C * 8.0 + pts * nN);
   }
   if (a.op == GRID_TRANSPORT || !grid_instantiated(d)) return launch_gridstep_chain(a, d, fr, st);
-  if (!tw.inv1 || !tw.inv2) return hipErrorInvalidValue;
+  if (!fr.row1 || !fr.row2) return hipErrorInvalidValue;
   const dim3 grid(d.N[1] / kGridRows, d.N[0]);
   return with_grid(d, [&](auto gs) -> hipError_t {
     using G = decltype(gs);
     if constexpr (G::kStatic) {
       static_assert(G::N1() % kGridRows == 0 && G::N2() % 16 == 0 && G::K1() % 4 == 0, "matrix-core grid shape");
       if (d.prec)
-        LAUNCH_TIMED(KF_GRID, (k_gridstep_mfma<G, true>), grid, dim3(256), 0, st, a, tw);
+        LAUNCH_TIMED(KF_GRID, (k_gridstep_mfma<G, true>), grid, dim3(256), 0, st, a, fr.row1, fr.row2);
       else
-        LAUNCH_TIMED(KF_GRID, (k_gridstep_mfma<G, false>), grid, dim3(256), 0, st, a, tw);
+        LAUNCH_TIMED(KF_GRID, (k_gridstep_mfma<G, false>), grid, dim3(256), 0, st, a, fr.row1, fr.row2);
     }
     return hipGetLastError();
   });
