@@ -168,9 +168,11 @@ __global__ void __launch_bounds__(256, BF3 ? 3 : 4) k_synth_chain(SynthArgs a, c
 #pragma unroll
       for (int q = 0; q < KQ; ++q)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const unsigned k = 16 * q + 4 * u + lk;  // only the last group can pass K1
-          t[q][u] = plane[row + (q == KQ - 1 ? min(k, (unsigned)K1 - 1) : k)];
+        for (int u = 0; u < 4; u += 2) {
+          const unsigned k = 16 * q + 4 * u + 2 * lk;  // only the last group can pass K1
+          const floatx4 v = *reinterpret_cast<const floatx4*>(plane + (row + (q == KQ - 1 ? min(k, (unsigned)K1 - 2) : k)));
+          t[q][u] = make_float2(v.x, v.y);
+          t[q][u + 1] = make_float2(v.z, v.w);
         }
       float4 tb[NV], nx[NV];
       auto table = [&](int pq, float4 (&w)[NV]) {
@@ -185,6 +187,13 @@ __global__ void __launch_bounds__(256, BF3 ? 3 : 4) k_synth_chain(SynthArgs a, c
       for (int pq = 0; pq < 2 * KQ; ++pq) {
         const int part = pq / KQ, q = pq % KQ;
         if (pq + 1 < 2 * KQ) table(pq + 1, nx);
+        if (part == 0) {
+#pragma unroll
+          for (int u = 0; u < 4; u += 2) {
+            swap_quarters(t[q][u].x, t[q][u + 1].x);
+            swap_quarters(t[q][u].y, t[q][u + 1].y);
+          }
+        }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const float2 p = t[q][u];

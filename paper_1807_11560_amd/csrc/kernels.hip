@@ -218,13 +218,14 @@ __global__ void __launch_bounds__(256) k_prods(ProdArgs a, Twiddles tw, BandDyn 
   const int P = R * M2;
   const int LV = M2 + 2;  // product rows: 2 mod 4 floats, an MFMA A operand read along rows
   const long long nM = (long long)M0 * M1 * M2;
-  float2* wfx = (float2*)smp;                  // [M2][Kh]
-  float* outv = (float*)(wfx + M2 * Kh);       // [nout][R][LV]
+  const int LW = row_ld(M2);
+  float2* wfx = (float2*)smp;                  // [Kh][LW]
+  float* outv = (float*)(wfx + Kh * LW);       // [nout][R][LV]
   // the stage-2 table goes to LDS after the products (its loads overlap theirs)
   const int nw = M2 * Kh;
   const bool wreg = nw <= 256 * 4 && blockDim.x == 256;  // the register stage covers 256 threads
   RegStage<4, float2> rw;
-  if (wreg) rw.load(nw, [&](int i) { return tw.fwd2[(size_t)(i % Kh) * M2 + i / Kh]; });
+  if (wreg) rw.load(nw, [&](int i) { return tw.fwd2[i]; });
   for (int p = threadIdx.x; p < P; p += blockDim.x) {
     const int r = p / M2;
     float o[9];
@@ -355,11 +356,12 @@ __global__ void __launch_bounds__(256) k_prods(ProdArgs a, Twiddles tw, BandDyn 
     if (p < P)
       for (int i = 0; i < a.nout; ++i) outv[((size_t)i * R + p / M2) * LV + p % M2] = o[i];
   }
+  // (read along its rows: across them each lane touched a line of its own)
+  auto put = [&](int i, float2 v) { wfx[(i / M2) * LW + i % M2] = v; };
   if (wreg)
-    rw.store(nw, [&](int i, float2 v) { wfx[i] = v; });
+    rw.store(nw, put);
   else
-    batched_fill<float2>(nw, [&](int i) { return tw.fwd2[(size_t)(i % Kh) * M2 + i / Kh]; },
-                         [&](int i, float2 v) { wfx[i] = v; });
+    batched_fill<float2>(nw, [&](int i) { return tw.fwd2[i]; }, put);
   __syncthreads();
   if (M2 % 4 == 0) {
     // forward stage 2 on the matrix cores: D[row][kh] = sum_x2 outv[row][x2] fwd2[kh][x2],
@@ -370,11 +372,11 @@ __global__ void __launch_bounds__(256) k_prods(ProdArgs a, Twiddles tw, BandDyn 
       const int ti = t / tcol, tj = t % tcol;
       const int arow = ti * 16 + li, kh = tj * 16 + li;
       const float* A = outv + (size_t)(arow < rows ? arow : 0) * LV + lk;
-      const float2* B = wfx + (size_t)lk * Kh + (kh < Kh ? kh : 0);
+      const float2* B = wfx + (kh < Kh ? kh : 0) * LW + lk;
       floatx4 dre = {0.f, 0.f, 0.f, 0.f}, dim = {0.f, 0.f, 0.f, 0.f};
       for (int ks = 0; ks < M2 / 4; ++ks) {
         const float av = (arow < rows) ? A[4 * ks] : 0.f;
-        const float2 bv = (kh < Kh) ? B[(size_t)4 * ks * Kh] : make_float2(0.f, 0.f);
+        const float2 bv = (kh < Kh) ? B[4 * ks] : make_float2(0.f, 0.f);
         dre = mma<BF3>(av, bv.x, dre);
         dim = mma<BF3>(av, bv.y, dim);
       }
@@ -396,7 +398,7 @@ __global__ void __launch_bounds__(256) k_prods(ProdArgs a, Twiddles tw, BandDyn 
     const float* row = outv + ((size_t)o * R + r) * LV;
     float2 acc = make_float2(0.f, 0.f);
     for (int x2 = 0; x2 < M2; ++x2) {
-      const float2 w = wfx[(size_t)x2 * Kh + kh];
+      const float2 w = wfx[kh * LW + x2];
       acc.x = fmaf(row[x2], w.x, acc.x);
       acc.y = fmaf(row[x2], w.y, acc.y);
     }
@@ -1730,6 +1732,7 @@ static int prod_rows(const Dims& d) {
   return (d.tile_prod_rows > 0 && d.tile_prod_rows < R) ? d.tile_prod_rows : R;
 }
 
+// Limit on the problem sizes (validated at the boundary).
 size_t prods_shared_bytes(const Dims& d, int nout) {
   return (size_t)d.M[2] * d.Kh * sizeof(float2) + (size_t)nout * prod_rows(d) * (d.M[2] + 2) * sizeof(float);
 }
@@ -1737,7 +1740,8 @@ size_t prods_shared_bytes(const Dims& d, int nout) {
 hipError_t launch_prods(const ProdArgs& a, const Dims& d, const Twiddles& tw, hipStream_t st) {
   const int R = prod_rows(d);
   dim3 grid(nblk(d.M[1], R), d.M[0]);
-  size_t shm = prods_shared_bytes(d, a.nout);
+  const size_t shm = (size_t)d.Kh * row_ld(d.M[2]) * sizeof(float2) +
+                     (size_t)a.nout * R * (d.M[2] + 2) * sizeof(float);
   {
     static const double prog_flops[11] = {0, 47, 94, 136, 272, 136, 18, 36, 18, 36, 89};
     static const int prog_fields[11] = {0, 24, 48, 48, 96, 48, 12, 24, 12, 24, 36};

@@ -69,6 +69,9 @@ struct Op<true> {
 // in all lanes (addresses built from it stay in scalar registers).
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
+// Row stride of complex values read 16 rows at a time: twice an odd number.
+__host__ __device__ constexpr int row_ld(int n) { return 2 * (((n + 1) / 2) | 1); }
+
 __device__ __forceinline__ floatx4 zero4() { return floatx4{0.f, 0.f, 0.f, 0.f}; }
 
 // ------------------------------------------------------------ chained stages
@@ -114,6 +117,16 @@ __device__ __forceinline__ void swap_halves(float& x, float& y) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
   x = __uint_as_float(r[0]);
   y = __uint_as_float(r[1]);
+}
+
+// Rows of 16 lanes lk = 0 .. 3 hold (x, y) = values 2 lk and 2 lk + 1 of eight:
+// after the exchange x holds value lk, y value 4 + lk (two k-steps of four from
+// one load of consecutive values).
+__device__ __forceinline__ void swap_quarters(float& x, float& y) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(a[0], a[1], false, false);
+  x = __uint_as_float(b[0]);
+  y = __uint_as_float(b[1]);
 }
 
 // 16-byte loads and stores of 4- or 8-byte aligned addresses

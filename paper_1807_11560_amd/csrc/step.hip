@@ -19,9 +19,6 @@ constexpr int step_cached(int prog) {
   return prog == PROG_SHOOT ? 0 : prog == PROG_H5 ? 6 : prog == PROG_DEF_FWD ? 1 : prog == PROG_DEF_H ? 3 : 2;
 }
 
-// Row stride of complex values read 16 rows at a time: twice an odd number.
-__host__ __device__ constexpr int row_ld(int n) { return 2 * (((n + 1) / 2) | 1); }
-
 // One block per (x0 plane, 16 x1): inverse stages 1 and 2 of the step's new
 // fields, the products of the program with them and the cached groups, and
 // the products' forward stage 2, in the orders of k_synth_chain and k_prods.
