@@ -358,59 +358,44 @@ __global__ void __launch_bounds__(64 * NW, 4) k_column_chain(ColJobs jobs, Frags
     const int t = un / XT, xt = un % XT;
     const float2* plane = (t ? job.b : job.a) + (size_t)kh * M0 * M1;
     const unsigned row = min(16 * xt + li, M0 - 1) * M1;
-    // two k-steps' values per 16-byte load (an odd row length: one load each)
-    auto load = [&](int j, float2 (&s)[kS][4]) {
-      if (M1 & 1) {
+    // four k-steps' values per 16-byte load (a row of odd length: its last pair
+    // begins one earlier)
+    auto load = [&](int j, float4 (&s)[kS]) {
 #pragma unroll
-        for (int q = 0; q < kS; ++q)
-#pragma unroll
-          for (int u = 0; u < 4; ++u) s[q][u] = plane[row + min(2 * (4 * (j + q) + u) + h, M1 - 1)];
-      } else {
-#pragma unroll
-        for (int q = 0; q < kS; ++q)
-#pragma unroll
-          for (int u = 0; u < 4; u += 2) {
-            const float4 v = ldu4(reinterpret_cast<const float*>(plane + (row + min(2 * (4 * (j + q) + u) + 2 * h, M1 - 2))));
-            s[q][u] = make_float2(v.x, v.y);
-            s[q][u + 1] = make_float2(v.z, v.w);
-          }
-      }
-    };
-    auto arrange = [&](float2 (&s)[kS][4]) {  // after the loads have arrived
-      if (M1 & 1) return;
-#pragma unroll
-      for (int q = 0; q < kS; ++q)
-#pragma unroll
-        for (int u = 0; u < 4; u += 2) {
-          swap_halves(s[q][u].x, s[q][u + 1].x);
-          swap_halves(s[q][u].y, s[q][u + 1].y);
+      for (int q = 0; q < kS; ++q) {
+        const int k = 8 * (j + q) + 2 * lk;
+        s[q] = ldu4(reinterpret_cast<const float*>(plane + (row + min(k, M1 - 2))));
+        if ((M1 & 1) && k > M1 - 2) {
+          s[q].x = s[q].z;
+          s[q].y = s[q].w;
         }
+      }
     };
     ColTab<kS> f1;
     f1.open(fM.fwd1 + (size_t)kc * JM1 * 64, JM1);
-    float2 s[kS][4], sn[kS][4];
+    float4 s[kS], sn[kS];
     load(0, s);
     floatx4 re = zero4(), im = zero4();
     for (int j = 0; j < JM1; j += kS) {
       float4 wn[kS];
       f1.load(j + kS, wn);
       load(j + kS, sn);
-      arrange(s);
 #pragma unroll
       for (int q = 0; q < kS; ++q) {
         if (j + q >= JM1) break;
+        float sr[4], si[4];
+        pair_operands(s[q], sr, si);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const float wi = elem(f1.w[q], u), wr = flip(wi, neg);
-          re = Op<false>::mma(part ? s[q][u].y : s[q][u].x, wr, re);
-          im = Op<false>::mma(part ? s[q][u].x : s[q][u].y, wi, im);
+          re = Op<false>::mma(sr[u], wr, re);
+          im = Op<false>::mma(si[u], wi, im);
         }
       }
 #pragma unroll
       for (int q = 0; q < kS; ++q) {
         f1.w[q] = wn[q];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) s[q][u] = sn[q][u];
+        s[q] = sn[q];
       }
     }
 #pragma unroll
@@ -649,32 +634,23 @@ __global__ void __launch_bounds__(256, 4) k_gridstep(GridStepArgs a, const float
     } else {
       re = im = zero4();
       for (int j0 = 0; j0 < J1; j0 += 4) {
-        float4 w[4];
-        float2 t[4][4];
+        float4 w[4], t[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int j = min(j0 + q, J1 - 1);
           w[q] = (f1 + ((size_t)x1t * J1 + j) * 64)[lane];
-#pragma unroll
-          for (int u = 0; u < 4; u += 2) {
-            const float4 v = ldu4(reinterpret_cast<const float*>(plane + (row + min(2 * (4 * j + u) + 2 * h, K1 - 2))));
-            t[q][u] = make_float2(v.x, v.y);
-            t[q][u + 1] = make_float2(v.z, v.w);
-          }
+          t[q] = ldu4(reinterpret_cast<const float*>(plane + (row + min(8 * j + 2 * lk, K1 - 2))));
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           if (j0 + q >= J1) break;
-#pragma unroll
-          for (int u = 0; u < 4; u += 2) {
-            swap_halves(t[q][u].x, t[q][u + 1].x);
-            swap_halves(t[q][u].y, t[q][u + 1].y);
-          }
+          float tr[4], ti[4];
+          pair_operands(t[q], tr, ti);
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const float wi = elem(w[q], u), wr = flip(wi, neg);
-            re = Op<false>::mma(part ? t[q][u].y : t[q][u].x, wr, re);
-            im = Op<false>::mma(part ? t[q][u].x : t[q][u].y, wi, im);
+            re = Op<false>::mma(tr[u], wr, re);
+            im = Op<false>::mma(ti[u], wi, im);
           }
         }
       }

@@ -110,15 +110,6 @@ __device__ __forceinline__ float flip(float x, unsigned sign) {
   return __uint_as_float(__float_as_uint(x) ^ sign);
 }
 
-// A lane of the lower half (lanes 0-31) holds the values (2 m, 2 m + 1) of a
-// row, its partner in the upper half (2 m + 2, 2 m + 3): after the exchange x
-// holds 2 m + h and y 2 m + 2 + h, h = 0 in the lower, 1 in the upper half.
-__device__ __forceinline__ void swap_halves(float& x, float& y) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-  x = __uint_as_float(r[0]);
-  y = __uint_as_float(r[1]);
-}
-
 // Rows of 16 lanes lk = 0 .. 3 hold (x, y) = values 2 lk and 2 lk + 1 of eight:
 // after the exchange x holds value lk, y value 4 + lk (two k-steps of four from
 // one load of consecutive values).
@@ -127,6 +118,24 @@ __device__ __forceinline__ void swap_quarters(float& x, float& y) {
   const auto b = __builtin_amdgcn_permlane32_swap(a[0], a[1], false, false);
   x = __uint_as_float(b[0]);
   y = __uint_as_float(b[1]);
+}
+
+// A lane of row lk holds complex elements 2 lk (v.x, v.y) and 2 lk + 1 (v.z,
+// v.w) of eight: the operands of four k-steps in "pairs" order, k-step s element
+// 2 s + lk / 2, the part of it that meets re w (lk even) or im w (lk odd).
+__device__ __forceinline__ void pair_operands(const float4& v, float (&re)[4], float (&im)[4]) {
+  auto four = [](float x0, float y0, float x1, float y1, float (&o)[4]) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x0), __float_as_uint(y0), false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x1), __float_as_uint(y1), false, false);
+    const auto e = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
+    const auto f = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
+    o[0] = __uint_as_float(e[0]);
+    o[1] = __uint_as_float(f[0]);
+    o[2] = __uint_as_float(e[1]);
+    o[3] = __uint_as_float(f[1]);
+  };
+  four(v.x, v.y, v.z, v.w, re);
+  four(v.y, v.x, v.w, v.z, im);
 }
 
 // 16-byte loads and stores of 4- or 8-byte aligned addresses

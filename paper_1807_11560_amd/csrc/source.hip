@@ -373,54 +373,52 @@ __global__ void __launch_bounds__(256) k_rho_fwd2(RhoArgs a, float2* __restrict_
 // Complex sums over x of a 16 x 16 tile as matrix products, k-step ks holding
 // x = 2 ks + h and the two parts of the product (lane lk = 2 h + part): per x
 // first re w, then im w, the order of scalar code.  w is the table's row of this
-// lane (w(k, x), k = lane % 16: read as it is, 16 bytes or two x a lane for two
+// lane (w(k, x), k = lane % 16: read as it is, 16 bytes or two x a lane for four
 // k-steps), v its data column (element lane % 16, the next x ld further).  The
-// operands of the next 4 U x are on their way while the present ones are
+// operands of the next 8 U x are on their way while the present ones are
 // summed.  DataA: the data are the tile's rows, else its columns.  (A thread per
 // output column and sums out of LDS: 20 and 17 us for stages 1 and 0 at
 // 144x176x144 / band 24.)
 template <bool DataA>
 __device__ __forceinline__ void fwd_sum(const float2* __restrict__ w, const float2* __restrict__ v, unsigned ld, int N,
                                         floatx4* re, floatx4* im) {
-  constexpr int U = 4;
+  constexpr int U = 2;
   const int lk = (threadIdx.x & 63) >> 4, h = lk >> 1, part = lk & 1;
   struct Batch {
     float4 w[U];
-    float2 v[2 * U];
+    float2 v[U][4];
   } cur, nxt;
   auto load = [&](int x, Batch& b) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      b.w[u] = ldu4(reinterpret_cast<const float*>(w + min(x + 4 * u + 2 * h, N - 2)));
-      b.v[2 * u] = v[(unsigned)min(x + 4 * u + h, N - 1) * ld];
-      b.v[2 * u + 1] = v[(unsigned)min(x + 4 * u + 2 + h, N - 1) * ld];
+      b.w[u] = ldu4(reinterpret_cast<const float*>(w + min(x + 8 * u + 2 * lk, N - 2)));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) b.v[u][k] = v[(unsigned)min(x + 8 * u + 2 * k + h, N - 1) * ld];
     }
   };
   floatx4 r = zero4(), i = zero4();
-  auto step = [&](float t, float ex, float ey) {
-    const float a = part ? -ey : ex, b = part ? ex : ey;
-    if constexpr (DataA) {
-      r = __builtin_amdgcn_mfma_f32_16x16x4f32(a, t, r, 0, 0, 0);
-      i = __builtin_amdgcn_mfma_f32_16x16x4f32(b, t, i, 0, 0, 0);
-    } else {
-      r = __builtin_amdgcn_mfma_f32_16x16x4f32(t, a, r, 0, 0, 0);
-      i = __builtin_amdgcn_mfma_f32_16x16x4f32(t, b, i, 0, 0, 0);
-    }
-  };
   load(0, cur);
-  for (int x = 0; x < N; x += 4 * U) {
-    if (x + 4 * U < N) load(x + 4 * U, nxt);
+  for (int x = 0; x < N; x += 8 * U) {
+    if (x + 8 * U < N) load(x + 8 * U, nxt);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int s = x + 4 * u + 2 * h;
-      const float wx = cur.w[u].x, wy = cur.w[u].y, wz = cur.w[u].z, ww = cur.w[u].w;
-      float t0 = part ? wy : wx, t1 = part ? ww : wz;
-      if (s > N - 2) t0 = t1;  // the load began at N - 2
-      swap_halves(t0, t1);
-      const bool in0 = x + 4 * u + h < N, in1 = x + 4 * u + 2 + h < N;
-      const float2 e0 = cur.v[2 * u], e1 = cur.v[2 * u + 1];
-      step(t0, in0 ? e0.x : 0.f, in0 ? e0.y : 0.f);
-      step(t1, in1 ? e1.x : 0.f, in1 ? e1.y : 0.f);
+      float4 q = cur.w[u];
+      if (x + 8 * u + 2 * lk > N - 2) q = make_float4(q.z, q.w, q.z, q.w);  // the load began at N - 2
+      float t[4], unused[4];
+      pair_operands(q, t, unused);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const bool in = x + 8 * u + 2 * k + h < N;
+        const float ex = in ? cur.v[u][k].x : 0.f, ey = in ? cur.v[u][k].y : 0.f;
+        const float a = part ? -ey : ex, b = part ? ex : ey;
+        if constexpr (DataA) {
+          r = __builtin_amdgcn_mfma_f32_16x16x4f32(a, t[k], r, 0, 0, 0);
+          i = __builtin_amdgcn_mfma_f32_16x16x4f32(b, t[k], i, 0, 0, 0);
+        } else {
+          r = __builtin_amdgcn_mfma_f32_16x16x4f32(t[k], a, r, 0, 0, 0);
+          i = __builtin_amdgcn_mfma_f32_16x16x4f32(t[k], b, i, 0, 0, 0);
+        }
+      }
     }
     cur = nxt;
   }
