@@ -379,12 +379,13 @@ int lddmm_register_batch(int32_t n, const lddmm_params* p, const float* const* I
  * against concurrent enabling. */
 enum {
   LDDMM_KF_NONE = 0,
-  LDDMM_KF_SYNTH = 1,      /* k_synth: padded-grid synthesis of new fields (inverse stages 1-2, MFMA) */
+  LDDMM_KF_SYNTH = 1,      /* k_synth_chain: padded-grid synthesis of new fields (inverse stages 1-2, MFMA) */
   LDDMM_KF_GRID = 2,       /* k_gridstep: grid velocity / incremental-state source (inverse stages 1-2) */
   LDDMM_KF_SL = 3,         /* k_sl: semi-Lagrangian transport step */
   LDDMM_KF_INV0 = 4,       /* k_inv0 (padded grid): inverse stage 0 at the start of a sweep */
   LDDMM_KF_COLUMN = 5,     /* k_colstep: forward stages 1-0, band update, next inverse stage 0 */
-  LDDMM_KF_PRODS = 6,      /* k_prods: Lie products and forward stage 2 on the padded grid */
+  LDDMM_KF_PRODS = 6,      /* k_prods, k_step: Lie products and forward stage 2 on the padded grid; k_step (small
+                            * bands) with the synthesis in the same launch */
   LDDMM_KF_INV0_GRID = 7,  /* k_inv0 (image grid): inverse stage 0 of a grid velocity */
   LDDMM_KF_FWD1_GRID = 8,  /* k_fwd1: forward stage 1 of a grid field */
   LDDMM_KF_FWD0_GRID = 9,  /* k_fwd0: forward stage 0 of a grid field and its band epilogue */
@@ -417,7 +418,9 @@ int lddmm_use_graphs(int32_t enable);
  * table).  They change which thread blocks compute what, never the
  * arithmetic of an output: results are bitwise those of the built-in rule.
  *   prod_rows   padded-grid rows per block of the pointwise Lie products
- *               (1 .. floor(256 / M2), capped at M1; 0: the largest)
+ *               (1 .. floor(256 / M2), capped at M1; 0: the largest) where they are
+ *               a launch of their own: no effect on steps that form them with the
+ *               synthesis (half spectra up to 16, K1 up to 32, M2 up to 48)
  *   col_split   band column steps: 0 the built-in rule, 1 one block per
  *               column tile, 2 two blocks per tile sharing its next-stage
  *               outputs, 3 as 2 with the lean kernel for the forward

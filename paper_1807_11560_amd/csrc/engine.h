@@ -32,6 +32,8 @@ class Engine {
  public:
   Engine(const Dims& d, void* ws, hipStream_t st);
   static size_t workspace_bytes(const Dims& d);
+  // What the fragment tables take of that above the plain tables' room.
+  static size_t table_surplus(const Dims& d);
 
   hipError_t init_tables();
   // band I/O in the caller's full layout
@@ -151,6 +153,7 @@ class Engine {
   bool one_stream_ = false;
   std::vector<hipEvent_t>* ev_ = nullptr;
   Twiddles twM_{}, twN_{};
+  size_t table_surplus_ = 0;
   float2* twbuf_ = nullptr;
   float2 *T1_ = nullptr, *S1_ = nullptr, *S1N_ = nullptr, *S2N_ = nullptr;
   float2 *T1NA_ = nullptr, *S1A_ = nullptr;  // displacement chain: image-grid stage 0, products

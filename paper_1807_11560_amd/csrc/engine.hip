@@ -151,8 +151,8 @@ void Engine::layout(Carver& c) {
   {
     // One region for the tables: those of the instantiated shapes, or the
     // fragment tables in their place.  Never smaller than the former, so that
-    // the workspace of a problem (and with it what lddmm_shoot_static takes)
-    // does not depend on which kernels serve it.
+    // the workspace of a problem does not depend on which kernels serve it;
+    // larger by up to table_surplus where few k1 or k2 fill a 16-row fragment.
     auto tables = [&](Carver& r, bool inst) {
       twbuf_ = r.take<float2>((inst ? 2 * ((size_t)d.M[0] + d.N[0]) * d.K[0] : 0) +
                               (size_t)d.K[0] * d.N[0] + (size_t)d.K[1] * d.N[1] +
@@ -166,6 +166,7 @@ void Engine::layout(Carver& c) {
     a.take<float2>(col_table_count(d));
     tables(b, band_instantiated(d));
     Carver r{c.take<char>(std::max(a.off, b.off))};
+    table_surplus_ = b.off > a.off ? b.off - a.off : 0;
     tables(r, band_instantiated(d));
   }
   const size_t C = (size_t)d.K[1] * d.Kh;
@@ -244,6 +245,10 @@ size_t Engine::workspace_bytes(const Dims& d) {
   Carver c{nullptr};
   e.layout(c);
   return c.off + 256;
+}
+
+size_t Engine::table_surplus(const Dims& d) {
+  return Engine(d, nullptr, nullptr).table_surplus_;
 }
 
 hipError_t Engine::init_tables() {
