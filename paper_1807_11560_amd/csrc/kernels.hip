@@ -1453,10 +1453,24 @@ __global__ void __launch_bounds__(kRedThreads) k_sqdiff(const float* a, const fl
                                                         double* partial) {
   __shared__ double sh[kRedThreads / 64];
   double s = 0.0;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    double d = (double)a[i] - (double)(b ? b[i] : 0.f);
-    s += d * d;
+  // eight points' loads in flight, added in the order of the points (one at a
+  // time: 37 us at 180x210x180, a memory latency per point)
+  constexpr int U = 8;
+  const long long stride = (long long)gridDim.x * blockDim.x;
+  const float* bb = b ? b : a;  // (a load under a branch waits for every load in flight)
+  for (long long i0 = (long long)blockIdx.x * blockDim.x + threadIdx.x; i0 < n; i0 += U * stride) {
+    float x[U], y[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const long long i = min(i0 + u * stride, n - 1);
+      x[u] = a[i];
+      y[u] = bb[i];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double d = i0 + u * stride < n ? (double)x[u] - (double)(b ? y[u] : 0.f) : 0.0;
+      s += d * d;
+    }
   }
   double r = block_sum(s, sh);
   if (threadIdx.x == 0) partial[blockIdx.x] = r;

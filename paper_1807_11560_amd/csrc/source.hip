@@ -382,7 +382,7 @@ __global__ void __launch_bounds__(256) k_rho_fwd2(RhoArgs a, float2* __restrict_
 template <bool DataA>
 __device__ __forceinline__ void fwd_sum(const float2* __restrict__ w, const float2* __restrict__ v, unsigned ld, int N,
                                         floatx4* re, floatx4* im) {
-  constexpr int U = 2;
+  constexpr int U = 4;
   const int lk = (threadIdx.x & 63) >> 4, h = lk >> 1, part = lk & 1;
   struct Batch {
     float4 w[U];
