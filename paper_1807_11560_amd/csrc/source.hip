@@ -10,52 +10,60 @@ namespace {
 // --------------------------------------------- forward stage 2 of a tile
 // A tile of 16 rows of x1 of three real fields in LDS, vals[(3 fields) 16 rows
 // of LV floats], the columns x2 = N2 .. 4 ceil(N2 / 4) - 1 zero: a wave takes
-// (field, 16 kh) products D[row][kh] = sum_x2 vals[row][x2] w(kh, x2), the real
-// and the imaginary part as two chains of matrix products, each the sequential
+// (field, real or imaginary part, 16 kh) products D[row][kh] = sum_x2
+// vals[row][x2] w(kh, x2), each a chain of matrix products and so the sequential
 // sum over x2 (v_mfma_f32_16x16x4f32 adds its four products in turn), as scalar
-// code forms it.  (With a thread per (row, kh) and the table in LDS the source
-// kernel took 102 us at 180x210x180 / band 32, 52 so.)  LV is an odd multiple of 4 floats: the 16 rows and 4 columns
-// that a wave reads at once lie in different banks.
+// code forms it.  LV is an odd multiple of 4 floats: the 16 rows and 4 columns
+// that a wave reads at once lie in different banks.  The table goes through
+// LDS: a wave's operand of it from memory touches 16 rows per 16 lanes, 64
+// cycles of the address unit.  The source kernel at 144x176x144 / band 24: 61 us
+// with a thread per (row, kh), 44 with the table from memory, 30 so; at
+// 180x210x180 / band 32 102, 51 and 56 (whose product phases overlap less).
 __host__ __device__ constexpr int tile_ld(int N2) {
   const int q = (N2 + 3) / 4;
   return 4 * (q | 1);
 }
+constexpr int kSrcThreads = 512;
+// The stage-2 table w(kh, x2) to LDS, ws[Kh][row_ld(N2)]: read along its rows.
+__device__ __forceinline__ void stage_fwd2(float2* ws, const float2* __restrict__ w, int N2, int Kh) {
+  const int n = Kh * N2, LW = row_ld(N2);
+  constexpr int U = 4;
+  for (int i0 = threadIdx.x; i0 < n; i0 += U * kSrcThreads) {
+    float2 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = w[min(i0 + u * kSrcThreads, n - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * kSrcThreads;
+      if (i < n) ws[(i / N2) * LW + i % N2] = v[u];
+    }
+  }
+}
 template <class Store>
-__device__ __forceinline__ void fwd2_tile(const float* vals, const float2* __restrict__ w, int N2, int Kh, int waves,
-                                          Store store) {
+__device__ __forceinline__ void fwd2_tile(const float* vals, const float2* ws, int N2, int Kh, int waves, Store store) {
   const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
   const int LV = tile_ld(N2), kt = (Kh + 15) / 16, nk = (N2 + 3) / 4;
-  for (int job = wave_id(); job < 3 * kt; job += waves) {
-    const int j = job % 3, kh = (job / 3) * 16 + li;
+  for (int job = wave_id(); job < 6 * kt; job += waves) {
+    const int j = job % 3, part = (job / 3) & 1, kh = (job / 6) * 16 + li;
     const float* row = vals + (j * 16 + li) * LV + lk;
-    const float2* wr = w + (unsigned)(min(kh, Kh - 1) * N2);
-    floatx4 re = zero4(), im = zero4();
-    // the table of the next U k-steps is on its way while the present ones are summed
+    const float* wr = reinterpret_cast<const float*>(ws + min(kh, Kh - 1) * row_ld(N2)) + part;
+    floatx4 acc = zero4();
     constexpr int U = 8;
-    float2 t[U], n[U];
-    auto load = [&](int ks, float2(&q)[U]) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) q[u] = wr[min(4 * (ks + u) + lk, N2 - 1)];
-    };
-    load(0, t);
     for (int ks = 0; ks < nk; ks += U) {
       float a[U];
+      float t[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         a[u] = row[4 * min(ks + u, nk - 1)];
+        t[u] = wr[2 * min(4 * (ks + u) + lk, N2 - 1)];
         if (ks + u >= nk) a[u] = 0.f;
       }
-      if (ks + U < nk) load(ks + U, n);
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        re = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], t[u].x, re, 0, 0, 0);
-        im = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], t[u].y, im, 0, 0, 0);
-        t[u] = n[u];
-      }
+      for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], t[u], acc, 0, 0, 0);
     }
     if (kh < Kh) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) store(j, 4 * lk + r, kh, make_float2(re[r], im[r]));
+      for (int r = 0; r < 4; ++r) store(j, 4 * lk + r, 2 * kh + part, acc[r]);
     }
   }
 }
@@ -79,7 +87,7 @@ __device__ __forceinline__ float central_diff(const float* __restrict__ m, int x
 // differences; b and res may be null) at the points of 16 x1 rows of plane x0, contracted
 // over x2: s1[j][x0][x1][kh].
 template <class G>
-__global__ void __launch_bounds__(256) k_src_fwd2(const float* __restrict__ a,
+__global__ void __launch_bounds__(kSrcThreads) k_src_fwd2(const float* __restrict__ a,
                                                   const float* __restrict__ b,
                                                   const float* __restrict__ res,
                                                   const float* __restrict__ m, float coef,
@@ -91,31 +99,38 @@ __global__ void __launch_bounds__(256) k_src_fwd2(const float* __restrict__ a,
   const int rv = min(16, N1 - x1b);
   const int LV = tile_ld(N2), L4 = (N2 + 3) & ~3;
   float* vals = shs;  // [3][16][LV]
-  for (int p = threadIdx.x; p < 16 * L4; p += blockDim.x) {
-    int r = p / L4, x2 = p % L4;
-    int x1 = x1b + r;
-    float v0 = 0.f, v1 = 0.f, v2 = 0.f;
-    if (r < rv && x2 < N2) {
-      const unsigned gi = ((unsigned)x0 * N1 + x1) * N2 + x2;
-      float s = coef * (a[gi] - (b ? b[gi] : 0.f));
-      v0 = s * central_diff(m, x0, x1, x2, N0, N1, N2, 0);
-      v1 = s * central_diff(m, x0, x1, x2, N0, N1, N2, 1);
-      v2 = s * central_diff(m, x0, x1, x2, N0, N1, N2, 2);
-      if (res) {
-        const float t = coef * res[gi];
-        v0 = fmaf(t, central_diff(a, x0, x1, x2, N0, N1, N2, 0), v0);
-        v1 = fmaf(t, central_diff(a, x0, x1, x2, N0, N1, N2, 1), v1);
-        v2 = fmaf(t, central_diff(a, x0, x1, x2, N0, N1, N2, 2), v2);
-      }
+  float2* ws = reinterpret_cast<float2*>(shs + 48 * LV);
+  stage_fwd2(ws, tw.fwd2, N2, Kh);
+  // Two points per iteration, every load of a point unconditional (a load under a
+  // branch waits for every load in flight): points past the tile repeat one.
+  const float* bb = b ? b : a;
+#pragma unroll 2
+  for (int p = threadIdx.x; p < 16 * L4; p += kSrcThreads) {
+    const int r = p / L4, x2 = p - r * L4;
+    const int x1 = min(x1b + r, N1 - 1), xc = min(x2, N2 - 1);
+    const unsigned gi = ((unsigned)x0 * N1 + x1) * N2 + xc;
+    const float av = a[gi], bv = bb[gi];
+    float v0 = central_diff(m, x0, x1, xc, N0, N1, N2, 0), v1 = central_diff(m, x0, x1, xc, N0, N1, N2, 1),
+          v2 = central_diff(m, x0, x1, xc, N0, N1, N2, 2);
+    const float s = coef * (av - (b ? bv : 0.f));
+    v0 = s * v0;
+    v1 = s * v1;
+    v2 = s * v2;
+    if (res) {
+      const float t = coef * res[gi];
+      v0 = fmaf(t, central_diff(a, x0, x1, xc, N0, N1, N2, 0), v0);
+      v1 = fmaf(t, central_diff(a, x0, x1, xc, N0, N1, N2, 1), v1);
+      v2 = fmaf(t, central_diff(a, x0, x1, xc, N0, N1, N2, 2), v2);
     }
+    if (r >= rv || x2 >= N2) v0 = v1 = v2 = 0.f;
     float* at = vals + r * LV + x2;
     at[0] = v0;
     at[16 * LV] = v1;
     at[32 * LV] = v2;
   }
   __syncthreads();
-  fwd2_tile(vals, tw.fwd2, N2, Kh, 4, [&](int j, int r, int kh, float2 v) {
-    if (r < rv) s1[(unsigned)(((j * N0 + x0) * N1 + x1b + r) * Kh + kh)] = v;
+  fwd2_tile(vals, ws, N2, Kh, kSrcThreads / 64, [&](int j, int r, int e, float v) {
+    if (r < rv) reinterpret_cast<float*>(s1)[(unsigned)(((j * N0 + x0) * N1 + x1b + r) * 2 * Kh + e)] = v;
   });
 }
 
@@ -289,7 +304,7 @@ __global__ void __launch_bounds__(kAdjThreads, 4) k_adj_src_fwd2(const float* __
 // [+ coef res (h du)_j when res is set].  Then forward stage 2 of the three
 // sources like k_src_fwd2.
 template <class G>
-__global__ void __launch_bounds__(256) k_rho_fwd2(RhoArgs a, float2* __restrict__ s1, Twiddles tw, G gs) {
+__global__ void __launch_bounds__(kSrcThreads) k_rho_fwd2(RhoArgs a, float2* __restrict__ s1, Twiddles tw, G gs) {
   extern __shared__ float shs[];
   const int N0 = gs.N0(), N1 = gs.N1(), N2 = gs.N2(), Kh = gs.Kh();
   const long long nN = (long long)N0 * N1 * N2;
@@ -298,6 +313,8 @@ __global__ void __launch_bounds__(256) k_rho_fwd2(RhoArgs a, float2* __restrict_
   const int rv = min(16, N1 - x1b);
   const int LV = tile_ld(N2), L4 = (N2 + 3) & ~3;
   float* vals = shs;  // [3][16][LV]
+  float2* ws = reinterpret_cast<float2*>(shs + 48 * LV);
+  stage_fwd2(ws, tw.fwd2, N2, Kh);
   // two points per iteration, so that two chains of dependent loads are in flight
 #pragma unroll 2
   for (int p = threadIdx.x; p < 16 * L4; p += blockDim.x) {
@@ -363,8 +380,8 @@ __global__ void __launch_bounds__(256) k_rho_fwd2(RhoArgs a, float2* __restrict_
     at[32 * LV] = v2;
   }
   __syncthreads();
-  fwd2_tile(vals, tw.fwd2, N2, Kh, 4, [&](int j, int r, int kh, float2 v) {
-    if (r < rv) s1[(unsigned)(((j * N0 + x0) * N1 + x1b + r) * Kh + kh)] = v;
+  fwd2_tile(vals, ws, N2, Kh, kSrcThreads / 64, [&](int j, int r, int e, float v) {
+    if (r < rv) reinterpret_cast<float*>(s1)[(unsigned)(((j * N0 + x0) * N1 + x1b + r) * 2 * Kh + e)] = v;
   });
 }
 
@@ -498,8 +515,10 @@ __global__ void __launch_bounds__(64) k_fwd0(Fwd0Jobs jobs, const float2* __rest
   }
 }
 
-// LDS of a tile of fwd2_tile (at most 50 KB)
-size_t tile_bytes(const Dims& d) { return 48 * (size_t)tile_ld(d.N[2]) * sizeof(float); }
+// LDS of a tile of fwd2_tile and its table (at most 50 + 66 KB)
+size_t tile_bytes(const Dims& d) {
+  return 48 * (size_t)tile_ld(d.N[2]) * sizeof(float) + (size_t)d.Kh * row_ld(d.N[2]) * sizeof(float2);
+}
 
 }  // namespace
 
@@ -542,7 +561,7 @@ hipError_t launch_src_fwd2(const float* a, const float* b, const float* r, const
                (b ? 12.0 : 8.0) * nN + (r ? 4.0 : 0.0) * nN + 3.0 * d.N[0] * (double)d.N[1] * d.Kh * 8.0);
   }
   hipError_t e = with_grid(d, [&](auto gs) {
-    LAUNCH_TIMED(KF_SRC, (k_src_fwd2<decltype(gs)>), grid, dim3(256), shm, st, a, b, r, m, coef, s1, tw, gs);
+    LAUNCH_TIMED(KF_SRC, (k_src_fwd2<decltype(gs)>), grid, dim3(kSrcThreads), shm, st, a, b, r, m, coef, s1, tw, gs);
     return hipGetLastError();
   });
   return e;
@@ -585,7 +604,7 @@ hipError_t launch_rho_fwd2(const RhoArgs& a, float2* s1, const Dims& d, const Tw
                (nf + rd) * 4.0 * nN + 3.0 * d.N[0] * (double)d.N[1] * d.Kh * 8.0);
   }
   hipError_t e = with_grid(d, [&](auto gs) {
-    LAUNCH_TIMED(KF_SRC, (k_rho_fwd2<decltype(gs)>), grid, dim3(256), shm, st, a, s1, tw, gs);
+    LAUNCH_TIMED(KF_SRC, (k_rho_fwd2<decltype(gs)>), grid, dim3(kSrcThreads), shm, st, a, s1, tw, gs);
     return hipGetLastError();
   });
   return e;
