@@ -137,7 +137,9 @@ hipError_t launch_tables(const TableJobs& jobs, int njobs, hipStream_t st) {
 // loaded at once and used for both parts.
 // Bound by the matrix cores at large bands (band 64, M = 96: 768 products a
 // wave, 35 us of them in a launch, 85 MB stored): 324 us with the operands staged
-// through LDS one compute unit at a time, 86 us here; band 40: 41 -> 27 us.
+// through LDS one compute unit at a time, 73 us here (86 with an 8-byte load per
+// operand, whose 16-lane quarters touch 16 rows and take 64 cycles of the address
+// unit: now one 16-byte load for two k-steps); band 40: 41 -> 25 us.
 template <int KT, int KQ, bool BF3>
 __global__ void __launch_bounds__(256, BF3 ? 3 : 4) k_synth_chain(SynthArgs a, const float4* __restrict__ fr1,
                                                                   const float4* __restrict__ fr2, BandDyn sh) {
@@ -299,8 +301,9 @@ hipError_t launch_synth_chain(const SynthArgs& a, int nf, const Frags& fr, const
 // bands the launch is one chain of latencies: the update's values and the
 // first tables of a phase are loaded before the phase begins, and the registers
 // are kept under 128 so that two blocks share a compute unit (142: 85 us at band
-// 64).  Against scalar sums out of LDS: 243 -> 65 us at band 64, 34 -> 21 us at
-// band 40, 13.1 -> 11.4 us at band 24x20x20.
+// 64).  Against scalar sums out of LDS: 243 -> 47 us at band 64, 34 -> 19 us at
+// band 40, 13.1 -> 9.4 us at band 24x20x20 (with two loads for four k-steps of the
+// field 52, 20 and 10).
 template <int GC>       // groups of four k-steps per load; the next ones are in flight
 struct ColTab {         // a fragment table being walked: w holds groups j .. j + GC - 1
   const float4* p;

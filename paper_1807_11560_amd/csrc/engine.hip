@@ -1,10 +1,11 @@
 // Host engine of band-limited Jacobi PDE-EPDiff LDDMM (paper §3.2).
 //
-// Per Euler step on the padded grid the engine issues three launches: the
-// MFMA synthesis of the new fields (inverse stages 1-2; k_synth), their Lie
-// products with forward stage 2 (k_prods) and the column kernel (forward
-// stages 1-0, the band update, and stage 0 of the next step's inverse
-// transforms; k_colstep).  The first step of a sweep gets its stage 0 from k_inv0.
+// Per Euler step on the padded grid the engine issues two launches for small
+// bands, k_step (inverse stages 1-2 of the new fields, their Lie products,
+// forward stage 2) and the column kernel (forward stages 1-0, the band update,
+// and stage 0 of the next step's inverse transforms), or three for large ones,
+// k_synth_chain and k_prods in place of k_step.  The first step of a sweep gets
+// its stage 0 from k_inv0 or from the column kernel without products.
 // Fields of the trajectory that later sweeps reuse are cached on the padded
 // grid when they are first synthesised.
 #include "engine.h"

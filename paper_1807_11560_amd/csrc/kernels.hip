@@ -206,7 +206,10 @@ __global__ void __launch_bounds__(128) k_inv0(Inv0Jobs jobs, const float2* __res
 // the new and cached groups, forms the products of the program and
 // contracts them over x2 (forward stage 2) into s1[o][kh][x0][x1]: on the
 // matrix cores when M2 % 4 == 0 (rows (o, r) x columns (kh re | kh im), depth
-// x2), else one thread per output.
+// x2), else one thread per output.  For the steps that k_step does not take and
+// the products at t = 1 of the deformation state.  Bound by its groups' bytes
+// (band 64, M = 96: 340 MB in the coupled sweep, 67 us at the copy rate): 90 us
+// with the stage-2 table read across its rows, 78 along them.
 template <bool BF3>
 __global__ void __launch_bounds__(256) k_prods(ProdArgs a, Twiddles tw, BandDyn sh, int R) {
   // R: padded-grid rows of this block (R M2 <= blockDim.x rounded to waves)
