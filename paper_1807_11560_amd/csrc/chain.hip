@@ -65,14 +65,18 @@ __global__ void k_tables(TableJobs jobs) {
         static_cast<float2*>(j.dst)[i] = forward_entry(i / G, K, i % G, G, j.kind == TAB_FWD_HALF);
         break;
       case TAB_ROW_INV:
-      case TAB_ROW_INV_HALF: {
+      case TAB_ROW_INV_HALF:
+      case TAB_ROW_INV_POS:
+      case TAB_ROW_INV_HALF_POS: {
         const int KT = (K + 15) / 16, GT = (G + 15) / 16;
         const int lane = (i >> 2) & 63, rest = i >> 8;
         const int q = 16 * (rest % KT) + 4 * (i & 3) + (lane >> 4), part = (rest / KT) % 2;
         const int x = 16 * ((rest / (2 * KT)) % GT) + (lane & 15);
         float2 w = make_float2(0.f, 0.f);
-        if (q < K && x < G) w = inverse_entry(q, K, x, G, rest / (2 * KT * GT), j.kind == TAB_ROW_INV_HALF);
-        static_cast<float*>(j.dst)[i] = part ? -w.y : w.x;
+        if (q < K && x < G) w = inverse_entry(q, K, x, G, rest / (2 * KT * GT),
+                                              j.kind == TAB_ROW_INV_HALF || j.kind == TAB_ROW_INV_HALF_POS);
+        const bool neg = j.kind == TAB_ROW_INV || j.kind == TAB_ROW_INV_HALF;
+        static_cast<float*>(j.dst)[i] = part ? (neg ? -w.y : w.y) : w.x;
         break;
       }
       case TAB_PAIR_INV:
@@ -632,8 +636,8 @@ __global__ void __launch_bounds__(256, 4) k_gridstep(GridStepArgs a, const float
           s3 = O::mma_t(tr, wi, s3);
         }
       }
-      re = s0 + s1;  // wi holds -im w
-      im = s2 - s3;
+      re = s0 - s1;
+      im = s2 + s3;
     } else {
       re = im = zero4();
       for (int j0 = 0; j0 < J1; j0 += 4) {
@@ -706,7 +710,7 @@ __global__ void __launch_bounds__(256, 4) k_gridstep(GridStepArgs a, const float
             acc[c][1] = product(elem(w[kt][1], u), t[16], acc[c][1]);
           }
 #pragma unroll
-      for (int c = 0; c < 3; ++c) vel[c] = acc[c][0] + acc[c][1];
+      for (int c = 0; c < 3; ++c) vel[c] = acc[c][0] - acc[c][1];
     } else {
 #pragma unroll
       for (int c = 0; c < 3; ++c) vel[c] = zero4();

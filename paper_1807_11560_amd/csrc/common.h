@@ -46,6 +46,7 @@ enum TableKind {
   TAB_INV = 0, TAB_FWD = 2, TAB_FWD_HALF = 3,  // plain
   TAB_ROW_INV = 4, TAB_ROW_INV_HALF = 5,                         // fragment order, see mfma.h
   TAB_PAIR_INV = 6, TAB_PAIR_INV_HALF = 7, TAB_PAIR_FWD = 8,
+  TAB_ROW_INV_POS = 9, TAB_ROW_INV_HALF_POS = 10,               // as ROW_INV, with im w in part 1
   TAB_COL1 = 11, TAB_COL0 = 12, TAB_COL0_INV = 13,  // instantiated shapes
   TAB_SYMBOLS = 14,                                              // L~ to dst, K~ to dst2 (K = K0, G = K1)
   TAB_ZERO = 15                                                  // unsigned zeros

@@ -282,8 +282,8 @@ hipError_t Engine::init_tables() {
     add(frN_.inv0, TAB_PAIR_INV, K[0], d_.N[0], 2 * pair_inv(K[0], d_.N[0]));
   }
   if (grid_instantiated(d_)) {
-    add(frN_.row1, TAB_ROW_INV, K[1], d_.N[1], 2 * row_inv(K[1], d_.N[1]));
-    add(frN_.row2, TAB_ROW_INV_HALF, d_.Kh, d_.N[2], 2 * row_inv(d_.Kh, d_.N[2]));
+    add(frN_.row1, TAB_ROW_INV_POS, K[1], d_.N[1], 2 * row_inv(K[1], d_.N[1]));
+    add(frN_.row2, TAB_ROW_INV_HALF_POS, d_.Kh, d_.N[2], 2 * row_inv(d_.Kh, d_.N[2]));
   } else {
     add(frN_.inv1, TAB_PAIR_INV, K[1], d_.N[1], 2 * pair_inv(K[1], d_.N[1]));
     add(frN_.inv2, TAB_PAIR_INV_HALF, d_.Kh, d_.N[2], 2 * pair_inv(d_.Kh, d_.N[2]));

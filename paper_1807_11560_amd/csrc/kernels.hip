@@ -969,8 +969,7 @@ __global__ void __launch_bounds__(256, BF3 && G::N2() > 128 ? 3 : 4) k_gridstep_
     for (int g = 0; g < KT; ++g)
 #pragma unroll
       for (int p = 0; p < 2; ++p) w2[q][g][p] = (f2 + ((min(wave + 4 * q, NTJ - 1) * 2 + p) * KT + g) * 64)[lane];
-  // stage 1: one 16 x Kh complex tile per component (waves 0..2 when Kh = 16);
-  // the tables' second part is -im
+  // stage 1: one 16 x Kh complex tile per component (waves 0..2 when Kh = 16)
   for (int jb = wave; jb < 3 * (Khp / 16); jb += 4) {
     const int c = jb % 3, tj = jb / 3;
     floatx4 acc[4];
@@ -988,7 +987,7 @@ __global__ void __launch_bounds__(256, BF3 && G::N2() > 128 ? 3 : 4) k_gridstep_
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      t2s[c][4 * lk + r][tj * 16 + li] = make_float2(acc[0][r] + acc[1][r], acc[2][r] - acc[3][r]);
+      t2s[c][4 * lk + r][tj * 16 + li] = make_float2(acc[0][r] - acc[1][r], acc[2][r] + acc[3][r]);
   }
   __syncthreads();
   // stage 2 + epilogue: a wave takes whole column tiles (all components)
@@ -1002,7 +1001,7 @@ __global__ void __launch_bounds__(256, BF3 && G::N2() > 128 ? 3 : 4) k_gridstep_
     for (int c = 0; c < 3; ++c) {
       floatx4 acc[4];
       zero_acc(acc, 4);
-      // only the real part is needed
+      // only the real part is needed: acc0 - acc1
       const float2* A = &t2s[c][0][0] + li * LT2 + lk;
 #pragma unroll
       for (int ks = 0; ks < Khp / 4; ++ks) {
@@ -1010,7 +1009,7 @@ __global__ void __launch_bounds__(256, BF3 && G::N2() > 128 ? 3 : 4) k_gridstep_
         acc[0] = mma<BF3>(av.x, elem(w2[q][ks / 4][0], ks % 4), acc[0]);
         acc[1] = mma<BF3>(av.y, elem(w2[q][ks / 4][1], ks % 4), acc[1]);
       }
-      vel[c] = acc[0] + acc[1];
+      vel[c] = acc[0] - acc[1];
     }
     const int x2 = tj * 16 + li;
 #pragma unroll

@@ -100,6 +100,10 @@ __device__ __forceinline__ floatx4 zero4() { return floatx4{0.f, 0.f, 0.f, 0.f};
 //   ROW_INV   [v][x tile][part][k tile][64] float4: re w (part 0) or -im w of
 //             u = 0 .. 3; v = 1: w times 2 pi i k; the half form runs over
 //             k = 0 .. Kh - 1 with weight 1 at k = 0, else 2
+//   ROW_INV_POS  the same with im w in part 1, for kernels that form the parts
+//             apart and subtract: v_mfma_f32_16x16x16_bf16 does not round x and -x
+//             alike, so the sign a table holds decides the last bits of the
+//             compensated products (FP32 sums are the same either way)
 //   PAIR_INV  [v][x tile][ks / 4][64] float4: this lane's part of w (re or im)
 //             for four k-steps; the half form (real output) holds re and -im
 //   PAIR_FWD  [k tile][ks / 4][64] float4: the same with x = 2 ks + lk / 2
