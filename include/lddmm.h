@@ -199,15 +199,17 @@ int lddmm_shoot(const lddmm_params* p, const float* I0, const void* v0, float* m
 /* lddmm_shoot without a workspace argument, for callers that cannot allocate
  * device memory (code under stream capture, tight serving loops, harnesses
  * that forbid allocation): the same computation, arguments and outputs as
- * lddmm_shoot, working in LDDMM_STATIC_SCRATCH_BYTES of device memory that
- * the library holds as a fixed array, one copy per GPU, from its first use
- * on that GPU until the process ends (problems whose lddmm_workspace_bytes
- * exceeds that size, e.g. beyond 64^3 / band 16^3 / 10 steps, return
- * LDDMM_E_WORKSPACE before anything is enqueued).  It allocates nothing and
- * creates no stream or event: all work is enqueued on `stream`.  Every call
- * on one GPU uses that GPU's array and leaves its contents behind; nothing
- * in it needs to start at zero, and calls that overlap on one GPU (from
- * several host threads or streams) race. */
+ * lddmm_shoot, working in LDDMM_STATIC_SCRATCH_BYTES of device memory (and
+ * room for table padding) that the library holds as a fixed array, one copy
+ * per GPU, from its first use on that GPU until the process ends (problems
+ * whose lddmm_workspace_bytes exceeds that size, e.g. beyond 64^3 / band
+ * 16^3 / 10 steps, return LDDMM_E_WORKSPACE before anything is enqueued;
+ * padding of the transform tables, up to 160 KiB of lddmm_workspace_bytes
+ * where an axis has very few band frequencies, is not counted).  It
+ * allocates nothing and creates no stream or event: all work is enqueued on
+ * `stream`.  Every call on one GPU uses that GPU's array and leaves its
+ * contents behind; nothing in it needs to start at zero, and calls that
+ * overlap on one GPU (from several host threads or streams) race. */
 int lddmm_shoot_static(const lddmm_params* p, const float* I0, const void* v0, float* m1, void* v1,
                        void* stream);
 

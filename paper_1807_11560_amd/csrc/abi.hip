@@ -372,9 +372,11 @@ int euler_only(const Dims& d) {
 // and kept.  Every lddmm_shoot_static call on one GPU uses that GPU's copy,
 // so such calls that overlap on one GPU race.
 // Above the documented size it holds what fragment tables of few k take more
-// than plain ones (35 KB at the most), so that the documented size decides
-// what is taken.
-constexpr size_t kScratchSlack = 64 << 10;
+// than plain ones, so that the documented size decides what is taken: at most
+// 59280 + 58976 + 33728 bytes of the three axes over all sizes that validate()
+// accepts (band, padded and image size 34, 241, 34 on the first axis, 4, 249, 385
+// on the second, 8, 241, 241 on the third), and less than 256 of alignment.
+constexpr size_t kScratchSlack = 160 << 10;
 static __device__ __align__(256) unsigned char scratch[LDDMM_STATIC_SCRATCH_BYTES + kScratchSlack];
 std::mutex g_scratch_mu;
 std::map<int, void*> g_scratch_ptr;  // device -> its copy of scratch
@@ -1106,7 +1108,7 @@ int lddmm_shoot_static(const lddmm_params* p, const float* I0, const void* v0, f
   if ((rc = no_checkpoint(d))) return rc;
   if (!I0 || !v0 || !m1) return fail(LDDMM_E_INVALID_ARG, "null input or output");
   const size_t need = Engine::workspace_bytes(d);
-  if (need - std::min(Engine::table_surplus(d), kScratchSlack) > LDDMM_STATIC_SCRATCH_BYTES)
+  if (need - Engine::table_surplus(d) > LDDMM_STATIC_SCRATCH_BYTES || need > sizeof(scratch))
     return fail(LDDMM_E_WORKSPACE, "problem needs " + std::to_string(need) + " bytes of workspace, more than the " +
                                        std::to_string((size_t)LDDMM_STATIC_SCRATCH_BYTES) +
                                        " of lddmm_shoot_static; use lddmm_shoot with a caller workspace");

@@ -32,7 +32,7 @@ class Engine {
  public:
   Engine(const Dims& d, void* ws, hipStream_t st);
   static size_t workspace_bytes(const Dims& d);
-  // What the fragment tables take of that above the plain tables' room.
+  // What the fragment tables take of that above the plain tables' room (bytes).
   static size_t table_surplus(const Dims& d);
 
   hipError_t init_tables();

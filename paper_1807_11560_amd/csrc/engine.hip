@@ -150,10 +150,9 @@ void Engine::layout(Carver& c) {
   Lsym = c.take<float>((size_t)d.nb);
   Ksym = c.take<float>((size_t)d.nb);
   {
-    // One region for the tables: those of the instantiated shapes, or the
-    // fragment tables in their place.  Never smaller than the former, so that
-    // the workspace of a problem does not depend on which kernels serve it;
-    // larger by up to table_surplus where few k1 or k2 fill a 16-row fragment.
+    // One region for the tables that the problem's kernels read.  Never smaller
+    // than the plain tables it replaced, so that a workspace keeps its size; larger,
+    // by table_surplus, where few k leave a fragment of 16 mostly padding.
     auto tables = [&](Carver& r, bool inst) {
       twbuf_ = r.take<float2>((inst ? 2 * ((size_t)d.M[0] + d.N[0]) * d.K[0] : 0) +
                               (size_t)d.K[0] * d.N[0] + (size_t)d.K[1] * d.N[1] +
@@ -167,7 +166,8 @@ void Engine::layout(Carver& c) {
     a.take<float2>(col_table_count(d));
     tables(b, band_instantiated(d));
     Carver r{c.take<char>(std::max(a.off, b.off))};
-    table_surplus_ = b.off > a.off ? b.off - a.off : 0;
+    auto aligned = [](size_t n) { return (n + 255) & ~(size_t)255; };  // of the buffer that follows
+    table_surplus_ = b.off > a.off ? aligned(b.off) - aligned(a.off) : 0;
     tables(r, band_instantiated(d));
   }
   const size_t C = (size_t)d.K[1] * d.Kh;
