@@ -462,7 +462,8 @@ int lddmm_tiles_load(const char* path);
  * (leaving ws prepared for lddmm_hessvec, as lddmm_gradient does), then times
  * `reps` products (direction v0, after one untimed product) for the built-in
  * rule and for each candidate of one field at a time (sl_threads 64, 128;
- * prod_rows 1 .. max - 1; col_split 1, 2, 3), keeping a candidate when it is
+ * prod_rows 1 .. max - 1 where it has an effect on the product; col_split
+ * 1, 2, 3), keeping a candidate when it is
  * at least 1 % faster than the choice so far.  The winner is stored in the
  * table for p's shape on the current device and returned in *best, its time
  * per product (ms) in *ms_best and the built-in rule's in *ms_default (each

@@ -1835,7 +1835,10 @@ int lddmm_autotune(const lddmm_params* p, const float* I0, const float* I1, cons
     t.sl_threads = th;
     trial(t);
   }
-  for (int r = 1; r < prod_rows_max(d); ++r) {
+  // only where a product launches k_prods: in the sweeps that k_step does not
+  // serve, and at t = 1 of the deformation state
+  const bool prods = !step_fused(d) || d.state != LDDMM_STATE_IMAGE;
+  for (int r = 1; prods && r < prod_rows_max(d); ++r) {
     lddmm_tiles t = cur;
     t.prod_rows = r;
     trial(t);
