@@ -318,13 +318,13 @@ int validate(const lddmm_params* p, Dims* d) {
     if (K < 4 || K > kMaxBand || (K & 1) || K > N)
       return fail(LDDMM_E_SHAPE, "band sizes must be even, in [4, 64] and at most the grid size");
     const int M = p->spectral[j] ? p->spectral[j] : 3 * K / 2;
-    if (M < 3 * K / 2 - 2 || M > 256)
+    if (M < 3 * K / 2 - 2 || M > kMaxPadded)
       return fail(LDDMM_E_SHAPE, "spectral grid must satisfy 3K/2 - 2 <= M <= 256");
     o.N[j] = N;
     o.K[j] = K;
     o.M[j] = M;
   }
-  if (o.N[2] > 256) return fail(LDDMM_E_SHAPE, "the last grid axis must be at most 256");
+  if (o.N[2] > kMaxRow) return fail(LDDMM_E_SHAPE, "the last grid axis must be at most 256");
   o.Kh = o.K[2] / 2;
   o.nb = o.K[0] * o.K[1] * o.Kh;
   o.nN = (long long)o.N[0] * o.N[1] * o.N[2];
@@ -342,11 +342,7 @@ int validate(const lddmm_params* p, Dims* d) {
   if (p->checkpoint > 0 && (p->state != LDDMM_STATE_IMAGE || p->integrator != LDDMM_EULER))
     return fail(LDDMM_E_INVALID_ARG, "checkpoints need the image state and Euler steps");
   o.ckpt = p->checkpoint;
-  // each block keeps its tile in LDS (at most the 160 KiB of a gfx950 workgroup)
-  if (synth_shared_bytes(o) > kMaxLds || prods_shared_bytes(o, 9) > kMaxLds || colstep_shared_bytes(o) > kMaxLds)
-    return fail(LDDMM_E_SHAPE, "band/padded grid too large for the step kernel's LDS tile");
-  if (gridstep_shared_bytes(o) > kMaxLds || src_shared_bytes(o) > kMaxLds)
-    return fail(LDDMM_E_SHAPE, "grid rows too long for the grid kernels' LDS tile");
+  if (!band_sizes_taken(o)) return fail(LDDMM_E_SHAPE, "band and padded grid too large together");
   apply_tiles(o);
   return LDDMM_OK;
 }

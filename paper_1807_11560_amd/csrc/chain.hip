@@ -523,6 +523,7 @@ hipError_t launch_column_chain(const ColJobs& jobs, int njobs, const Dims& d, co
     if ((!jobs.j[i].a && (!jobs.j[i].base || jobs.j[i].b)) || (jobs.j[i].a && !jobs.j[i].out)) return hipErrorInvalidValue;
   const int M0p = 16 * tiles16(d.M[0]), K0p = 16 * tiles16(d.K[0]);
   const size_t shm = (size_t)(2 * M0p + 2 * K0p) * 16 * sizeof(float2);
+  static_assert((2 * kMaxPadded + 2 * kMaxBand) * 16 * sizeof(float2) <= kMaxLds);
   const dim3 grid(d.Kh, njobs, tiles16(d.K[1]));
   const BandDyn sh{d.K[0], d.K[1], d.Kh, d.M[0], d.M[1], d.M[2]};
   LAUNCH_TIMED(column_family(jobs), (k_column_chain<8>), grid, dim3(512), shm, st, jobs, frM, frN, Lsym, Ksym, sh, invG);

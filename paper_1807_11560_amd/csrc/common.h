@@ -9,6 +9,8 @@
 namespace lddmm {
 
 constexpr int kMaxBand = 64;   // K_j upper bound
+constexpr int kMaxPadded = 256;  // M_j
+constexpr int kMaxRow = 256;     // N_2
 constexpr size_t kMaxLds = 160 * 1024;  // LDS of one workgroup on gfx950
 constexpr int kMaxJobs = 32;   // jobs per batched launch
 
@@ -36,6 +38,10 @@ struct Dims {
   int tile_col;        // column step: 1 one block per column tile, 2 two (general kernel), 3 two (lean kernel where it applies)
   int tile_sl;         // threads per block of k_sl (64, 128 or 256)
 };
+
+// Whether the library takes the band with its padded grid (host only; K and M
+// within their own ranges).
+bool band_sizes_taken(const Dims& d);
 
 // Valid range of the tile fields for a shape (host only).
 int prod_rows_max(const Dims& d);
@@ -216,7 +222,6 @@ hipError_t launch_inv0(const Inv0Jobs& jobs, int njobs, int nvar, const float2* 
 // Table jobs of the instantiated shapes' column step; returns their number.
 int col_table_jobs(TableJob* j, float2* tab, const Dims& d);
 size_t synth_table_floats(const Dims& d);
-size_t synth_shared_bytes(const Dims& d);
 // Synthesis of group 0 and, when t1g1 is set, group 1.
 hipError_t launch_synth(const float2* t1g0, const float2* t1g1, float* dst0, float* dst1,
                         const Frags& fr, const Dims& d, hipStream_t st);
@@ -228,7 +233,6 @@ hipError_t launch_column_chain(const ColJobs& jobs, int njobs, const Dims& d, co
 bool step_fused(const Dims& d);
 hipError_t launch_step(int prog, const StepArgs& a, const Frags& fr, const Twiddles& tw, const Dims& d,
                        hipStream_t st);
-size_t prods_shared_bytes(const Dims& d, int nout);
 hipError_t launch_prods(const ProdArgs& a, const Dims& d, const Twiddles& tw, hipStream_t st);
 hipError_t launch_colstep(const ColJobs& jobs, int njobs, const Dims& d, const Twiddles& tw,
                           const float2* coltab, const Frags& frM, const Frags& frN, const float* Lsym,
@@ -236,7 +240,6 @@ hipError_t launch_colstep(const ColJobs& jobs, int njobs, const Dims& d, const T
 size_t col_table_count(const Dims& d);
 // Whether the column kernel can form the image-grid stage 0 (t1n) for this shape.
 bool colstep_fuses_grid0(const Dims& d);
-size_t colstep_shared_bytes(const Dims& d);
 hipError_t launch_fwd1(const Fwd1Jobs& jobs, int njobs, const float2* tw, int G0, int G1, int K1,
                        int Kh, hipStream_t st);
 hipError_t launch_fwd0(const Fwd0Jobs& jobs, int njobs, const float2* tw, const float* Ksym, int G0,
@@ -319,8 +322,6 @@ hipError_t launch_band_maxabs(const float2* a, const Dims& d, double* partial, d
                               hipStream_t st);
 hipError_t launch_scalar_copy(const double* src, double* dst, int n, hipStream_t st);
 hipError_t launch_energy_combine(double* sc, hipStream_t st);  // sc[0] = sc[1] + sc[2]
-size_t gridstep_shared_bytes(const Dims& d);
-size_t src_shared_bytes(const Dims& d);
 // CG in the V metric, all scalars on the device (see engine).
 hipError_t launch_pcg_reset(double* sc, hipStream_t st);
 hipError_t launch_pcg_init(const float2* g, float2* p, float2* r, float2* dvec, int n,

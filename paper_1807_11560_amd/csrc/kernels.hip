@@ -1713,15 +1713,6 @@ size_t synth_table_floats(const Dims& d) {
   return 2 * (size_t)M1p * 2 * d.K[1] + 2 * 2 * (size_t)Khp * M2p;
 }
 
-size_t synth_shared_bytes(const Dims& d) {
-  int M1p, M2p, Khp;
-  synth_padding(d, &M1p, &M2p, &Khp);
-  const int K2r = 2 * d.K[1], N1 = 2 * Khp;
-  const int ldbT = K2r + 2, ldw2 = (M2p % 32 == 0) ? M2p + 16 : M2p;
-  return (2 * 16 * (size_t)(K2r + 2) + 2 * (size_t)N1 * (ldbT > ldw2 ? ldbT : ldw2) + 3 * 16 * (size_t)(N1 + 2)) *
-         sizeof(float);
-}
-
 hipError_t launch_synth(const float2* t1g0, const float2* t1g1, float* dst0, float* dst1, const Frags& fr,
                         const Dims& d, hipStream_t st) {
   SynthArgs a{};
@@ -1748,16 +1739,13 @@ static int prod_rows(const Dims& d) {
   return (d.tile_prod_rows > 0 && d.tile_prod_rows < R) ? d.tile_prod_rows : R;
 }
 
-// Limit on the problem sizes (validated at the boundary).
-size_t prods_shared_bytes(const Dims& d, int nout) {
-  return (size_t)d.M[2] * d.Kh * sizeof(float2) + (size_t)nout * prod_rows(d) * (d.M[2] + 2) * sizeof(float);
-}
-
 hipError_t launch_prods(const ProdArgs& a, const Dims& d, const Twiddles& tw, hipStream_t st) {
   const int R = prod_rows(d);
   dim3 grid(nblk(d.M[1], R), d.M[0]);
   const size_t shm = (size_t)d.Kh * row_ld(d.M[2]) * sizeof(float2) +
                      (size_t)a.nout * R * (d.M[2] + 2) * sizeof(float);
+  // R M2 <= 256 or R = 1, and R <= 64
+  static_assert(kMaxBand / 2 * row_ld(kMaxPadded) * sizeof(float2) + 9 * (256 + 2 * 64) * sizeof(float) <= kMaxLds);
   {
     static const double prog_flops[11] = {0, 47, 94, 136, 272, 136, 18, 36, 18, 36, 89};
     static const int prog_fields[11] = {0, 24, 48, 48, 96, 48, 12, 24, 12, 24, 36};
@@ -1774,16 +1762,6 @@ hipError_t launch_prods(const ProdArgs& a, const Dims& d, const Twiddles& tw, hi
   else
     LAUNCH_TIMED(KF_PRODS, k_prods<false>, grid, dim3(threads), shm, st, a, tw, sh, R);
   return hipGetLastError();
-}
-
-// Limit on the problem sizes (validated at the boundary): the LDS tile of a
-// column step with one product slice and, where they fit too, its tables.
-size_t colstep_shared_bytes(const Dims& d) {
-  const int M0 = d.M[0], M1 = d.M[1], K0 = d.K[0], G = 8;
-  const size_t rest = (size_t)G * M1 + 2 * (size_t)M0 * G + (size_t)K0 * M0 + 2 * (size_t)K0 * G;
-  const size_t staged = (size_t)std::max(M0 * M1, 2 * M0 * K0);
-  const size_t with_table = (staged + rest) * sizeof(float2);
-  return with_table <= kMaxLds ? with_table : ((size_t)M0 * M1 + rest) * sizeof(float2);
 }
 
 size_t col_table_count(const Dims& d) {
@@ -1922,17 +1900,18 @@ hipError_t launch_colstep(const ColJobs& jobs, int njobs, const Dims& d, const T
   return e;
 }
 
-// Limits on the problem sizes (validated at the boundary): the LDS tiles of a
-// grid step with all its tables, and of the image-term sources.
-size_t gridstep_shared_bytes(const Dims& d) {
-  const int C = d.K[1] * d.Kh;
-  return (3 * (size_t)C + 3 * (size_t)kGridRows * d.Kh + (size_t)kGridRows * d.K[1] +
-          (size_t)d.N[2] * d.Kh) * sizeof(float2);
-}
-
-size_t src_shared_bytes(const Dims& d) {
-  return (size_t)((3 * kGridRows * d.N[2] + 3) & ~3) * sizeof(float) +
-         (size_t)d.Kh * d.N[2] * sizeof(float2);
+// The bands and padded grids that are taken: those whose tiles in the LDS-staged
+// form of the synthesis and of the column step fit a compute unit.  The kernels here
+// keep less in LDS (each launch states the most), so the rule binds none of
+// them: it stands so that what is refused does not change.
+bool band_sizes_taken(const Dims& d) {
+  const size_t M0 = d.M[0], M1 = d.M[1], K0 = d.K[0], K1 = d.K[1];
+  int M1p, M2p, Khp;
+  synth_padding(d, &M1p, &M2p, &Khp);
+  const size_t row1 = 2 * K1 + 2, row2 = (M2p % 32 == 0) ? M2p + 16 : M2p, n1 = 2 * Khp;
+  const size_t synth = (32 * row1 + 2 * n1 * std::max(row1, row2) + 48 * (n1 + 2)) * sizeof(float);
+  const size_t column = (M0 * M1 + 8 * M1 + 16 * M0 + K0 * M0 + 16 * K0) * sizeof(float2);
+  return synth <= kMaxLds && column <= kMaxLds;
 }
 
 hipError_t launch_gridstep(const GridStepArgs& a, const Dims& d, const Frags& fr, hipStream_t st) {

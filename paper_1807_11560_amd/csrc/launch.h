@@ -22,5 +22,5 @@
 
 namespace lddmm {
 inline unsigned nblk(long long n, int t) { return (unsigned)((n + t - 1) / t); }
-inline int tiles16(int n) { return (n + 15) / 16; }
+constexpr int tiles16(int n) { return (n + 15) / 16; }
 }  // namespace lddmm

@@ -73,14 +73,6 @@ inline bool band_iso(const Dims& d, int K, int M) {
 inline bool band_instantiated(const Dims& d) {
   return band_iso(d, 32, 48) || band_iso(d, 16, 24) || band_iso(d, 24, 36);
 }
-// Calls f with the band shape type for these sizes.
-template <class F>
-hipError_t with_band(const Dims& d, F&& f) {
-  if (band_iso(d, 32, 48)) return f(BandIso<32, 48>{});
-  if (band_iso(d, 16, 24)) return f(BandIso<16, 24>{});
-  if (band_iso(d, 24, 36)) return f(BandIso<24, 36>{});
-  return f(BandDyn{d.K[0], d.K[1], d.Kh, d.M[0], d.M[1], d.M[2]});
-}
 inline bool grid_iso(const Dims& d, int N, int K) {
   return d.N[0] == N && d.N[1] == N && d.N[2] == N && d.K[1] == K && d.K[2] == K;
 }

@@ -516,9 +516,17 @@ __global__ void __launch_bounds__(64) k_fwd0(Fwd0Jobs jobs, const float2* __rest
 }
 
 // LDS of a tile of fwd2_tile and its table (at most 50 + 66 KB)
-size_t tile_bytes(const Dims& d) {
-  return 48 * (size_t)tile_ld(d.N[2]) * sizeof(float) + (size_t)d.Kh * row_ld(d.N[2]) * sizeof(float2);
+constexpr size_t tile_bytes(int N2, int Kh) {
+  return 48 * (size_t)tile_ld(N2) * sizeof(float) + (size_t)Kh * row_ld(N2) * sizeof(float2);
 }
+static_assert(tile_bytes(kMaxRow, kMaxBand / 2) <= kMaxLds);
+
+// LDS of a brick of k_adj_src_fwd2 in chunks of CW columns (at most 67 KB, so that
+// two fit a compute unit)
+constexpr size_t adj_bytes(int CW) {
+  return 96 * (size_t)(CW + 2) * sizeof(float) + (size_t)kAdjW0 * kAdjW1 * (CW + 3) * sizeof(double);
+}
+static_assert(2 * adj_bytes(kAdjCols) <= kMaxLds);
 
 }  // namespace
 
@@ -553,7 +561,7 @@ hipError_t launch_fwd0(const Fwd0Jobs& jobs, int njobs, const float2* tw, const 
 hipError_t launch_src_fwd2(const float* a, const float* b, const float* r, const float* m, float coef,
                            float2* s1, const Dims& d, const Twiddles& tw, hipStream_t st) {
   const dim3 grid(tiles16(d.N[1]), d.N[0]);
-  const size_t shm = tile_bytes(d);
+  const size_t shm = tile_bytes(d.N[2], d.Kh);
   {
     // gradient of m (6 flops / point / axis), the source, forward stage 2 of 3 fields
     const double nN = (double)d.nN;
@@ -571,7 +579,7 @@ hipError_t launch_adj_src_fwd2(const float* lam, const float* m, const float* ve
                                float dt, float2* s1, const Dims& d, const Twiddles& tw, hipStream_t st) {
   const dim3 grid(nblk(d.N[1], kAdjRows), nblk(d.N[0], kAdjPlanes));
   const int CW = adj_cols(d.N[2]);
-  const size_t shm = 96 * (size_t)(CW + 2) * sizeof(float) + (size_t)kAdjW0 * kAdjW1 * (CW + 3) * sizeof(double);
+  const size_t shm = adj_bytes(CW);
   {
     // departure point, 8 gathers, slopes, 8 scattered weights, forward stage 2 of 3 fields
     const double nN = (double)d.nN;
@@ -592,7 +600,7 @@ hipError_t launch_adj_src_fwd2(const float* lam, const float* m, const float* ve
 
 hipError_t launch_rho_fwd2(const RhoArgs& a, float2* s1, const Dims& d, const Twiddles& tw, hipStream_t st) {
   const dim3 grid(tiles16(d.N[1]), d.N[0]);
-  const size_t shm = tile_bytes(d);
+  const size_t shm = tile_bytes(d.N[2], d.Kh);
   {
     // trilinear interpolation of 4 (op 0), 3 or 9 (op 1) fields, the source,
     // forward stage 2 of 3 fields; point reads u (3) and I1 | du (3), res

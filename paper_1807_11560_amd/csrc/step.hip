@@ -280,6 +280,13 @@ __global__ void __launch_bounds__(768) k_step(StepArgs a, const float4* __restri
   }
 }
 
+// LDS of a block: T2 or the products, the fields, the table of forward stage 2.
+constexpr size_t step_bytes(int nf, int nout, int K1, int Kh, int M2) {
+  const int L4 = (M2 + 3) & ~3, LV = 4 * ((L4 / 4) | 1), LF = 16 * tiles16(M2) + 4;
+  return ((size_t)std::max(nf * 6 * 64 * 4, nout * 16 * LV) + 2 * (size_t)nf * 2 * 16 * std::max(LF, row_ld(K1)) +
+          2 * (size_t)Kh * row_ld(M2)) * sizeof(float);
+}
+
 template <int PROG>
 hipError_t launch_prog(const StepArgs& a, const Frags& fr, const float2* fwd2, const Dims& d, hipStream_t st) {
   constexpr int NF = step_fields(PROG), NOUT = step_outs(PROG);
@@ -287,9 +294,9 @@ hipError_t launch_prog(const StepArgs& a, const Frags& fr, const float2* fwd2, c
     if (!a.cached[k]) return hipErrorInvalidValue;
   if (!a.t1[0] || (NF == 6 && !a.t1[1]) || !a.s1) return hipErrorInvalidValue;
   const BandDyn sh{d.K[0], d.K[1], d.Kh, d.M[0], d.M[1], d.M[2]};
-  const int L4 = (d.M[2] + 3) & ~3, LV = 4 * ((L4 / 4) | 1), LF = 16 * tiles16(d.M[2]) + 4;
-  const size_t shm = ((size_t)std::max(NF * 6 * 64 * 4, NOUT * 16 * LV) + 2 * (size_t)NF * 2 * 16 * std::max(LF, row_ld(d.K[1])) +
-                      2 * (size_t)d.Kh * row_ld(d.M[2])) * sizeof(float);
+  const size_t shm = step_bytes(NF, NOUT, d.K[1], d.Kh, d.M[2]);
+  static_assert(step_bytes(NF, NOUT, 32, 16, kStepM2) <= kMaxLds);
+  const int L4 = (d.M[2] + 3) & ~3;
   const dim3 grid(tiles16(d.M[1]), d.M[0]), block(64 * std::max(2 * NF, (16 * L4 + 63) / 64));
   auto go = [&](auto kq, auto bf) {
     constexpr int KQ = decltype(kq)::value;
