@@ -91,44 +91,42 @@ def roofline(fam, name, launches, ms, flops, nbytes, traffic):
                  "unit": "TFLOP/s", "frac": f_cmp, "traffic": traffic, "gbs": gbs}, **common)
 
 
-def stored_traffic(kernel_name):
-    """HBM bytes per launch of `kernel_name` from the committed rocprofv3 PMC
-    summary (FETCH_SIZE + WRITE_SIZE scaled by the copy-kernel calibration),
-    or None if there is none or the kernel source changed since."""
+def stored_value(path, what, kernel_name, csrc=os.path.join(ROOT, "paper_1807_11560_amd", "csrc")):
+    """The value of a line "| what | kernel | value | digest |" of a committed
+    profile, or None if there is none or the kernel's source changed since.
+    The digest is that of kernels.hip, or with "what of FILE [FILE ...]" that
+    of these files of csrc, one after the other."""
     import hashlib
-    path = os.path.join(ROOT, "profiles", "traffic.md")
-    src = os.path.join(ROOT, "paper_1807_11560_amd", "csrc", "kernels.hip")
     if not os.path.exists(path):
         return None
-    digest = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
     for line in open(path):
         cells = [c.strip() for c in line.strip().strip("|").split("|")]
-        if len(cells) >= 4 and cells[0] == "traffic" and cells[1] == kernel_name:
-            if cells[3] != digest:
-                log(f"traffic: {kernel_name} changed since its counters were taken")
-                return None
-            return float(cells[2])
+        if len(cells) < 4 or cells[1] != kernel_name:
+            continue
+        tag, _, files = cells[0].partition(" of ")
+        if tag != what:
+            continue
+        h = hashlib.sha256()
+        for f in files.split() or ["kernels.hip"]:
+            with open(os.path.join(csrc, f), "rb") as src:
+                h.update(src.read())
+        if cells[3] != h.hexdigest()[:16]:
+            log(f"{what}: {kernel_name} changed since it was measured")
+            return None
+        return float(cells[2])
     return None
+
+
+def stored_traffic(kernel_name):
+    """HBM bytes per launch of `kernel_name` from the committed rocprofv3 PMC
+    summary (FETCH_SIZE + WRITE_SIZE scaled by the copy-kernel calibration)."""
+    return stored_value(os.path.join(ROOT, "profiles", "traffic.md"), "traffic", kernel_name)
 
 
 def stored_trace(kernel_name):
     """Average duration (us) per launch of `kernel_name` in the committed
-    rocprofv3 kernel trace of the measured workload, or None if there is
-    none or the kernel source changed since the trace was taken."""
-    import hashlib
-    path = os.path.join(ROOT, "profiles", "kernels_register_128cubed_band32.md")
-    src = os.path.join(ROOT, "paper_1807_11560_amd", "csrc", "kernels.hip")
-    if not os.path.exists(path):
-        return None
-    digest = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
-    for line in open(path):
-        cells = [c.strip() for c in line.strip().strip("|").split("|")]
-        if len(cells) >= 4 and cells[0] == "trace" and cells[1] == kernel_name:
-            if cells[3] != digest:
-                log(f"trace: {kernel_name} changed since the kernel trace was taken")
-                return None
-            return float(cells[2])
-    return None
+    rocprofv3 kernel trace of the measured workload."""
+    return stored_value(os.path.join(ROOT, "profiles", "kernels_register_128cubed_band32.md"), "trace", kernel_name)
 
 
 def _cpu_model():

@@ -46,8 +46,9 @@ SYMBOL_L = 0
 SYMBOL_K = 1
 KF_SYNTH, KF_GRID, KF_SL, KF_INV0, KF_COLUMN, KF_PRODS = 1, 2, 3, 4, 5, 6
 KF_INV0_GRID, KF_FWD1_GRID, KF_FWD0_GRID, KF_SRC = 7, 8, 9, 10
-KERNEL_FAMILIES = {KF_SYNTH: "k_synth", KF_GRID: "k_gridstep", KF_SL: "k_sl", KF_INV0: "k_inv0 (padded grid)",
-                   KF_COLUMN: "k_colstep", KF_PRODS: "k_prods", KF_INV0_GRID: "k_inv0 (image grid)",
+# what a family's launches are, by the kernels of the sizes that they serve
+KERNEL_FAMILIES = {KF_SYNTH: "k_synth_chain", KF_GRID: "k_gridstep", KF_SL: "k_sl", KF_INV0: "k_inv0 (padded grid)",
+                   KF_COLUMN: "k_colstep", KF_PRODS: "k_step, k_prods", KF_INV0_GRID: "k_inv0 (image grid)",
                    KF_FWD1_GRID: "k_fwd1", KF_FWD0_GRID: "k_fwd0", KF_SRC: "k_src_fwd2"}
 
 
