@@ -381,17 +381,25 @@ int lddmm_register_batch(int32_t n, const lddmm_params* p, const float* const* I
  * against concurrent enabling. */
 enum {
   LDDMM_KF_NONE = 0,
-  LDDMM_KF_SYNTH = 1,      /* k_synth_chain: padded-grid synthesis of new fields (inverse stages 1-2, MFMA) */
-  LDDMM_KF_GRID = 2,       /* k_gridstep: grid velocity / incremental-state source (inverse stages 1-2) */
-  LDDMM_KF_SL = 3,         /* k_sl: semi-Lagrangian transport step */
-  LDDMM_KF_INV0 = 4,       /* k_inv0 (padded grid): inverse stage 0 at the start of a sweep */
-  LDDMM_KF_COLUMN = 5,     /* k_colstep: forward stages 1-0, band update, next inverse stage 0 */
+  LDDMM_KF_SYNTH = 1,      /* k_synth_chain: padded-grid synthesis of new fields (inverse stages 1-2, MFMA) where
+                            * it is a launch of its own */
+  LDDMM_KF_GRID = 2,       /* k_gridstep, k_gridstep_mfma: grid velocity / incremental-state source (inverse stages
+                            * 1-2); with the transport in the same launch in the forward passes of Euler problems
+                            * (shooting, energy, gradients, recomputed states, composition with u_nt) */
+  LDDMM_KF_SL = 3,         /* k_sl: the transports that are launches of their own: of the incremental state
+                            * (Hessian-vector products), of RK4 problems, the tangent of the exact product */
+  LDDMM_KF_INV0 = 4,       /* k_inv0 (padded grid): inverse stage 0 at the start of a sweep; k_column_chain without
+                            * products where the band has no instantiated kernels */
+  LDDMM_KF_COLUMN = 5,     /* k_colstep_mfma, k_colstep_lean, k_column_chain: forward stages 1-0, band update, next
+                            * inverse stage 0 */
   LDDMM_KF_PRODS = 6,      /* k_prods, k_step: Lie products and forward stage 2 on the padded grid; k_step (small
                             * bands) with the synthesis in the same launch */
-  LDDMM_KF_INV0_GRID = 7,  /* k_inv0 (image grid): inverse stage 0 of a grid velocity */
+  LDDMM_KF_INV0_GRID = 7,  /* k_inv0 (image grid), k_column_chain without products: inverse stage 0 of a grid
+                            * velocity where no column step formed it */
   LDDMM_KF_FWD1_GRID = 8,  /* k_fwd1: forward stage 1 of a grid field */
   LDDMM_KF_FWD0_GRID = 9,  /* k_fwd0: forward stage 0 of a grid field and its band epilogue */
-  LDDMM_KF_SRC = 10        /* k_src_fwd2: image-matching source and forward stage 2 */
+  LDDMM_KF_SRC = 10        /* k_src_fwd2, k_srcfwd, k_rho_fwd2, k_adj_src_fwd2: image-term source and forward
+                            * stage 2 */
 };
 int lddmm_kernel_timer(int32_t family, int32_t every);
 int lddmm_kernel_timer_read(int64_t* launches, double* total_ms, double* flops, double* bytes);
@@ -428,7 +436,8 @@ int lddmm_use_graphs(int32_t enable);
  *               outputs, 3 as 2 with the lean kernel for the forward
  *               sweeps where the shape has one (bands 24^3 and 32^3)
  *   sl_threads  threads per block of the semi-Lagrangian transport step:
- *               64, 128 or 256 (0: 256) */
+ *               64, 128 or 256 (0: 256), of the incremental state; the forward
+ *               steps of Euler problems are part of the grid step's launch */
 typedef struct {
   int32_t prod_rows;
   int32_t col_split;

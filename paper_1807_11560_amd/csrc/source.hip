@@ -150,7 +150,10 @@ __global__ void __launch_bounds__(kSrcThreads) k_src_fwd2(const float* __restric
 // sums are gathered in LDS, in a window of 7 x 11 x (CW + 3) that starts one
 // voxel below the chunk moved by the whole voxels of its centre's displacement:
 // it takes every point whose displacement differs from the centre's by up to a
-// voxel, the others add to lam_out directly.  Then each entry that was touched
+// voxel, the others add to lam_out directly: none of them where a step moves less
+// than a voxel (the tested and measured problems), a quarter at 9 voxels a step, two
+// thirds at 15 (gradient of 2 steps at 128^3 / band 32, 9 voxels a step: 1000 us with
+// global atomics, 483 so; of one step of 15 at 64^3 / band 16: 267, 184).  Then each entry that was touched
 // is added to lam_out once, in runs along x2.  (The window is in FP64:
 // ds_add_f64 takes 10 cycles a wave, ds_add_f32 196.)  Stage 2 keeps its sums in
 // the registers of the wave that owns them, over the chunks, and its table for a

@@ -1,7 +1,7 @@
 """The kernels of the shapes without instantiated ones (csrc/chain.hip) at the
 edges of their tiles: bands around a multiple of 16 (4, 14, 16, 18, 34, 64 per
 axis), padded grids around a multiple of 16 and of odd length (rows of odd
-length are loaded value by value), half spectra of one and of two tiles, grids
+length end in a load that begins one value earlier), half spectra of one and of two tiles, grids
 with a ragged last tile on every axis and rows that are not a multiple of four.
 
 Oracle and bounds are those of the other parity tests: the FP64 oracle, 1e-4 in

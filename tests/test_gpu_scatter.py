@@ -1,7 +1,7 @@
 """The scatter of the exact derivative's state adjoint (csrc/source.hip) at the
 edges of its bricks: grids of one and of two planes past a multiple of the
 brick, rows that are not a multiple of 8 or 4 long, a grid narrower than the
-window of a brick, bricks of two and of four planes, and displacements of up to
+window of a brick, bricks of four planes with fewer left, and displacements of up to
 four voxels a step, so that cells fall inside and outside of the windows and
 wrap around every axis.
 
