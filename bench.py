@@ -315,6 +315,15 @@ def dominant_family(L, run):
     return max(fam_ms, key=fam_ms.get)
 
 
+def on_band(v, band):
+    """A band field [3][...] on another band: the frequencies both hold, zero elsewhere."""
+    out = np.zeros((v.shape[0],) + tuple(band), dtype=v.dtype)
+    f = [np.arange(1 - min(a, b) // 2, min(a, b) // 2) for a, b in zip(v.shape[1:], band)]
+    out[(slice(None),) + np.ix_(*[q % n for q, n in zip(f, band)])] = \
+        v[(slice(None),) + np.ix_(*[q % n for q, n in zip(f, v.shape[1:])])]
+    return out
+
+
 def select_tiles(args, L, jobs):
     """The launch shapes of the timed region: the tile table loaded from
     --tiles, else the autotuner's choice for each problem shape (one untimed
@@ -501,7 +510,8 @@ def main():
     I1 = L.shoot(prob_img, I0, vstar, L.Workspace(prob_img, dev))
     torch.cuda.synchronize()
     log(f"workload ready: grid {prob.grid} band {prob.band} ws {ws.nbytes / 2**20:.0f} MiB")
-    tiles = select_tiles(args, L, [(prob, I0, I1, 0.5 * vstar, ws)])
+    v0 = torch.from_numpy(0.5 * on_band(w["v_star"], band)).to(torch.complex64).to(dev)
+    tiles = select_tiles(args, L, [(prob, I0, I1, v0, ws)])
     L.use_graphs(bool(args.graphs))
 
     def registration():

@@ -1,5 +1,5 @@
 """bench.py's stored profile values: a line holds for the source files that its kernel is built from, and the
-kernel families are named after kernels that exist."""
+kernel families are named after kernels that exist.  And its initial velocity on another band (--band)."""
 
 import hashlib
 import os
@@ -10,6 +10,8 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
+
+import numpy as np  # noqa: E402
 
 import bench  # noqa: E402
 from paper_1807_11560_amd import lddmm as L  # noqa: E402
@@ -45,3 +47,18 @@ def test_families_are_named_after_kernels():
         for k in re.findall(r"k_\w+", name):
             # a kernel, or the stem of several
             assert k in kernels or sum(q.startswith(k + "_") for q in kernels) > 1, k
+
+
+@pytest.mark.parametrize("band", [(4, 6, 8), (12, 10, 8), (8, 8, 8), (16, 4, 8)])
+def test_a_velocity_on_another_band_keeps_the_common_frequencies(band):
+    rng = np.random.default_rng(0)
+    v = rng.standard_normal((3, 8, 8, 8)) + 1j * rng.standard_normal((3, 8, 8, 8))
+    v[:, 4], v[:, :, 4], v[:, :, :, 4] = 0, 0, 0  # a band field holds nothing at -K/2
+    got = bench.on_band(v, band)
+    assert got.shape == (3,) + band
+    for k in np.ndindex(*band):
+        f = [q if q < n // 2 else q - n for q, n in zip(k, band)]
+        common = all(abs(q) < min(n, 8) // 2 for q, n in zip(f, band))
+        assert np.array_equal(got[(slice(None),) + k], v[(slice(None),) + tuple(f)] if common else np.zeros(3))
+    if band == (8, 8, 8):
+        assert np.array_equal(got, v)
