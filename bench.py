@@ -658,6 +658,8 @@ def main():
             log(f"{other['dtype']} accuracy against the oracle: {other['accuracy_vs_fp64']}")
 
     name = L.KERNEL_FAMILIES[dominant]
+    # the committed counters and trace are of this workload
+    default_workload = (args.state == "image" and band == tuple(pp["band"]) and prec == L.FP32)
     res = {
         "metric": METRIC,
         "value": hvps / T,
@@ -698,12 +700,12 @@ def main():
         "workspace_mib": ws.nbytes / 2**20,
         "tiles": tiles,
         "graphs": bool(args.graphs),
-        "roofline": roofline(dominant, name, launches, kms, kfl, kby, stored_traffic(name)),
+        "roofline": roofline(dominant, name, launches, kms, kfl, kby,
+                             stored_traffic(name) if default_workload else None),
         "cpu_baseline": cpu,
     }
     # the same kernel's average duration in the committed kernel trace of this workload (the
     # events of a timed launch also span the command processor's work around it)
-    default_workload = (args.state == "image" and band == tuple(pp["band"]) and prec == L.FP32)
     tr = stored_trace(name) if default_workload else None
     if tr:
         rl = res["roofline"]
